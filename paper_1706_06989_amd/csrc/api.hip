@@ -51,16 +51,22 @@ static void release(Ctx& c, DevBuf& b) {
   }
 }
 
-// an arena block of `bytes` (a multiple of kArenaAlign): the first free block
-// that holds it
+// an arena block of `bytes` (a multiple of kArenaAlign): the start of the
+// first free block that holds it, or (top) the end of the last one; nullptr
+// when none does
+static void* arena_take(Ctx& c, size_t bytes, bool top = false) {
+  auto hit = c.arena_free.end();
+  for (auto it = c.arena_free.begin(); it != c.arena_free.end(); ++it)
+    if (it->second >= bytes && (top || hit == c.arena_free.end())) hit = it;
+  if (hit == c.arena_free.end()) return nullptr;
+  const size_t off = hit->first, rest = hit->second - bytes;
+  c.arena_free.erase(hit);
+  if (rest) c.arena_free.emplace(top ? off : off + bytes, rest);
+  return c.arena + (top ? off + rest : off);
+}
+
 static void* arena_alloc(Ctx& c, size_t bytes) {
-  for (auto it = c.arena_free.begin(); it != c.arena_free.end(); ++it) {
-    if (it->second < bytes) continue;
-    const size_t off = it->first, rest = it->second - bytes;
-    c.arena_free.erase(it);
-    if (rest) c.arena_free.emplace(off + bytes, rest);
-    return c.arena + off;
-  }
+  if (void* p = arena_take(c, bytes)) return p;
   size_t largest = 0, total = 0;
   for (const auto& f : c.arena_free) {
     largest = std::max(largest, f.second);
@@ -70,6 +76,18 @@ static void* arena_alloc(Ctx& c, size_t bytes) {
                                std::to_string(c.arena_cap >> 20) + " MiB static array (request of " +
                                std::to_string(bytes) + " bytes; " + std::to_string(total) + " bytes free, " +
                                "largest block " + std::to_string(largest) + ")");
+}
+
+// grow an arena block in place into the free block behind it
+static bool arena_extend(Ctx& c, DevBuf& b, size_t want) {
+  const size_t end = (size_t)((char*)b.p - c.arena) + b.cap, more = want - b.cap;
+  auto it = c.arena_free.find(end);
+  if (it == c.arena_free.end() || it->second < more) return false;
+  const size_t rest = it->second - more;
+  c.arena_free.erase(it);
+  if (rest) c.arena_free.emplace(end + more, rest);
+  b.cap = want;
+  return true;
 }
 
 static void* alloc(Ctx& c, size_t bytes) {
@@ -113,26 +131,31 @@ void* ensure(Ctx& c, DevBuf& b, size_t bytes) {
   return b.p;
 }
 
+void* ensure_top(Ctx& c, DevBuf& b, size_t bytes) {
+  if (!c.arena) return ensure(c, b, bytes);
+  if (b.cap >= bytes) return b.p;
+  release(c, b);
+  const size_t want = (std::max<size_t>(bytes, 8) + kArenaAlign - 1) & ~(kArenaAlign - 1);
+  b.p = arena_take(c, want, true);
+  if (!b.p) b.p = arena_alloc(c, want);  // reports the shortage
+  b.cap = want;
+  return b.p;
+}
+
 void* ensure_keep(Ctx& c, DevBuf& b, size_t bytes, size_t keep) {
   if (bytes == 0) bytes = 8;
   if (b.cap >= bytes) return b.p;
   size_t want = bytes + bytes / 4;
+  void* p = nullptr;
   if (c.arena) {
-    want = (want + kArenaAlign - 1) & ~(kArenaAlign - 1);
-    // an arena block followed by a large enough free block grows in place
-    if (b.p && in_arena(c, b.p)) {
-      const size_t end = (size_t)((char*)b.p - c.arena) + b.cap, more = want - b.cap;
-      auto it = c.arena_free.find(end);
-      if (it != c.arena_free.end() && it->second >= more) {
-        const size_t rest = it->second - more;
-        c.arena_free.erase(it);
-        if (rest) c.arena_free.emplace(end + more, rest);
-        b.cap = want;
-        return b.p;
-      }
-    }
+    // with headroom where there is room for it, else without
+    const size_t exact = (bytes + kArenaAlign - 1) & ~(kArenaAlign - 1);
+    want = c.arena_tight ? exact : (want + kArenaAlign - 1) & ~(kArenaAlign - 1);
+    if (b.p && in_arena(c, b.p) && (arena_extend(c, b, want) || arena_extend(c, b, exact))) return b.p;
+    p = arena_take(c, want);
+    if (!p) want = exact;
   }
-  void* p = alloc(c, want);
+  if (!p) p = alloc(c, want);
   if (b.p && keep) AMFMM_HIP(hipMemcpyAsync(p, b.p, std::min(keep, b.cap), hipMemcpyDeviceToDevice, c.stream));
   if (b.p) {
     AMFMM_HIP(hipStreamSynchronize(c.stream));
@@ -147,7 +170,7 @@ void sync(Ctx& c) { AMFMM_HIP(hipStreamSynchronize(c.stream)); }
 
 static DevBuf* all_bufs(Ctx& c, int i) {
   DevBuf* v[] = {&c.pos4, &c.keys, &c.perm, &c.keys2, &c.perm2, &c.bbox, &c.scratch, &c.scratch2, &c.hist,
-                 &c.c_begin, &c.c_count, &c.c_parent, &c.c_child0, &c.c_nchild, &c.leaves, &c.geo, &c.mom,
+                 &c.c_begin, &c.c_count, &c.c_parent, &c.c_child0, &c.c_nchild, &c.c_level, &c.leaves, &c.leafof, &c.geo, &c.mom,
                  &c.msum, &c.loc, &c.far_start, &c.far_count, &c.far_src, &c.near_start, &c.near_count,
                  &c.near_src, &c.fx, &c.fy, &c.fx2, &c.fy2, &c.fcnt, &c.grp, &c.walkrec, &c.fsave, &c.gsave, &c.counters, &c.gqueue, &c.stage, &c.farrec, &c.gmin, &c.model, &c.mlp_tmp, &c.mlp_part,
                  &c.mlp_grad, &c.mono, &c.locg};
@@ -338,7 +361,7 @@ int amfmm_create(const amfmm_options* opt, void* stream, amfmm_ctx** out) {
     delete ctx;
     return AMFMM_E_HIP;
   }
-  if (hipHostMalloc((void**)&ctx->c.pinned, 8 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&ctx->c.pinned, amfmm::kPinWords * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
     delete ctx;
     return AMFMM_E_HIP;
   }
@@ -459,13 +482,13 @@ static int build_tree_impl(Ctx& c, int64_t n, const double* x, const double* y, 
   c.have_tree = c.have_moments = c.have_lists = false;
   c.ev_used = 0;
   amfmm::mark(c, amfmm::kPhValidate);
-  int st = amfmm::bbox_validate(c, x, y, z, m, n);
-  if (st == AMFMM_E_NONFINITE) return fail(c, st, "non-finite position or mass");
-  if (st != AMFMM_OK) return fail(c, st, "masses must be positive");
+  amfmm::bbox_start(c, x, y, z, m, n);
   amfmm::mark(c, amfmm::kPhSort);
   amfmm::build_keys_sort(c, x, y, z, m, n);
   amfmm::mark(c, amfmm::kPhTree);
-  amfmm::build_levels(c);
+  const int st = amfmm::build_levels(c);
+  if (st == AMFMM_E_NONFINITE) return fail(c, st, "non-finite position or mass");
+  if (st != AMFMM_OK) return fail(c, st, "masses must be positive");
   amfmm::mark(c, amfmm::kPhEnd);
   c.have_tree = true;
   return AMFMM_OK;
@@ -807,6 +830,7 @@ int amfmm_solve_gravity_noalloc(amfmm_ctx* ctx, int64_t n, const double* x, cons
       ~Saved() {
         for (int i = 0; amfmm::DevBuf* b = amfmm::all_bufs(c, i); ++i) *b = bufs[(size_t)i];
         c.arena = nullptr;
+        c.arena_tight = false;
         c.arena_cap = 0;
         c.arena_free.clear();
         c.have_tree = c.have_moments = c.have_lists = false;
@@ -821,10 +845,21 @@ int amfmm_solve_gravity_noalloc(amfmm_ctx* ctx, int64_t n, const double* x, cons
     } saved(c);
     c.arena = amfmm::device_scratch(c.device);
     c.arena_cap = amfmm::kNoAllocBytes;
-    c.arena_free.clear();
-    c.arena_free.emplace(0, amfmm::kNoAllocBytes);
     c.ev_used = 0;
-    return solve_impl(c, n, x, y, z, m, theta, ax, ay, az, pot);
+    // a solve that runs out of room is run once more with the walk's transient
+    // buffers held small (more of its chunks are then walked twice)
+    for (c.arena_tight = false;; c.arena_tight = true) {
+      for (int i = 0; amfmm::DevBuf* b = amfmm::all_bufs(c, i); ++i)
+        if (b != &c.model) *b = amfmm::DevBuf{};
+      c.arena_free.clear();
+      c.arena_free.emplace(0, amfmm::kNoAllocBytes);
+      c.hint_n = 0;
+      try {
+        return solve_impl(c, n, x, y, z, m, theta, ax, ay, az, pot);
+      } catch (const Error& e) {
+        if (e.code != AMFMM_E_OOM || c.arena_tight) throw;
+      }
+    }
   });
 }
 

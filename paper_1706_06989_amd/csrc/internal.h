@@ -18,6 +18,10 @@ constexpr int kMom = 18;       // per cell: M, M_ij (6), M_ijk (10), pad
 constexpr int kLoc = 24;       // per cell: C (1), C_k (3), C_kl (6), C_klm (10), g_c (3), pad
 constexpr int kLocGen = 40;    // expansion order 4: 35 local coefficients, g_c (3), pad
 
+// words of the pinned read-back buffer: walk totals, bounding box and input
+// flags (8 doubles), cells per level (2 per level)
+constexpr int kPinWalk = 0, kPinBox = 16, kPinTree = 24, kPinWords = 24 + 2 * (kMaxLevel + 1);
+
 // index of a symmetric pair / triple inside the packed arrays
 //   pairs   xx xy xz yy yz zz
 //   triples xxx xxy xxz xyy xyz xzz yyy yyz yzz zzz
@@ -69,7 +73,9 @@ struct Ctx {
   int32_t ncells = 0, depth = 0, nleaves = 0;
   std::vector<int32_t> level_start;  // host copy, size depth+2
   DevBuf c_begin, c_count, c_parent, c_child0, c_nchild;  // int32
+  DevBuf c_level;  // int8 level per cell
   DevBuf leaves;   // int32 ids of leaf cells
+  DevBuf leafof;   // int32 leaf cell of every (sorted) particle
   DevBuf geo;      // double4 per cell
   DevBuf mom;      // kMom doubles per cell
   DevBuf msum;     // double4 per cell: sum m*X (x,y,z), unused
@@ -103,7 +109,8 @@ struct Ctx {
   std::vector<std::pair<int32_t, int32_t>> near_pairs_host;
   bool near_pairs_valid = false;
   int grp_cur = 0;
-  int64_t* pinned = nullptr;  // small pinned host buffer for read-backs
+  int64_t* pinned = nullptr;  // kPinWords pinned host words for read-backs (kernels write them)
+  double box[6] = {};         // bounding box of the tree's particles: lo, hi
   int64_t far_evals = 0;      // directed far-field evaluations of the last solve
   int64_t far_launches = 0, near_launches = 0;  // kernel launches of the last evaluation
   int64_t pass_launches = 0;    // launches of the walk's pass kernel in the last walk
@@ -128,6 +135,7 @@ struct Ctx {
   // their neighbours), and no timing events are recorded
   char* arena = nullptr;
   size_t arena_cap = 0;
+  bool arena_tight = false;  // second attempt of a solve that did not fit
   std::map<size_t, size_t> arena_free;  // offset -> bytes of each free block
 };
 
@@ -137,6 +145,9 @@ size_t free_device_bytes(Ctx& c);
 
 // allocate (grow-only) a device buffer of at least `bytes`; contents are lost on growth
 void* ensure(Ctx& c, DevBuf& b, size_t bytes);
+// ensure, in an arena from its top end: the walk's transient buffers stay out
+// of the way of the lists that grow beside them
+void* ensure_top(Ctx& c, DevBuf& b, size_t bytes);
 // grow keeping the first `keep` bytes
 void* ensure_keep(Ctx& c, DevBuf& b, size_t bytes, size_t keep);
 template <typename T>
@@ -158,12 +169,13 @@ void radix_sort(Ctx& c, uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32
                 int64_t n, int bits);
 
 // ---- tree.hip ----
-// validate + bounding box; returns 0 or an amfmm_status (reads back flags)
-int bbox_validate(Ctx& c, const double* x, const double* y, const double* z, const double* m,
-                  int64_t n);
+// bounding box and input checks (enqueued: build_levels reads the result)
+void bbox_start(Ctx& c, const double* x, const double* y, const double* z, const double* m, int64_t n);
 void build_keys_sort(Ctx& c, const double* x, const double* y, const double* z, const double* m,
                      int64_t n);
-void build_levels(Ctx& c);
+// cells of all levels; synchronises once; returns 0, or the amfmm_status of a
+// non-finite or non-positive input (the keys of such inputs are arbitrary but valid)
+int build_levels(Ctx& c);
 
 // ---- moments.hip ----
 void upward_pass(Ctx& c);

@@ -2,7 +2,7 @@
 // (eq. quad) and octupole M_ijk about Z, and R_max.
 //
 //  * leaves: one thread per leaf, sequential over its particles in key order;
-//  * parents: one thread per cell per level, bottom-up, summing the children in
+//  * parents: 8 lanes per cell, level by level, summing the children in
 //    octant order (mass and first moment), then shifting the children's M_ij,
 //    M_ijk to the parent's centre (exact for moments about a centre of mass);
 //  * R_max: exact largest distance to Z over the cell's particles; every
@@ -73,36 +73,53 @@ __global__ void __launch_bounds__(kBS) k_leaf_moments(const double4* __restrict_
   o[17] = 0.0;
 }
 
-__global__ void __launch_bounds__(kBS) k_m2m(int32_t c0, int32_t nl, const int32_t* __restrict__ ch0,
-                                             const int32_t* __restrict__ nch, double4* __restrict__ geo,
-                                             double* __restrict__ mom, double4* __restrict__ msum) {
-  int32_t i = blockIdx.x * kBS + threadIdx.x;
-  if (i >= nl) return;
-  int32_t c = c0 + i;
-  int32_t k = nch[c];
-  if (k == 0) return;
-  int32_t f = ch0[c];
-  double M = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
-  for (int32_t q = f; q < f + k; ++q) {
-    double4 s = msum[q];
-    M += s.w;
-    Sx += s.x;
-    Sy += s.y;
-    Sz += s.z;
+// One parent from its children, 8 lanes per parent (lane q of the group holds
+// child q).  The sums over the children run in octant order: mass and first
+// moment by passing the children's values through the group, the shifted
+// M_ij and M_ijk through the group's rows of LDS, summed by 8 lanes two
+// components each.  One thread per parent took 8 dependent rounds of loads
+// (12-15 us a level however small); this takes one.
+constexpr int kM2MGroup = 8;
+constexpr int kM2MPad = 17;  // LDS row of one child: 6 + 10 values, padded
+
+__device__ inline void m2m_parent(int32_t c, int lane8, double (*rows)[kM2MPad], const int32_t* __restrict__ ch0,
+                                  const int32_t* __restrict__ nch, double4* geo, double* mom, double4* msum,
+                                  bool valid) {
+  const int32_t k = valid ? nch[c] : 0;
+  const int32_t q = (k ? ch0[c] : 0) + lane8;
+  const bool has = lane8 < k;
+  double4 s = make_double4(0.0, 0.0, 0.0, 0.0), g = s;
+  double cm[17];
+#pragma unroll
+  for (int u = 0; u < 17; ++u) cm[u] = 0.0;
+  if (has) {
+    s = msum[q];
+    g = geo[q];
+#pragma unroll
+    for (int u = 0; u < 17; ++u) cm[u] = mom[(int64_t)q * kMom + u];
   }
-  double Zx = Sx / M, Zy = Sy / M, Zz = Sz / M;
-  double M2[6] = {}, M3[10] = {};
-  for (int32_t q = f; q < f + k; ++q) {
-    double4 g = geo[q];
-    const double* cm = mom + (int64_t)q * kMom;
-    double mc = cm[0];
-    double d[3] = {g.x - Zx, g.y - Zy, g.z - Zz};
+  double M = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
+#pragma unroll
+  for (int j = 0; j < kM2MGroup; ++j) {
+    const double w = __shfl(s.w, j, kM2MGroup), x = __shfl(s.x, j, kM2MGroup);
+    const double y = __shfl(s.y, j, kM2MGroup), z = __shfl(s.z, j, kM2MGroup);
+    if (j < k) {
+      M += w;
+      Sx += x;
+      Sy += y;
+      Sz += z;
+    }
+  }
+  const double Zx = Sx / M, Zy = Sy / M, Zz = Sz / M;
+  if (has) {
+    const double mc = cm[0];
+    const double d[3] = {g.x - Zx, g.y - Zy, g.z - Zz};
     const double* a = cm + 1;  // child M_ij
     const double* t = cm + 7;  // child M_ijk
     // M_ij += Mc_ij + Mc d_i d_j
     const int I2[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
 #pragma unroll
-    for (int u = 0; u < 6; ++u) M2[u] += a[u] + mc * d[I2[u][0]] * d[I2[u][1]];
+    for (int u = 0; u < 6; ++u) rows[lane8][u] = a[u] + mc * d[I2[u][0]] * d[I2[u][1]];
     // M_ijk += Mc_ijk + Mc_ij d_k + Mc_jk d_i + Mc_ik d_j + Mc d_i d_j d_k
     const int I3[10][3] = {{0, 0, 0}, {0, 0, 1}, {0, 0, 2}, {0, 1, 1}, {0, 1, 2},
                            {0, 2, 2}, {1, 1, 1}, {1, 1, 2}, {1, 2, 2}, {2, 2, 2}};
@@ -113,34 +130,58 @@ __global__ void __launch_bounds__(kBS) k_m2m(int32_t c0, int32_t nl, const int32
 #pragma unroll
     for (int u = 0; u < 10; ++u) {
       int ii = I3[u][0], jj = I3[u][1], kk = I3[u][2];
-      M3[u] += t[u] + p2(ii, jj) * d[kk] + p2(jj, kk) * d[ii] + p2(ii, kk) * d[jj] +
-               mc * d[ii] * d[jj] * d[kk];
+      rows[lane8][6 + u] = t[u] + p2(ii, jj) * d[kk] + p2(jj, kk) * d[ii] + p2(ii, kk) * d[jj] +
+                           mc * d[ii] * d[jj] * d[kk];
     }
   }
-  geo[c] = make_double4(Zx, Zy, Zz, 0.0);
-  msum[c] = make_double4(Sx, Sy, Sz, M);
-  double* o = mom + (int64_t)c * kMom;
-  o[0] = M;
-  for (int q = 0; q < 6; ++q) o[1 + q] = M2[q];
-  for (int q = 0; q < 10; ++q) o[7 + q] = M3[q];
-  o[17] = 0.0;
+  __syncthreads();
+  if (k) {
+    double* o = mom + (int64_t)c * kMom;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int u = 2 * lane8 + h;
+      double v = 0.0;
+      for (int j = 0; j < k; ++j) v += rows[j][u];
+      o[1 + u] = v;
+    }
+    if (lane8 == 0) {
+      geo[c] = make_double4(Zx, Zy, Zz, 0.0);
+      msum[c] = make_double4(Sx, Sy, Sz, M);
+      o[0] = M;
+      o[17] = 0.0;
+    }
+  }
 }
 
-__global__ void __launch_bounds__(kBS) k_leaf_of(const int32_t* __restrict__ leaves, int32_t nleaves,
-                                                 const int32_t* __restrict__ beg, const int32_t* __restrict__ cnt,
-                                                 int32_t* __restrict__ leafof) {
-  int32_t i = blockIdx.x * kBS + threadIdx.x;
-  if (i >= nleaves) return;
-  int32_t c = leaves[i];
-  for (int32_t p = beg[c]; p < beg[c] + cnt[c]; ++p) leafof[p] = c;
+__global__ void __launch_bounds__(kBS) k_m2m(int32_t c0, int32_t nl, const int32_t* __restrict__ ch0,
+                                             const int32_t* __restrict__ nch, double4* geo, double* mom,
+                                             double4* msum) {
+  __shared__ double rows[kBS / kM2MGroup][kM2MGroup][kM2MPad];
+  const int32_t i = (blockIdx.x * kBS + threadIdx.x) / kM2MGroup;
+  m2m_parent(c0 + i, threadIdx.x % kM2MGroup, rows[threadIdx.x / kM2MGroup], ch0, nch, geo, mom, msum, i < nl);
 }
 
-__global__ void k_cell_level(const int32_t* __restrict__ level_start, int nlev, int32_t nc, int8_t* __restrict__ lev) {
-  int32_t c = blockIdx.x * kBS + threadIdx.x;
-  if (c >= nc) return;
-  int l = 0;
-  while (l + 1 < nlev && level_start[l + 1] <= c) ++l;
-  lev[c] = (int8_t)l;
+// The top levels (those of at most kTopCells cells), bottom-up, in one block:
+// a launch each costs more than their work.
+constexpr int kTopBS = 1024;
+constexpr int kTopCells = 2 * kTopBS / kM2MGroup;
+struct TopLevels {
+  int32_t n;                         // levels 0 .. n-1
+  int32_t start[kMaxLevel + 2];
+};
+
+__global__ void __launch_bounds__(kTopBS) k_m2m_top(TopLevels t, const int32_t* __restrict__ ch0,
+                                                    const int32_t* __restrict__ nch, double4* geo, double* mom,
+                                                    double4* msum) {
+  __shared__ double rows[kTopBS / kM2MGroup][kM2MGroup][kM2MPad];
+  for (int l = t.n - 1; l >= 0; --l) {
+    for (int32_t b = t.start[l]; b < t.start[l + 1]; b += kTopBS / kM2MGroup) {
+      const int32_t c = b + threadIdx.x / kM2MGroup;
+      m2m_parent(c, threadIdx.x % kM2MGroup, rows[threadIdx.x / kM2MGroup], ch0, nch, geo, mom, msum,
+                 c < t.start[l + 1]);
+      __syncthreads();  // the parents written, the rows read
+    }
+  }
 }
 
 __global__ void __launch_bounds__(kBS) k_zero_u64(unsigned long long* p, int64_t n) {
@@ -148,23 +189,26 @@ __global__ void __launch_bounds__(kBS) k_zero_u64(unsigned long long* p, int64_t
   if (i < n) p[i] = 0ull;
 }
 
-// 64-particle slabs one wave of k_rmax takes, in key order
+// 64-particle slabs one wave of k_rmax takes, in key order: as many as leave
+// kRmaxWaves waves to fill the chip, at most kRmaxSlabs (a fixed 32 left
+// 100003 particles on 49 waves: 269 us).
 constexpr int kRmaxSlabs = 32;
+constexpr int64_t kRmaxWaves = 8192;
 
 // R_max^2 of every ancestor of every particle, by atomic max on the bit
 // pattern (order-preserving for non-negative doubles).  A wave takes
-// kRmaxSlabs consecutive slabs of 64 particles; on each level, lanes with
+// `slabs` consecutive slabs of 64 particles; on each level, lanes with
 // the same ancestor (contiguous, as cells are) reduce to the run's first
 // lane, and the run that reaches the slab's end stays pending in the wave
 // and joins the next slab's first run when that has the same cell.  A cell
 // of many particles so gets one atomic per wave that touches it rather than
 // one per slab (all waves otherwise meet on the same few top cells).
-__global__ void __launch_bounds__(kBS) k_rmax(const double4* __restrict__ pos, int64_t n,
+__global__ void __launch_bounds__(kBS) k_rmax(const double4* __restrict__ pos, int64_t n, int slabs,
                                               const int32_t* __restrict__ leafof, const int32_t* __restrict__ par,
                                               const int8_t* __restrict__ lev, const double4* __restrict__ geo,
                                               unsigned long long* __restrict__ r2max) {
   const int lane = threadIdx.x & 63;
-  const int64_t p0 = (((int64_t)blockIdx.x * kBS + threadIdx.x) >> 6) * (64 * kRmaxSlabs);
+  const int64_t p0 = (((int64_t)blockIdx.x * kBS + threadIdx.x) >> 6) * (64 * (int64_t)slabs);
   // per level, the pending run (wave-uniform): its cell (-1: none) and max
   int32_t pend_id[kMaxLevel + 1];
   double pend_r2[kMaxLevel + 1];
@@ -173,7 +217,7 @@ __global__ void __launch_bounds__(kBS) k_rmax(const double4* __restrict__ pos, i
     pend_id[l] = -1;
     pend_r2[l] = -1.0;
   }
-  for (int s = 0; s < kRmaxSlabs; ++s) {
+  for (int s = 0; s < slabs; ++s) {
     const int64_t p = p0 + (int64_t)s * 64 + lane;
     if (p0 + (int64_t)s * 64 >= n) break;  // wave-uniform
     const bool valid = p < n;
@@ -249,34 +293,28 @@ void upward_pass(Ctx& c) {
   hipLaunchKernelGGL(k_leaf_moments, dim3(blocks_for(c.nleaves, kBS)), dim3(kBS), 0, c.stream,
                      (const double4*)c.pos4.p, as<int32_t>(c.leaves), c.nleaves, beg, cnt, geo, mom, msum);
   AMFMM_HIP(hipGetLastError());
-  for (int l = c.depth - 1; l >= 0; --l) {
+  TopLevels top{};
+  while (top.n <= c.depth && c.level_start[top.n + 1] - c.level_start[top.n] <= kTopCells) ++top.n;
+  std::copy(c.level_start.begin(), c.level_start.end(), top.start);
+  for (int l = c.depth - 1; l >= top.n; --l) {
     int32_t c0 = c.level_start[l], nl = c.level_start[l + 1] - c0;
-    hipLaunchKernelGGL(k_m2m, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, c0, nl,
+    hipLaunchKernelGGL(k_m2m, dim3(blocks_for((int64_t)nl * kM2MGroup, kBS)), dim3(kBS), 0, c.stream, c0, nl,
                        as<int32_t>(c.c_child0), as<int32_t>(c.c_nchild), geo, mom, msum);
     AMFMM_HIP(hipGetLastError());
   }
-  // R_max: scratch = leafof (int32 n) + level (int8 nc) + r2max (u64 nc) + level_start
-  size_t nlev = c.level_start.size();
-  size_t bytes = sizeof(int32_t) * c.n + sizeof(unsigned long long) * nc + nc + 64 + sizeof(int32_t) * nlev;
-  char* s = (char*)ensure(c, c.scratch2, bytes);
-  int32_t* leafof = (int32_t*)s;
-  unsigned long long* r2 = (unsigned long long*)(s + ((sizeof(int32_t) * c.n + 7) & ~size_t(7)));
-  int32_t* ls = (int32_t*)(r2 + nc);
-  int8_t* lev = (int8_t*)(ls + nlev);
-  AMFMM_HIP(hipMemcpyAsync(ls, c.level_start.data(), sizeof(int32_t) * nlev, hipMemcpyHostToDevice, c.stream));
-  hipLaunchKernelGGL(k_cell_level, dim3(blocks_for(nc, kBS)), dim3(kBS), 0, c.stream, (const int32_t*)ls,
-                     (int)nlev, nc, lev);
-  hipLaunchKernelGGL(k_leaf_of, dim3(blocks_for(c.nleaves, kBS)), dim3(kBS), 0, c.stream,
-                     as<int32_t>(c.leaves), c.nleaves, beg, cnt, leafof);
+  hipLaunchKernelGGL(k_m2m_top, dim3(1), dim3(kTopBS), 0, c.stream, top, as<int32_t>(c.c_child0),
+                     as<int32_t>(c.c_nchild), geo, mom, msum);
+  // R_max
+  unsigned long long* r2 = (unsigned long long*)ensure(c, c.scratch2, sizeof(unsigned long long) * (size_t)nc);
   hipLaunchKernelGGL(k_zero_u64, dim3(blocks_for(nc, kBS)), dim3(kBS), 0, c.stream, r2, (int64_t)nc);
-  const int64_t rmax_waves = (c.n + 64 * kRmaxSlabs - 1) / (64 * kRmaxSlabs);
+  const int slabs = (int)std::max<int64_t>(1, std::min<int64_t>(kRmaxSlabs, c.n / (64 * kRmaxWaves)));
+  const int64_t rmax_waves = (c.n + 64 * slabs - 1) / (64 * slabs);
   hipLaunchKernelGGL(k_rmax, dim3(blocks_for(rmax_waves * 64, kBS)), dim3(kBS), 0, c.stream, (const double4*)c.pos4.p,
-                     c.n, (const int32_t*)leafof, as<int32_t>(c.c_parent), (const int8_t*)lev,
+                     c.n, slabs, as<int32_t>(c.leafof), as<int32_t>(c.c_parent), as<int8_t>(c.c_level),
                      (const double4*)geo, r2);
   hipLaunchKernelGGL(k_rmax_final, dim3(blocks_for(nc, kBS)), dim3(kBS), 0, c.stream, nc,
                      (const unsigned long long*)r2, geo);
   AMFMM_HIP(hipGetLastError());
-  // keep the cell levels for the walk and the getters
   c.have_moments = true;
 }
 

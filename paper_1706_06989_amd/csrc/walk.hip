@@ -910,11 +910,8 @@ void walk_prepare(Ctx& c, double theta) {
   ensure(c, c.grp, 2 * (sizeof(int64_t) + sizeof(int32_t)) * (size_t)c.grp_width);
   ensure(c, c.fy, sizeof(int32_t) * 16);
   c.theta = theta;
-  double box[6];
-  AMFMM_HIP(hipMemcpyAsync(box, c.bbox.p, sizeof(box), hipMemcpyDeviceToHost, c.stream));
-  AMFMM_HIP(hipStreamSynchronize(c.stream));
   double scale = 0.0;
-  for (double v : box) scale = std::max(scale, std::fabs(v));
+  for (double v : c.box) scale = std::max(scale, std::fabs(v));
   c.walk_abs_tol = 1e-9 * scale;
 }
 
@@ -1005,9 +1002,11 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
   const size_t fr = free_device_bytes(c);
   // (the staging buffer of an earlier walk is given back when it grows; in an
   // arena its block need not join the largest free one)
-  const size_t stage_limit = std::min<size_t>(fr / 3 + (c.arena ? 0 : c.stage.cap), size_t(64) << 30);
-  // global work queues: at most kGlobalQueueBytes, an eighth of an arena
-  const int64_t queue_limit = c.arena ? (int64_t)(fr / 8) : kGlobalQueueBytes;
+  const size_t stage_limit =
+      std::min<size_t>(fr / (c.arena_tight ? 12 : 3) + (c.arena ? 0 : c.stage.cap), size_t(64) << 30);
+  // global work queues: at most kGlobalQueueBytes, an eighth of an arena (both
+  // a quarter of that in the second attempt of an arena's solve)
+  const int64_t queue_limit = c.arena ? (int64_t)(fr / (c.arena_tight ? 32 : 8)) : kGlobalQueueBytes;
   double prev[3];
   bool have_prev = false;
   int64_t cand = 0;  // candidate pairs, counted once the levels are done (a batch over budget is walked again)
@@ -1054,13 +1053,13 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
       while (g > 4 * kQ && (int64_t)sizeof(int32_t) * g * kn > queue_limit) g >>= 1;
       if ((int64_t)sizeof(int32_t) * g * kn <= queue_limit) {
         qcap = (int32_t)g;
-        gq = (int32_t*)ensure(c, c.gqueue, sizeof(int32_t) * (size_t)kn * qcap);
+        gq = (int32_t*)ensure_top(c, c.gqueue, sizeof(int32_t) * (size_t)kn * qcap);
       }
     }
     StageLayout sl{};
     const size_t stage_bytes = stage_layout(c, lev, F, kn, have_prev ? prev : nullptr, stage_limit, sl);
     {
-      int64_t* st64 = (int64_t*)ensure(c, c.stage, stage_bytes);
+      int64_t* st64 = (int64_t*)ensure_top(c, c.stage, stage_bytes);
       sl.ksec = st64;
       int32_t* st = (int32_t*)(st64 + 3 * kRegions * kn);
       for (int w = 0; w < 3; ++w) {
