@@ -172,7 +172,7 @@ static DevBuf* all_bufs(Ctx& c, int i) {
   DevBuf* v[] = {&c.pos4, &c.keys, &c.perm, &c.keys2, &c.perm2, &c.bbox, &c.scratch, &c.scratch2, &c.hist,
                  &c.c_begin, &c.c_count, &c.c_parent, &c.c_child0, &c.c_nchild, &c.c_level, &c.leaves, &c.leafof, &c.geo, &c.mom,
                  &c.msum, &c.loc, &c.far_start, &c.far_count, &c.far_src, &c.near_start, &c.near_count,
-                 &c.near_src, &c.fx, &c.fy, &c.fx2, &c.fy2, &c.fcnt, &c.grp, &c.walkrec, &c.fsave, &c.gsave, &c.counters, &c.gqueue, &c.stage, &c.farrec, &c.gmin, &c.model, &c.mlp_tmp, &c.mlp_part,
+                 &c.near_src, &c.near_parts, &c.fx, &c.fy, &c.fx2, &c.fy2, &c.grp, &c.walkrec, &c.fsave, &c.gsave, &c.counters, &c.gqueue, &c.stage, &c.farrec, &c.gmin, &c.model, &c.mlp_tmp, &c.mlp_part,
                  &c.mlp_grad, &c.mono, &c.locg};
   const int nv = (int)(sizeof(v) / sizeof(v[0]));
   return i < nv ? v[i] : nullptr;
@@ -649,7 +649,7 @@ static void solve_batched(Ctx& c, double theta, double* ax, double* ay, double* 
   AMFMM_HIP(hipMemcpyAsync(fsave, c.fy.p, sizeof(int32_t) * FL, hipMemcpyDeviceToDevice, c.stream));
   AMFMM_HIP(hipStreamSynchronize(c.stream));
   const int32_t L0 = c.level_start[Ls];
-  std::vector<int64_t> bbeg(nL);
+  std::vector<int64_t> bbeg(nL + 1);
   c.walk_budget = (size_t)budget;
   int32_t x0 = 0;
   // batch size in particles: the last solve's, never above 9/10 of a size
@@ -670,9 +670,11 @@ static void solve_batched(Ctx& c, double theta, double* ax, double* ay, double* 
       bbeg[i - x0] = hbeg[i] - base;
       F += hcnt[i];
     }
+    bbeg[x1 - x0] = F;
+    c.frontier_mapped = false;
     mark(c, kPhWalk);
     group_arrays(c, &gbeg, &gcnt);
-    AMFMM_HIP(hipMemcpyAsync(gbeg, bbeg.data(), sizeof(int64_t) * (x1 - x0), hipMemcpyHostToDevice, c.stream));
+    AMFMM_HIP(hipMemcpyAsync(gbeg, bbeg.data(), sizeof(int64_t) * (x1 - x0 + 1), hipMemcpyHostToDevice, c.stream));
     AMFMM_HIP(hipMemcpyAsync(gcnt, hcnt.data() + x0, sizeof(int32_t) * (x1 - x0), hipMemcpyHostToDevice, c.stream));
     int32_t* fy = (int32_t*)ensure(c, c.fy, sizeof(int32_t) * (F + 1));
     AMFMM_HIP(hipMemcpyAsync(fy, fsave + base, sizeof(int32_t) * F, hipMemcpyDeviceToDevice, c.stream));

@@ -86,8 +86,12 @@ struct Ctx {
   int64_t n_far = 0, n_near = 0;
   DevBuf far_start, far_count, far_src;     // int32 (start as int64)
   DevBuf near_start, near_count, near_src;
+  DevBuf near_parts;  // int64 per cell: particles behind its near list
   // walk frontier
-  DevBuf fx, fy, fx2, fy2, fcnt, grp, walkrec, fsave, gsave, counters, gqueue;
+  // (fx, fx2: the cell of every chunk; fy, fy2: the frontier's source cells;
+  // gsave: chunk counts of a level and their offsets)
+  DevBuf fx, fy, fx2, fy2, grp, walkrec, fsave, gsave, counters, gqueue;
+  bool frontier_mapped = false;  // fx holds the cell of every frontier entry
   DevBuf stage;  // walk: per-chunk staging windows of one level's terminal pairs
   DevBuf farrec; // far field, mixed UC/TC: 128-byte source record per cell
   // walk: terminal pairs per frontier entry of every level (far, near, split-X
@@ -159,8 +163,14 @@ void sync(Ctx& c);
 // ---- scan.hip ----
 // exclusive prefix sum of n int32 values into out[0..n], out[n] = total
 void scan_i32(Ctx& c, const int32_t* in, int32_t* out, int64_t n);
-// the same for int64 values
-void scan_i64(Ctx& c, const int64_t* in, int64_t* out, int64_t n);
+// the same for `count` int64 arrays of length n at once
+constexpr int kScanMax = 6;
+template <typename T>
+struct ScanSet {
+  const T* in[kScanMax];
+  T* out[kScanMax];
+};
+void scan_i64(Ctx& c, const ScanSet<int64_t>& set, int count, int64_t n);
 
 // ---- sort.hip ----
 // stable LSD radix sort of (key, value) pairs by the low `bits` bits of key;

@@ -1,5 +1,9 @@
-// Device-wide exclusive prefix sums (reduce -> scan of block sums -> down-sweep).
-// Deterministic: integer sums in a fixed tree order.  In place is allowed.
+// Device-wide exclusive prefix sums of one or several arrays of one length, in
+// one launch up to kChunk values and two beyond (block sums, then every block
+// adds up the block sums before its own: at most a few hundred loads a thread
+// at 10^8 values).  Launches are what bounds it at the walk's sizes (about 3 us
+// each): a walk level scans six arrays at once, in 2 launches where it took 18.
+// Deterministic: integer sums in a fixed order.  In place is allowed.
 #include "internal.h"
 
 namespace amfmm {
@@ -39,8 +43,10 @@ __device__ T block_excl_scan(T v, T* tot) {
   return off + inc - v;
 }
 
+// block sums of every array of the set (blockIdx.y)
 template <typename T>
-__global__ void __launch_bounds__(kBS) k_reduce(const T* __restrict__ in, int64_t n, T* __restrict__ bsum) {
+__global__ void __launch_bounds__(kBS) k_reduce(ScanSet<T> set, int64_t n, T* __restrict__ bsum) {
+  const T* __restrict__ in = set.in[blockIdx.y];
   const int64_t base = (int64_t)blockIdx.x * kChunk;
   T s = 0;
 #pragma unroll
@@ -50,21 +56,26 @@ __global__ void __launch_bounds__(kBS) k_reduce(const T* __restrict__ in, int64_
   }
   T tot;
   block_excl_scan(s, &tot);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+  if (threadIdx.x == 0) bsum[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = tot;
 }
 
-// scans one chunk per block; offs (may be null) holds each block's exclusive prefix;
-// writes out[0..n) and out[n] = total
+// scans one chunk per block of every array of the set; the block's offset is
+// the sum of the block sums before it; writes out[0..n) and out[n] = total
 template <typename T>
-__global__ void __launch_bounds__(kBS) k_scan_chunk(const T* in, T* out, int64_t n,
-                                                     const T* __restrict__ offs) {
+__global__ void __launch_bounds__(kBS) k_scan_chunk(ScanSet<T> set, int64_t n, const T* __restrict__ bsum) {
   __shared__ T tile[kChunk];
+  const T* in = set.in[blockIdx.y];
+  T* out = set.out[blockIdx.y];
   const int64_t base = (int64_t)blockIdx.x * kChunk;
 #pragma unroll
   for (int i = 0; i < kIT; ++i) {
     int64_t idx = base + i * kBS + threadIdx.x;
     tile[i * kBS + threadIdx.x] = idx < n ? in[idx] : T(0);
   }
+  T before = 0;
+  for (unsigned b = threadIdx.x; b < blockIdx.x; b += kBS) before += bsum[(int64_t)blockIdx.y * gridDim.x + b];
+  T offset;
+  block_excl_scan(before, &offset);
   __syncthreads();
   T v[kIT];
   T s = 0;
@@ -74,8 +85,7 @@ __global__ void __launch_bounds__(kBS) k_scan_chunk(const T* in, T* out, int64_t
     s += v[i];
   }
   T tot;
-  T ex = block_excl_scan(s, &tot);
-  if (offs) ex += offs[blockIdx.x];
+  T ex = block_excl_scan(s, &tot) + offset;
 #pragma unroll
   for (int i = 0; i < kIT; ++i) {
     tile[threadIdx.x * kIT + i] = ex;
@@ -91,63 +101,30 @@ __global__ void __launch_bounds__(kBS) k_scan_chunk(const T* in, T* out, int64_t
 }
 
 template <typename T>
-__global__ void k_zero_one(T* out) {
-  out[0] = 0;
+__global__ void k_zero_heads(ScanSet<T> set) {
+  set.out[threadIdx.x][0] = 0;
 }
 
 template <typename T>
-void scan_impl(Ctx& c, const T* in, T* out, int64_t n, DevBuf& tmpbuf) {
+void scan_impl(Ctx& c, const ScanSet<T>& set, int count, int64_t n) {
   if (n <= 0) {
-    hipLaunchKernelGGL(k_zero_one<T>, dim3(1), dim3(1), 0, c.stream, out);
+    hipLaunchKernelGGL(k_zero_heads<T>, dim3(1), dim3(count), 0, c.stream, set);
     AMFMM_HIP(hipGetLastError());
     return;
   }
-  // block-sum arrays of every recursion level, carved from one buffer
-  std::vector<int64_t> sizes;
-  for (int64_t m = n; m > kChunk;) {
-    m = (m + kChunk - 1) / kChunk;
-    sizes.push_back(m);
-  }
-  size_t total = 0;
-  for (int64_t s : sizes) total += (size_t)(s + 1);
-  T* tmp = (T*)ensure(c, tmpbuf, sizeof(T) * (total + 1));
-  std::vector<T*> lev;
-  size_t off = 0;
-  for (int64_t s : sizes) {
-    lev.push_back(tmp + off);
-    off += (size_t)(s + 1);
-  }
-  // up-sweep
-  const T* src = in;
-  int64_t m = n;
-  for (size_t l = 0; l < sizes.size(); ++l) {
-    hipLaunchKernelGGL(k_reduce<T>, dim3((unsigned)sizes[l]), dim3(kBS), 0, c.stream, src, m, lev[l]);
-    AMFMM_HIP(hipGetLastError());
-    src = lev[l];
-    m = sizes[l];
-  }
-  // top level in one block (in place), then down-sweeps
-  if (!sizes.empty()) {
-    T* top = lev.back();
-    hipLaunchKernelGGL(k_scan_chunk<T>, dim3(1), dim3(kBS), 0, c.stream, top, top, sizes.back(),
-                       (const T*)nullptr);
-    AMFMM_HIP(hipGetLastError());
-    for (int l = (int)sizes.size() - 2; l >= 0; --l) {
-      hipLaunchKernelGGL(k_scan_chunk<T>, dim3((unsigned)sizes[l + 1]), dim3(kBS), 0, c.stream,
-                         lev[l], lev[l], sizes[l], (const T*)lev[l + 1]);
-      AMFMM_HIP(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_scan_chunk<T>, dim3((unsigned)sizes[0]), dim3(kBS), 0, c.stream, in, out, n,
-                       (const T*)lev[0]);
-  } else {
-    hipLaunchKernelGGL(k_scan_chunk<T>, dim3(1), dim3(kBS), 0, c.stream, in, out, n, (const T*)nullptr);
-  }
+  const int64_t nb = (n + kChunk - 1) / kChunk;
+  T* bsum = (T*)ensure(c, c.scratch, sizeof(T) * (size_t)(nb * count));
+  const dim3 grid((unsigned)nb, (unsigned)count);
+  if (nb > 1) hipLaunchKernelGGL(k_reduce<T>, grid, dim3(kBS), 0, c.stream, set, n, bsum);
+  hipLaunchKernelGGL(k_scan_chunk<T>, grid, dim3(kBS), 0, c.stream, set, n, (const T*)bsum);
   AMFMM_HIP(hipGetLastError());
 }
 
 }  // namespace
 
-void scan_i32(Ctx& c, const int32_t* in, int32_t* out, int64_t n) { scan_impl<int32_t>(c, in, out, n, c.scratch); }
-void scan_i64(Ctx& c, const int64_t* in, int64_t* out, int64_t n) { scan_impl<int64_t>(c, in, out, n, c.scratch); }
+void scan_i32(Ctx& c, const int32_t* in, int32_t* out, int64_t n) {
+  scan_impl<int32_t>(c, ScanSet<int32_t>{{in}, {out}}, 1, n);
+}
+void scan_i64(Ctx& c, const ScanSet<int64_t>& set, int count, int64_t n) { scan_impl<int64_t>(c, set, count, n); }
 
 }  // namespace amfmm

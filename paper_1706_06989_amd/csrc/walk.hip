@@ -195,16 +195,16 @@ __device__ inline int decide(const TreeView& t, int32_t X, const WalkCell& a, in
 }
 
 // Visits the pairs of entry (X, Y) in depth-first order (children of Y in
-// octant order) and calls f(kind, Y') for each decision: the terminal ones
-// and the opened ones (kSplitY, Y itself first).
+// octant order) and calls f(kind, Y', particles of Y') for each decision: the
+// terminal ones and the opened ones (kSplitY, Y itself first).
 template <int EXT, typename F>
 __device__ inline void traverse(const TreeView& t, int32_t X, int32_t Y, F&& f) {
   const WalkCell a = load_cell(t.rec, X);
   if (X == Y) {
     if (a.nch == 0) {
-      f(kNear, X);
+      f(kNear, X, a.count);
     } else {
-      for (int32_t j = 0; j < a.nch; ++j) f(kSplitX, a.ch0 + j);
+      for (int32_t j = 0; j < a.nch; ++j) f(kSplitX, a.ch0 + j, 0);
     }
     return;
   }
@@ -213,12 +213,12 @@ __device__ inline void traverse(const TreeView& t, int32_t X, int32_t Y, F&& f) 
   for (;;) {
     int d = decide<EXT>(t, X, a, cur, b);
     if (d == kSplitY) {
-      f(kSplitY, cur);
+      f(kSplitY, cur, b.count);
       cur = b.ch0;
       b = load_cell(t.rec, cur);
       continue;
     }
-    f(d, cur);
+    f(d, cur, b.count);
     for (;;) {
       if (cur == Y) return;
       if (b.next >= 0) {
@@ -407,6 +407,8 @@ struct EmitDst {
   int32_t* far_src;
   int32_t* near_src;
   int32_t* fy_n;
+  int32_t* fx_n;  // cell (in its level's range) of every next entry, or nullptr
+  int32_t c0n;
   int64_t B0;  // rank of this chunk's first split-X base inside the cell
   // STAGE
   const StageLayout* sl;
@@ -427,11 +429,12 @@ enum : int { kStage = 0, kEmit = 1 };
 // staging run and an emitting run visit the same pairs in the same order.
 // Returns the chunk's totals in tm, tp, tq, the pairs it decided on (its
 // candidate pairs, taken from the frontier or the queue, self pairs included)
-// in td, and (STAGE) whether it ran out of room.
+// in td, (STAGE) the particles behind its near entries in ts, and (STAGE)
+// whether it ran out of room.
 template <int PASS, int EXT, typename Q>
 __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& cx, const int32_t* __restrict__ fy,
                                  int64_t b, int32_t n, Q qbuf, int32_t qcap, int64_t& tm, int64_t& tp, int64_t& tq,
-                                 int64_t& td, EmitDst dst, unsigned long long* dbg) {
+                                 int64_t& td, int64_t& ts, EmitDst dst, unsigned long long* dbg) {
   const int32_t qmask = qcap - 1;
   const int lane = threadIdx.x & 63;
   // mode 2: this lane's part of the network, for the wave's cooperative
@@ -440,6 +443,7 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
   if (EXT == kExtLearned) ml = mlp_lane(t.lmodel);
   int32_t head = 0, tail = 0, fpos = 0;
   int64_t fo = dst.fo, no = dst.no, B = dst.B0;
+  int64_t parts = 0;  // STAGE: this lane's near particles
   unsigned long long dsteps = 0, ddeep = 0, dpairs = 0, dask = 0, daskw = 0;
   int32_t nreg[3] = {0, 0, 0};  // STAGE: spill regions held (wave-uniform)
   bool ovf = false;              // STAGE: out of room; writes stop
@@ -464,7 +468,10 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
   };
   auto put_split = [&](int64_t r, int32_t v) {
     if (PASS == kEmit) {
-      for (int32_t c = 0; c < cx.nch; ++c) dst.fy_n[dst.nb + c * dst.S + r] = v;
+      for (int32_t c = 0; c < cx.nch; ++c) {
+        dst.fy_n[dst.nb + c * dst.S + r] = v;
+        if (dst.fx_n) dst.fx_n[dst.nb + c * dst.S + r] = cx.ch0 + c - dst.c0n;
+      }
     } else {
       stage_put(2, r, v);
     }
@@ -568,12 +575,15 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
     }
     int32_t nd = 0;  // decisions inside a descent
     if (deep)
-      traverse<EXT>(t, X, Y, [&](int d, int32_t) {
+      traverse<EXT>(t, X, Y, [&](int d, int32_t, int32_t cnt) {
         m += d == kAccept;
         p += d == kNear;
         q += d == kSplitX;
+        if (PASS == kStage && d == kNear) parts += cnt;
         ++nd;
       });
+    else if (PASS == kStage && p)
+      parts += self ? cx.count : cy.count;
     if (__ballot(deep)) {
       // candidate pairs decided inside descents (the entry's own, decided
       // again first, is counted already)
@@ -605,7 +615,7 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
     }
     if (deep) {
       int64_t f = fo + om, g = no + op, bb = B + oq;
-      traverse<EXT>(t, X, Y, [&](int d, int32_t Z) {
+      traverse<EXT>(t, X, Y, [&](int d, int32_t Z, int32_t) {
         if (d == kAccept) put_far(f++, Z);
         else if (d == kNear) put_near(g++, Z);
         else if (d == kSplitX) put_split(bb++, Z);
@@ -627,6 +637,7 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
   tm = fo - dst.fo;
   tp = no - dst.no;
   tq = B - dst.B0;
+  if (PASS == kStage) ts = wave_sum64(parts);
 
   if (dbg && (threadIdx.x & 63) == 0) {
     atomicAdd(&dbg[0], dsteps);
@@ -643,11 +654,19 @@ constexpr int64_t kGlobalQueueBytes = int64_t(1) << 31;  // global work queues o
 constexpr int32_t kGlobalQueueMax = 1 << 18;  // at most this many entries per wave, used when at least 4 kQ
 
 // chunk -> cell map of the level: kcell[k] = i for cbase[i] <= k < cbase[i+1]
-__global__ void __launch_bounds__(kBS) k_chunk_map(int32_t nl, const int64_t* __restrict__ cbase,
+// (a search per chunk: a loop per cell over its chunks left the cells with
+// thousands of them to one lane each, up to 27 us a level)
+__global__ void __launch_bounds__(kBS) k_chunk_map(int32_t nl, const int64_t* __restrict__ cbase, int64_t kmax,
                                                    int32_t* __restrict__ kcell) {
-  const int32_t i = blockIdx.x * kBS + threadIdx.x;
-  if (i >= nl) return;
-  for (int64_t k = cbase[i]; k < cbase[i + 1]; ++k) kcell[k] = i;
+  const int64_t k = (int64_t)blockIdx.x * kBS + threadIdx.x;
+  if (k >= kmax || k >= cbase[nl]) return;
+  int32_t lo = 0, hi = nl;  // cbase[lo] <= k < cbase[hi]
+  while (hi - lo > 1) {
+    const int32_t mid = lo + ((hi - lo) >> 1);
+    if (cbase[mid] <= k) lo = mid;
+    else hi = mid;
+  }
+  kcell[k] = lo;
 }
 
 __global__ void __launch_bounds__(kBS) k_chunk_counts(int32_t nl, const int32_t* __restrict__ gcnt, int32_t chunk,
@@ -667,14 +686,20 @@ __device__ inline const float* stage_model(const float* __restrict__ g, float* l
 // One wave per chunk of a cell's frontier entries: walk it once, writing its
 // terminal pairs to its staging room, and record its counts (and whether it
 // ran out of room).
+// km .. ks: far, near, split-X, split-X times children, candidate pairs and
+// near particles of every chunk (zeros for k past the level's chunks, whose
+// number the host may know only as the bound kn)
+struct ChunkCounts {
+  int64_t *km, *kp, *kq, *kr, *kd, *ks;
+  int32_t* kov;
+};
+
 template <int EXT>
-__global__ void __launch_bounds__(kBS) k_walk_stage(TreeView t, int32_t c0, int64_t kn, int32_t chunk,
+__global__ void __launch_bounds__(kBS) k_walk_stage(TreeView t, int32_t c0, int32_t nl, int64_t kn, int32_t chunk,
                                                     const int32_t* __restrict__ kcell, const int64_t* __restrict__ cbase,
                                                     const int64_t* __restrict__ gbeg, const int32_t* __restrict__ gcnt,
                                                     const int32_t* __restrict__ fy, const StageLayout* __restrict__ sl,
-                                                    int64_t* __restrict__ km, int64_t* __restrict__ kp,
-                                                    int64_t* __restrict__ kq, int32_t* __restrict__ kov,
-                                                    int64_t* __restrict__ kd, unsigned long long* __restrict__ nov,
+                                                    ChunkCounts out, unsigned long long* __restrict__ nov,
                                                     int32_t* __restrict__ gq, int32_t qcap, unsigned long long* dbg) {
   __shared__ int32_t queue[kBS / 64][kQ];
   __shared__ int64_t regions[kBS / 64][3 * kRegions];
@@ -685,13 +710,20 @@ __global__ void __launch_bounds__(kBS) k_walk_stage(TreeView t, int32_t c0, int6
   // loaded once per wave into scalar registers
   const int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kBS / 64) + (threadIdx.x >> 6)));
   if (k >= kn) return;
+  if (k >= cbase[nl]) {
+    if (lane == 0) {
+      out.km[k] = out.kp[k] = out.kq[k] = out.kr[k] = out.kd[k] = out.ks[k] = 0;
+      out.kov[k] = 0;
+    }
+    return;
+  }
   const int32_t i = kcell[k];
   const int32_t X = c0 + i;
   const WalkCell cx = load_cell(t.rec, X);
   const int64_t e0 = (k - cbase[i]) * chunk;
   const int32_t n = (int32_t)min<int64_t>(chunk, gcnt[i] - e0);
   const int64_t e = gbeg[i] + e0;
-  EmitDst dst{0, 0, 0, 0, nullptr, nullptr, nullptr, 0, sl, {}, {}, k, regions[threadIdx.x >> 6]};
+  EmitDst dst{0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, sl, {}, {}, k, regions[threadIdx.x >> 6]};
 #pragma unroll
   for (int w = 0; w < 3; ++w) {
     const int64_t lo = stage_lo(*sl, w, e, k);
@@ -699,51 +731,64 @@ __global__ void __launch_bounds__(kBS) k_walk_stage(TreeView t, int32_t c0, int6
     dst.wcap[w] = stage_lo(*sl, w, e + n, k + 1) - lo;
     dst.wsh |= spill_shift(dst.wcap[w]) << (8 * w);
   }
-  int64_t tm = 0, tp = 0, tq = 0, td = 0;
+  int64_t tm = 0, tp = 0, tq = 0, td = 0, ts = 0;
   bool over;
   if (gq)
-    over = wave_walk<kStage, EXT>(t, X, cx, fy, e, n, gq + k * qcap, qcap, tm, tp, tq, td, dst, dbg);
+    over = wave_walk<kStage, EXT>(t, X, cx, fy, e, n, gq + k * qcap, qcap, tm, tp, tq, td, ts, dst, dbg);
   else
-    over = wave_walk<kStage, EXT>(t, X, cx, fy, e, n, queue[threadIdx.x >> 6], kQ, tm, tp, tq, td, dst, dbg);
+    over = wave_walk<kStage, EXT>(t, X, cx, fy, e, n, queue[threadIdx.x >> 6], kQ, tm, tp, tq, td, ts, dst, dbg);
   if (lane == 0) {
-    kd[k] = td;
-    km[k] = tm;
-    kp[k] = tp;
-    kq[k] = tq;
-    kov[k] = over ? 1 : 0;
+    out.km[k] = tm;
+    out.kp[k] = tp;
+    out.kq[k] = tq;
+    out.kr[k] = tq * cx.nch;
+    out.kd[k] = td;
+    out.ks[k] = ts;
+    out.kov[k] = over ? 1 : 0;
     if (over) atomicAdd(nov, 1ull);
   }
 }
 
-// per cell: list extents, the size of its children's entries, and their groups
+// prefix sums of the chunks' counts (see ChunkCounts)
+struct ChunkScans {
+  const int64_t *m, *p, *q, *r, *d, *s;
+};
+
+// Per cell: list extents, the particles behind its near list, and its
+// children's groups on the next level (gbeg_n holds one more entry, the end).
+// The level's totals go to the host's words: far, near, next entries, split-X
+// bases, chunks out of room, candidate pairs.
 __global__ void __launch_bounds__(kBS) k_walk_cells(TreeView t, int32_t c0, int32_t nl, int32_t c0n,
-                                                    const int64_t* __restrict__ cbase, const int64_t* __restrict__ mex,
-                                                    const int64_t* __restrict__ pex, const int64_t* __restrict__ qex,
+                                                    const int64_t* __restrict__ cbase, ChunkScans ex, int64_t kn,
                                                     int64_t far_base, int64_t near_base, int64_t* __restrict__ far_start,
                                                     int32_t* __restrict__ far_count, int64_t* __restrict__ near_start,
-                                                    int32_t* __restrict__ near_count, int64_t* __restrict__ ns) {
+                                                    int32_t* __restrict__ near_count, int64_t* __restrict__ near_parts,
+                                                    int64_t* __restrict__ gbeg_n, int32_t* __restrict__ gcnt_n,
+                                                    int32_t nln, const unsigned long long* __restrict__ nov,
+                                                    int64_t* __restrict__ host) {
   const int32_t i = blockIdx.x * kBS + threadIdx.x;
   if (i >= nl) return;
   const int32_t X = c0 + i;
   const int64_t k0 = cbase[i], k1 = cbase[i + 1];
-  far_start[X] = far_base + mex[k0];
-  far_count[X] = (int32_t)(mex[k1] - mex[k0]);
-  near_start[X] = near_base + pex[k0];
-  near_count[X] = (int32_t)(pex[k1] - pex[k0]);
-  ns[i] = (int64_t)load_cell(t.rec, X).nch * (qex[k1] - qex[k0]);
-}
-
-__global__ void __launch_bounds__(kBS) k_walk_groups(TreeView t, int32_t c0, int32_t nl, int32_t c0n,
-                                                     const int64_t* __restrict__ cbase, const int64_t* __restrict__ qex,
-                                                     const int64_t* __restrict__ nbase, int64_t* __restrict__ gbeg_n,
-                                                     int32_t* __restrict__ gcnt_n) {
-  const int32_t i = blockIdx.x * kBS + threadIdx.x;
-  if (i >= nl) return;
-  const WalkCell cx = load_cell(t.rec, c0 + i);
-  const int64_t S = qex[cbase[i + 1]] - qex[cbase[i]], nb = nbase[i];
+  far_start[X] = far_base + ex.m[k0];
+  far_count[X] = (int32_t)(ex.m[k1] - ex.m[k0]);
+  near_start[X] = near_base + ex.p[k0];
+  near_count[X] = (int32_t)(ex.p[k1] - ex.p[k0]);
+  near_parts[X] = ex.s[k1] - ex.s[k0];
+  const WalkCell cx = load_cell(t.rec, X);
+  const int64_t S = ex.q[k1] - ex.q[k0], nb = ex.r[k0];
   for (int32_t r = 0; r < cx.nch; ++r) {
     gbeg_n[cx.ch0 + r - c0n] = nb + r * S;
     gcnt_n[cx.ch0 + r - c0n] = (int32_t)S;
+  }
+  if (i == 0) {
+    gbeg_n[nln] = ex.r[kn];
+    host[0] = ex.m[kn];
+    host[1] = ex.p[kn];
+    host[2] = ex.r[kn];
+    host[3] = ex.q[kn];
+    host[4] = (int64_t)*nov;
+    host[5] = ex.d[kn];
   }
 }
 
@@ -756,14 +801,14 @@ __global__ void __launch_bounds__(kBS) k_walk_compact(TreeView t, int32_t c0, in
                                                       const int64_t* __restrict__ gbeg,
                                                       const int32_t* __restrict__ gcnt,
                                                       const StageLayout* __restrict__ slp,
-                                                      const int64_t* __restrict__ mex, const int64_t* __restrict__ pex,
-                                                      const int64_t* __restrict__ qex, const int64_t* __restrict__ nbase,
-                                                      const int32_t* __restrict__ kov, int64_t far_base,
+                                                      ChunkScans ex, const int32_t* __restrict__ kov, int32_t nl,
+                                                      int32_t c0n, int64_t far_base,
                                                       int64_t near_base, int32_t* __restrict__ far_src,
-                                                      int32_t* __restrict__ near_src, int32_t* __restrict__ fy_n) {
+                                                      int32_t* __restrict__ near_src, int32_t* __restrict__ fy_n,
+                                                      int32_t* __restrict__ fx_n) {
   const int lane = threadIdx.x & 63;
   const int64_t k = uniform((int32_t)(blockIdx.x * (kBS / 64) + (threadIdx.x >> 6)));
-  if (k >= kn || kov[k]) return;
+  if (k >= kn || k >= cbase[nl] || kov[k]) return;
   const StageLayout& sl = *slp;
   const int32_t i = kcell[k];
   const int64_t e0 = (k - cbase[i]) * chunk;
@@ -797,19 +842,24 @@ __global__ void __launch_bounds__(kBS) k_walk_compact(TreeView t, int32_t c0, in
       for (j = nw + lane; j < cnt; j += 64) d[j] = spilled(w, j, cap, sh);
     }
   };
-  const int64_t nm = mex[k + 1] - mex[k], np = pex[k + 1] - pex[k], nq = qex[k + 1] - qex[k];
-  copy(0, far_src + far_base + mex[k], nm);
-  copy(1, near_src + near_base + pex[k], np);
+  const int64_t nm = ex.m[k + 1] - ex.m[k], np = ex.p[k + 1] - ex.p[k], nq = ex.q[k + 1] - ex.q[k];
+  copy(0, far_src + far_base + ex.m[k], nm);
+  copy(1, near_src + near_base + ex.p[k], np);
   if (nq) {
-    const int32_t nch = load_cell(t.rec, c0 + i).nch;
-    const int64_t S = qex[cbase[i + 1]] - qex[cbase[i]];
-    int32_t* dq = fy_n + nbase[i] + (qex[k] - qex[cbase[i]]);
+    const WalkCell cx = load_cell(t.rec, c0 + i);
+    const int32_t nch = cx.nch;
+    const int64_t S = ex.q[cbase[i + 1]] - ex.q[cbase[i]];
+    const int64_t at = ex.r[cbase[i]] + (ex.q[k] - ex.q[cbase[i]]);
+    int32_t* dq = fy_n + at;
     const int64_t lo = stage_lo(sl, 2, e, k);
     const int64_t cap = stage_lo(sl, 2, e + n, k + 1) - lo;
     const int sh = spill_shift(cap);
     for (int64_t j = lane; j < nq; j += 64) {
       const int32_t v = j < cap ? sl.win[2][lo + j] : spilled(2, j, cap, sh);
-      for (int32_t r = 0; r < nch; ++r) dq[r * S + j] = v;
+      for (int32_t r = 0; r < nch; ++r) {
+        dq[r * S + j] = v;
+        if (fx_n) fx_n[at + r * S + j] = cx.ch0 + r - c0n;
+      }
     }
   }
 }
@@ -820,45 +870,46 @@ template <int EXT>
 __global__ void __launch_bounds__(kBS) k_walk_emit(TreeView t, int32_t c0, int64_t kn, int32_t chunk,
                                                    const int32_t* __restrict__ kcell, const int64_t* __restrict__ cbase,
                                                    const int64_t* __restrict__ gbeg, const int32_t* __restrict__ gcnt,
-                                                   const int32_t* __restrict__ fy, const int64_t* __restrict__ mex,
-                                                   const int64_t* __restrict__ pex, const int64_t* __restrict__ qex,
-                                                   const int64_t* __restrict__ nbase, const int32_t* __restrict__ kov,
+                                                   const int32_t* __restrict__ fy, ChunkScans ex,
+                                                   const int32_t* __restrict__ kov, int32_t nl, int32_t c0n,
                                                    int64_t far_base, int64_t near_base, int32_t* __restrict__ far_src,
                                                    int32_t* __restrict__ near_src, int32_t* __restrict__ fy_n,
-                                                   int32_t* __restrict__ gq, int32_t qcap) {
+                                                   int32_t* __restrict__ fx_n, int32_t* __restrict__ gq,
+                                                   int32_t qcap) {
   __shared__ int32_t queue[kBS / 64][kQ];
   __shared__ float model[EXT == kExtLearned ? AMFMM_MLP_MODEL : 1];
   if (EXT == kExtLearned) t.lmodel = stage_model(t.model, model);
   const int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kBS / 64) + (threadIdx.x >> 6)));
-  if (k >= kn || !kov[k]) return;
+  if (k >= kn || k >= cbase[nl] || !kov[k]) return;
   const int32_t i = kcell[k];
   const int32_t X = c0 + i;
   const WalkCell cx = load_cell(t.rec, X);
   const int64_t e0 = (k - cbase[i]) * chunk;
   const int32_t n = (int32_t)min<int64_t>(chunk, gcnt[i] - e0);
-  const int64_t S = qex[cbase[i + 1]] - qex[cbase[i]];
-  int64_t tm = 0, tp = 0, tq = 0, td = 0;
-  EmitDst dst{far_base + mex[k], near_base + pex[k], nbase[i], S, far_src, near_src, fy_n,
-              qex[k] - qex[cbase[i]], nullptr, {}, {}, k, nullptr};
+  const int64_t S = ex.q[cbase[i + 1]] - ex.q[cbase[i]];
+  int64_t tm = 0, tp = 0, tq = 0, td = 0, ts = 0;
+  EmitDst dst{far_base + ex.m[k], near_base + ex.p[k], ex.r[cbase[i]], S, far_src, near_src, fy_n, fx_n, c0n,
+              ex.q[k] - ex.q[cbase[i]], nullptr, {}, {}, k, nullptr};
   if (gq)
-    wave_walk<kEmit, EXT>(t, X, cx, fy, gbeg[i] + e0, n, gq + k * qcap, qcap, tm, tp, tq, td, dst, nullptr);
+    wave_walk<kEmit, EXT>(t, X, cx, fy, gbeg[i] + e0, n, gq + k * qcap, qcap, tm, tp, tq, td, ts, dst,
+                          nullptr);
   else
-    wave_walk<kEmit, EXT>(t, X, cx, fy, gbeg[i] + e0, n, queue[threadIdx.x >> 6], kQ, tm, tp, tq, td, dst, nullptr);
+    wave_walk<kEmit, EXT>(t, X, cx, fy, gbeg[i] + e0, n, queue[threadIdx.x >> 6], kQ, tm, tp, tq, td, ts, dst,
+                          nullptr);
 }
 
-__global__ void k_walk_init(int64_t* gbeg, int32_t* gcnt, int32_t* fy) {
+__global__ void k_walk_init(int64_t* gbeg, int32_t* gcnt, int32_t* fy, int32_t* fx) {
   gbeg[0] = 0;
+  gbeg[1] = 1;
   gcnt[0] = 1;
   fy[0] = 0;
+  fx[0] = 0;
 }
 
-__global__ void k_gather_totals(const int64_t* mex, const int64_t* pex, const int64_t* qex, const int64_t* nbase,
-                                const int64_t* kdex, int64_t kmax, int32_t nl, int64_t* out) {
-  out[0] = mex[kmax];
-  out[1] = pex[kmax];
-  out[2] = nbase[nl];
-  out[3] = qex[kmax];
-  out[5] = kdex[kmax];
+// a level's staging layout and its cleared counters
+__global__ void k_walk_level(StageLayout v, StageLayout* out, unsigned long long* counters) {
+  if (threadIdx.x < 16) counters[threadIdx.x] = 0ull;
+  if (threadIdx.x == 0) *out = v;
 }
 
 }  // namespace
@@ -903,12 +954,14 @@ void walk_prepare(Ctx& c, double theta) {
   ensure(c, c.far_count, sizeof(int32_t) * nc);
   ensure(c, c.near_start, sizeof(int64_t) * nc);
   ensure(c, c.near_count, sizeof(int32_t) * nc);
+  ensure(c, c.near_parts, sizeof(int64_t) * nc);
   int32_t maxw = 1;
   for (size_t l = 0; l + 1 < c.level_start.size(); ++l)
     maxw = std::max(maxw, c.level_start[l + 1] - c.level_start[l]);
   c.grp_width = maxw + 1;
   ensure(c, c.grp, 2 * (sizeof(int64_t) + sizeof(int32_t)) * (size_t)c.grp_width);
   ensure(c, c.fy, sizeof(int32_t) * 16);
+  ensure(c, c.fx, sizeof(int32_t) * 16);
   c.theta = theta;
   double scale = 0.0;
   for (double v : c.box) scale = std::max(scale, std::fabs(v));
@@ -930,9 +983,10 @@ void walk_start(Ctx& c) {
   int32_t* gcnt;
   group_ptrs(c, 0, &gbeg, &gcnt);
   c.grp_cur = 0;
-  hipLaunchKernelGGL(k_walk_init, dim3(1), dim3(1), 0, c.stream, gbeg, gcnt, as<int32_t>(c.fy));
+  hipLaunchKernelGGL(k_walk_init, dim3(1), dim3(1), 0, c.stream, gbeg, gcnt, as<int32_t>(c.fy), as<int32_t>(c.fx));
   AMFMM_HIP(hipGetLastError());
   c.frontier = 1;
+  c.frontier_mapped = true;
   c.walk_candidates = 0;
   c.pass_launches = 0;
 }
@@ -982,8 +1036,6 @@ static size_t stage_layout(Ctx& c, int lev, int64_t F, int64_t kn, const double*
   return sizeof(int32_t) * n + 3 * kRegions * sizeof(int64_t) * (size_t)kn + 64;
 }
 
-__global__ void k_set_layout(StageLayout v, StageLayout* out) { *out = v; }
-
 int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32_t>& lo,
                     const std::vector<int32_t>& hi, int64_t& far_base, int64_t& near_base) {
   TreeView t{(const WalkRec*)c.walkrec.p, c.theta, c.walk_abs_tol, c.walk_mode, c.opt.error_tol,
@@ -1014,36 +1066,47 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
   int64_t* tot_host = c.pinned;
   for (int lev = lev_first; lev <= lev_last && F > 0; ++lev) {
     const int32_t c0 = lo[lev], nl = hi[lev] - lo[lev];
-    const int32_t c0n = lev + 1 < (int)lo.size() ? lo[lev + 1] : 0;
+    const bool last = lev + 1 >= (int)lo.size();
+    const int32_t c0n = last ? 0 : lo[lev + 1], nln = last ? 0 : hi[lev + 1] - c0n;
     const size_t L = (size_t)nl + 1;
     // enough waves to fill the chip (small frontiers: one entry per wave),
     // few enough that dispatch does not dominate
     const int32_t chunk = (int32_t)std::min<int64_t>(kChunkMax, std::max<int64_t>(1, (F + kWavesPerLevel - 1) / kWavesPerLevel));
-    const int64_t kmax = F / chunk + nl + 1;  // upper bound on the chunks
-    const size_t K = (size_t)kmax + 1;
     int64_t *gbeg, *gbeg_n;
     int32_t *gcnt, *gcnt_n;
     group_ptrs(c, c.grp_cur, &gbeg, &gcnt);
     group_ptrs(c, 1 - c.grp_cur, &gbeg_n, &gcnt_n);
-    int64_t* w = (int64_t*)ensure(c, c.scratch2, sizeof(int64_t) * (4 * L + 9 * K + 48));
-    int64_t *nck = w, *cbase = nck + L, *ns = cbase + L, *nbase = ns + L;
-    int64_t *km = nbase + L, *kp = km + K, *kq = kp + K, *mex = kq + K, *pex = mex + K, *qex = pex + K;
-    int32_t* kov = (int32_t*)(qex + K);
-    int64_t *kd = qex + 2 * K, *kdex = kd + K;  // candidate pairs per chunk, and their scan
-    // [0..3] totals, [4] chunks out of room, [5] candidate pairs, [8..10] spill
-    // used, [12..16] debug counters, [20..] the staging layout
-    int64_t* tot = qex + 4 * K;
+    // Chunks of the level.  One entry each: the chunks are the entries, and
+    // their cells came with them.  Else their number has to be read back: it
+    // decides the work queues' size, and with it the order in which a chunk
+    // whose queue fills up lists its pairs.
+    int64_t kn = F;
+    const int64_t* cbase = gbeg;
+    const int32_t* kcell = as<int32_t>(c.fx);
+    if (chunk > 1 || !c.frontier_mapped) {
+      int64_t* nck = (int64_t*)ensure(c, c.gsave, sizeof(int64_t) * 2 * L);
+      hipLaunchKernelGGL(k_chunk_counts, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, nl, (const int32_t*)gcnt,
+                         chunk, nck);
+      AMFMM_HIP(hipGetLastError());
+      scan_i64(c, ScanSet<int64_t>{{nck}, {nck + L}}, 1, nl);
+      cbase = nck + L;
+      if (chunk > 1) {
+        AMFMM_HIP(hipMemcpyAsync(tot_host, cbase + nl, sizeof(int64_t), hipMemcpyDeviceToHost, c.stream));
+        sync(c);
+        kn = tot_host[0];
+      }
+      int32_t* map = (int32_t*)ensure(c, c.fx, sizeof(int32_t) * (kn + 1));
+      hipLaunchKernelGGL(k_chunk_map, dim3(blocks_for(kn, kBS)), dim3(kBS), 0, c.stream, nl, cbase, kn, map);
+      kcell = map;
+    }
+    const size_t K = (size_t)kn + 1;
+    int64_t* w = (int64_t*)ensure(c, c.scratch2, sizeof(int64_t) * (13 * K + 48));
+    const ChunkCounts kc{w, w + K, w + 2 * K, w + 3 * K, w + 4 * K, w + 5 * K, (int32_t*)(w + 12 * K)};
+    int64_t* e = w + 6 * K;
+    const ChunkScans ex{e, e + K, e + 2 * K, e + 3 * K, e + 4 * K, e + 5 * K};
+    // [4] chunks out of room, [8..10] spill used, [12..16] debug counters, [20..] the staging layout
+    int64_t* tot = w + 13 * K;
     const int32_t* fy = as<int32_t>(c.fy);
-    hipLaunchKernelGGL(k_chunk_counts, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, nl, (const int32_t*)gcnt,
-                       chunk, nck);
-    AMFMM_HIP(hipGetLastError());
-    scan_i64(c, nck, cbase, nl);
-    AMFMM_HIP(hipMemcpyAsync(tot_host, cbase + nl, sizeof(int64_t), hipMemcpyDeviceToHost, c.stream));
-    AMFMM_HIP(hipStreamSynchronize(c.stream));
-    const int64_t kn = tot_host[0];
-    int32_t* kcell = (int32_t*)ensure(c, c.fx, sizeof(int32_t) * (kn + 1));
-    hipLaunchKernelGGL(k_chunk_map, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, nl, (const int64_t*)cbase,
-                       kcell);
     const unsigned kgrid = blocks_for(kn, kBS / 64);
     // few chunks: a larger work queue per wave, in global memory
     int32_t* gq = nullptr;
@@ -1074,8 +1137,7 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     unsigned long long* dbg = debug ? (unsigned long long*)(tot + 12) : nullptr;
     StageLayout* sl_dev = (StageLayout*)(tot + 20);
     static_assert(20 + sizeof(StageLayout) / sizeof(int64_t) <= 48, "walk totals");
-    zero_u64(c, nov, 16);
-    hipLaunchKernelGGL(k_set_layout, dim3(1), dim3(1), 0, c.stream, sl, sl_dev);
+    hipLaunchKernelGGL(k_walk_level, dim3(1), dim3(64), 0, c.stream, sl, sl_dev, nov);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (debug) {
       AMFMM_HIP(hipEventCreate(&e0));
@@ -1086,30 +1148,20 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     hipLaunchKernelGGL(ext == kExtLearned     ? k_walk_stage<kExtLearned>
                        : ext == kExtMultipole ? k_walk_stage<kExtMultipole>
                                               : k_walk_stage<kExtBase>,
-                       dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, kn, chunk, (const int32_t*)kcell,
-                       (const int64_t*)cbase, (const int64_t*)gbeg, (const int32_t*)gcnt, fy,
-                       (const StageLayout*)sl_dev, km, kp, kq, kov, kd, nov, gq, qcap, dbg);
+                       dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, nl, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
+                       (const int32_t*)gcnt, fy, (const StageLayout*)sl_dev, kc, nov, gq, qcap, dbg);
     ++c.pass_launches;
     mark(c, kPhWalk);
     AMFMM_HIP(hipGetLastError());
     if (debug) AMFMM_HIP(hipEventRecord(e1, c.stream));
-    scan_i64(c, km, mex, kn);
-    scan_i64(c, kp, pex, kn);
-    scan_i64(c, kq, qex, kn);
-    scan_i64(c, kd, kdex, kn);
-    hipLaunchKernelGGL(k_walk_cells, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, t, c0, nl, c0n,
-                       (const int64_t*)cbase, (const int64_t*)mex, (const int64_t*)pex, (const int64_t*)qex, far_base,
-                       near_base, (int64_t*)c.far_start.p, (int32_t*)c.far_count.p, (int64_t*)c.near_start.p,
-                       (int32_t*)c.near_count.p, ns);
+    scan_i64(c, ScanSet<int64_t>{{kc.km, kc.kp, kc.kq, kc.kr, kc.kd, kc.ks}, {e, e + K, e + 2 * K, e + 3 * K, e + 4 * K, e + 5 * K}},
+             6, kn);
+    hipLaunchKernelGGL(k_walk_cells, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, t, c0, nl, c0n, cbase, ex, kn,
+                       far_base, near_base, (int64_t*)c.far_start.p, (int32_t*)c.far_count.p,
+                       (int64_t*)c.near_start.p, (int32_t*)c.near_count.p, (int64_t*)c.near_parts.p, gbeg_n, gcnt_n,
+                       nln, (const unsigned long long*)nov, tot_host);
     AMFMM_HIP(hipGetLastError());
-    scan_i64(c, ns, nbase, nl);
-    hipLaunchKernelGGL(k_walk_groups, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, t, c0, nl, c0n,
-                       (const int64_t*)cbase, (const int64_t*)qex, (const int64_t*)nbase, gbeg_n, gcnt_n);
-    hipLaunchKernelGGL(k_gather_totals, dim3(1), dim3(1), 0, c.stream, (const int64_t*)mex, (const int64_t*)pex,
-                       (const int64_t*)qex, (const int64_t*)nbase, (const int64_t*)kdex, kn, nl, tot);
-    AMFMM_HIP(hipGetLastError());
-    AMFMM_HIP(hipMemcpyAsync(tot_host, tot, sizeof(int64_t) * 6, hipMemcpyDeviceToHost, c.stream));
-    AMFMM_HIP(hipStreamSynchronize(c.stream));
+    sync(c);
     const int64_t mt = tot_host[0], pt = tot_host[1], Fn = tot_host[2], qt = tot_host[3], novh = tot_host[4];
     cand += tot_host[5];
     if (debug) {
@@ -1139,24 +1191,25 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     int32_t* near_src = (int32_t*)ensure_keep(c, c.near_src, sizeof(int32_t) * (near_base + pt + 1),
                                               sizeof(int32_t) * near_base);
     int32_t* fy_n = (int32_t*)ensure(c, c.fy2, sizeof(int32_t) * (Fn + 1));
+    // the next level's cells with its entries, where each will be a chunk
+    c.frontier_mapped = Fn <= kWavesPerLevel;
+    int32_t* fx_n = c.frontier_mapped ? (int32_t*)ensure(c, c.fx2, sizeof(int32_t) * (Fn + 1)) : nullptr;
     if (novh < kn)
       hipLaunchKernelGGL(k_walk_compact, dim3(blocks_for(kn, kBS / 64)), dim3(kBS), 0, c.stream, t, c0, kn, chunk,
-                         (const int32_t*)kcell, (const int64_t*)cbase, (const int64_t*)gbeg, (const int32_t*)gcnt,
-                         (const StageLayout*)sl_dev, (const int64_t*)mex,
-                         (const int64_t*)pex, (const int64_t*)qex, (const int64_t*)nbase, (const int32_t*)kov,
-                         far_base, near_base, far_src, near_src, fy_n);
+                         kcell, cbase, (const int64_t*)gbeg, (const int32_t*)gcnt, (const StageLayout*)sl_dev, ex,
+                         (const int32_t*)kc.kov, nl, c0n, far_base, near_base, far_src, near_src, fy_n, fx_n);
     if (novh > 0)
       hipLaunchKernelGGL(ext == kExtLearned     ? k_walk_emit<kExtLearned>
                          : ext == kExtMultipole ? k_walk_emit<kExtMultipole>
                                                 : k_walk_emit<kExtBase>,
-                         dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, kn, chunk, (const int32_t*)kcell,
-                         (const int64_t*)cbase, (const int64_t*)gbeg, (const int32_t*)gcnt, fy, (const int64_t*)mex,
-                         (const int64_t*)pex, (const int64_t*)qex, (const int64_t*)nbase, (const int32_t*)kov,
-                         far_base, near_base, far_src, near_src, fy_n, gq, qcap);
+                         dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
+                         (const int32_t*)gcnt, fy, ex, (const int32_t*)kc.kov, nl, c0n, far_base, near_base, far_src,
+                         near_src, fy_n, fx_n, gq, qcap);
     AMFMM_HIP(hipGetLastError());
     far_base += mt;
     near_base += pt;
     std::swap(c.fy, c.fy2);
+    if (fx_n) std::swap(c.fx, c.fx2);
     c.grp_cur = 1 - c.grp_cur;
     F = Fn;
   }
