@@ -172,7 +172,7 @@ static DevBuf* all_bufs(Ctx& c, int i) {
   DevBuf* v[] = {&c.pos4, &c.keys, &c.perm, &c.keys2, &c.perm2, &c.bbox, &c.scratch, &c.scratch2, &c.hist,
                  &c.c_begin, &c.c_count, &c.c_parent, &c.c_child0, &c.c_nchild, &c.c_level, &c.leaves, &c.leafof, &c.geo, &c.mom,
                  &c.msum, &c.loc, &c.far_start, &c.far_count, &c.far_src, &c.near_start, &c.near_count,
-                 &c.near_src, &c.near_parts, &c.fx, &c.fy, &c.fx2, &c.fy2, &c.grp, &c.walkrec, &c.fsave, &c.gsave, &c.counters, &c.gqueue, &c.stage, &c.farrec, &c.gmin, &c.model, &c.mlp_tmp, &c.mlp_part,
+                 &c.near_src, &c.near_parts, &c.near_plan, &c.fx, &c.fy, &c.fx2, &c.fy2, &c.grp, &c.walkrec, &c.fsave, &c.gsave, &c.counters, &c.gqueue, &c.stage, &c.farrec, &c.gmin, &c.model, &c.mlp_tmp, &c.mlp_part,
                  &c.mlp_grad, &c.mono, &c.locg};
   const int nv = (int)(sizeof(v) / sizeof(v[0]));
   return i < nv ? v[i] : nullptr;

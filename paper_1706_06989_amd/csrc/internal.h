@@ -87,6 +87,7 @@ struct Ctx {
   DevBuf far_start, far_count, far_src;     // int32 (start as int64)
   DevBuf near_start, near_count, near_src;
   DevBuf near_parts;  // int64 per cell: particles behind its near list
+  DevBuf near_plan;   // near field: segments of the cut lists and their partial sums
   // walk frontier
   // (fx, fx2: the cell of every chunk; fy, fy2: the frontier's source cells;
   // gsave: chunk counts of a level and their offsets)

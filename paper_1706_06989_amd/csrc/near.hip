@@ -11,6 +11,15 @@
 // The leaf's source entries are staged in LDS a bufferful at a time,
 // consecutive lanes copying consecutive particles.
 //
+// A leaf in the outskirts can face a whole core: its list is hundreds of
+// times the average and one wave's run over it was most of the phase (2.3 of
+// 2.4 ms at 100003 particles, theta 0.5).  Lists that cost more than twice a
+// share of the phase's total are cut into segments of whole buffer fills, one
+// wave each, which run first; k_near_join adds up their partial sums in segment
+// order.  The fills, and so the FP32 blocks, are those of the uncut list.  (One
+// kernel with the last segment to end adding them up needs a device-wide fence
+// per segment: 0.99 instead of 0.33 ms for a pilot solve at 262144.)
+//
 // Mixed precision: targets and staged sources are FP32 offsets from the
 // target leaf's centre of mass (each difference taken in FP64, then rounded),
 // the pair terms are FP32 (hardware reciprocal square root), and each lane's
@@ -135,18 +144,89 @@ __device__ inline int targets_per_lane(int ntc) {
   return best;
 }
 
-// One block of ntc <= 64 targets starting at tb, kTG per lane, against the
-// leaf's whole near list; returns the source particles of the list.
+// Partial sums of one segment's targets: four components and (mixed) their
+// compensation terms.
+struct NearPart {
+  double f[4];
+  float c[4];
+};
+
+// A wave's share of a list: the buffer fills that start at positions [lo, hi)
+// of the list's particles, and where its sums go (part: one per target of the
+// block, or nullptr: the wave has the whole list and finishes the targets).
+struct NearShare {
+  int64_t lo, hi;
+  NearPart* part;
+};
+
+// What every target of the phase needs to end: its cell's expansion and outputs.
+struct NearOut {
+  const int32_t* perm;
+  double G;
+  double *ax, *ay, *az, *pot;
+};
+
+__device__ inline void near_finish(const double4 pt, const double4 gx, const double* L, int32_t o, const NearOut& out,
+                                   double sx, double sy, double sz, double sp) {
+  const double x[3] = {pt.x - gx.x, pt.y - gx.y, pt.z - gx.z};
+  double gl[3], phi;
+  eval_local(L, x, gl, phi);
+  out.ax[o] = out.G * (sx + gl[0]);
+  out.ay[o] = out.G * (sy + gl[1]);
+  out.az[o] = out.G * (sz + gl[2]);
+  if (out.pot) out.pot[o] = out.G * (sp + phi);
+}
+
+// Skips the fills of a list that start before position lo: k and pos become
+// the first entry and position not skipped, off (a multiple of cap) the part
+// of an oversized entry k that is.  The entries' counts are fetched kSkip at a
+// time into the wave's staging buffer, so that a skipped fill costs an LDS
+// read and a scan, not two dependent loads from memory.
+constexpr int kSkip = 2048;
+
+__device__ inline void near_skip(int lane, int64_t st, int32_t nsc, int cap, int64_t lo, int32_t* cbuf,
+                                 const int32_t* __restrict__ nsrc, const int32_t* __restrict__ cnt, int32_t& k,
+                                 int64_t& pos, int32_t& off) {
+  while (k < nsc && pos < lo) {
+    const int32_t k0 = k, m = min(kSkip, nsc - k0);
+    for (int32_t i = lane; i < m; i += 64) cbuf[i] = cnt[nsrc[st + k0 + i]];
+    wave_sync();
+    while (pos < lo && k < nsc && (k - k0 + 64 <= m || k0 + m == nsc)) {
+      const int32_t i = k - k0 + lane;
+      const int32_t cl = i < m ? cbuf[i] : 0;
+      const int32_t inc = wave_incl_scan(cl);
+      const int take = __popcll(__ballot(i < m && inc <= cap));
+      if (take > 0) {
+        pos += __shfl(inc, take - 1, 64);
+        k += take;
+      } else {
+        const int32_t c0 = __shfl(cl, 0, 64);
+        if (pos + (int64_t)((c0 - 1) / cap) * cap < lo) {
+          pos += c0;
+          k += 1;
+        } else {
+          off = (int32_t)((lo - pos + cap - 1) / cap) * cap;
+          wave_sync();
+          return;
+        }
+      }
+    }
+    wave_sync();  // counts read before the next are fetched
+  }
+}
+
+// One block of ntc <= 64 targets starting at tb, kTG per lane, against this
+// wave's share of the leaf's near list.
 template <int kTG, bool MIXED, bool SOFT>
-__device__ __forceinline__ int64_t near_block(int lane, int32_t tb, int ntc, int64_t st, int32_t nsc, const double4 gx,
-                                     const double* L, double4* buf, const int32_t* __restrict__ nsrc,
-                                     const int32_t* __restrict__ beg, const int32_t* __restrict__ cnt,
-                                     const double4* __restrict__ pos, const int32_t* __restrict__ perm, double G,
-                                     double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az,
-                                     double* __restrict__ pot, double eps2) {
+__device__ __forceinline__ void near_block(int lane, int32_t tb, int ntc, int64_t st, int32_t nsc, const double4 gx,
+                                     const double* L, double4* buf, const NearShare& share,
+                                     const int32_t* __restrict__ nsrc, const int32_t* __restrict__ beg,
+                                     const int32_t* __restrict__ cnt, const double4* __restrict__ pos,
+                                     const NearOut& out, double eps2) {
   float4* buf32 = reinterpret_cast<float4*>(buf);
   constexpr int cap = MIXED ? 2 * kCap : kCap;
-  int64_t nsp = 0;
+  int64_t at = 0;    // position of the next fill in the list's particles
+  int32_t off0 = 0;  // particles of entry k that belong to other waves
   const int ng = (ntc + kTG - 1) / kTG;
   const int nsl = 64 / ng;  // slices per group: as many lanes as the groups leave
   const int g = lane / nsl, s = lane % nsl;
@@ -174,10 +254,11 @@ __device__ __forceinline__ int64_t near_block(int lane, int32_t tb, int ntc, int
   // taken while they fit.  The next round's entries are fetched while this
   // round copies and computes.
   int32_t k = 0;
-  int32_t Yl = lane < nsc ? nsrc[st + lane] : -1;
+  if (share.lo > 0) near_skip(lane, st, nsc, cap, share.lo, reinterpret_cast<int32_t*>(buf), nsrc, cnt, k, at, off0);
+  int32_t Yl = k + lane < nsc ? nsrc[st + k + lane] : -1;
   int32_t bl = Yl >= 0 ? beg[Yl] : 0;
   int32_t cl = Yl >= 0 ? cnt[Yl] : 0;
-  while (k < nsc) {
+  while (k < nsc && at < share.hi) {
     const int32_t inc = wave_incl_scan(cl);  // inclusive prefix over lanes
     const uint64_t fits = __ballot(Yl >= 0 && inc <= cap);
     const int take = __popcll(fits);  // prefix is monotone: leading lanes fit
@@ -215,12 +296,12 @@ __device__ __forceinline__ int64_t near_block(int lane, int32_t tb, int ntc, int
           else buf[vb] = pb;
         }
       }
-      nsp += fill;
+      at += fill;
     } else {
       // a single leaf larger than the buffer (coincident points at the
       // deepest level): stream it in buffer-sized pieces
       const int32_t b0 = __shfl(bl, 0, 64), c0 = __shfl(cl, 0, 64);
-      for (int32_t off = 0; off < c0; off += cap) {
+      for (int32_t off = off0; off < c0 && at + off < share.hi; off += cap) {
         const int part = min(cap, c0 - off);
         if (MIXED) {
           for (int i = lane; i < part; i += 64) buf32[i] = offset32(pos[b0 + off + i], gx);
@@ -234,7 +315,8 @@ __device__ __forceinline__ int64_t near_block(int lane, int32_t tb, int ntc, int
         }
         wave_sync();
       }
-      nsp += c0;
+      at += c0;
+      off0 = 0;
     }
     // the next round's extents load while this round computes
     const int32_t bn = Yn >= 0 ? beg[Yn] : 0;
@@ -281,6 +363,28 @@ __device__ __forceinline__ int64_t near_block(int lane, int32_t tb, int ntc, int
       }
     }
   }
+  if (share.part) {
+    if (active && s == 0) {
+#pragma unroll
+      for (int u = 0; u < kTG; ++u) {
+        const int t = g * kTG + u;
+        if (t < ntc) {
+          NearPart& o = share.part[t];
+          o.f[0] = fx[u];
+          o.f[1] = fy[u];
+          o.f[2] = fz[u];
+          o.f[3] = ph[u];
+          if (MIXED) {
+            o.c[0] = cx[u];
+            o.c[1] = cy[u];
+            o.c[2] = cz[u];
+            o.c[3] = cp[u];
+          }
+        }
+      }
+    }
+    return;
+  }
   if (MIXED) {
     // the compensated sums, rounded once to FP64
 #pragma unroll
@@ -306,19 +410,143 @@ __device__ __forceinline__ int64_t near_block(int lane, int32_t tb, int ntc, int
       sp = vp;
     }
   }
-  if (active && s < kTG && t < ntc) {
-    const double4 pt = pos[tb + t];  // reloaded: the mixed path keeps no FP64 copy
-    const double x[3] = {pt.x - gx.x, pt.y - gx.y, pt.z - gx.z};
-    double gl[3], phi;
-    eval_local(L, x, gl, phi);
-    const int32_t o = perm[tb + t];
-    ax[o] = G * (sx + gl[0]);
-    ay[o] = G * (sy + gl[1]);
-    az[o] = G * (sz + gl[2]);
-    if (pot) pot[o] = G * (sp + phi);
-  }
-  return nsp;
+  if (active && s < kTG && t < ntc)  // (reloaded: the mixed path keeps no FP64 copy)
+    near_finish(pos[tb + t], gx, L, out.perm[tb + t], out, sx, sy, sz, sp);
 }
+
+template <bool MIXED, bool SOFT>
+__device__ __forceinline__ void near_targets(int lane, int32_t tb, int ntc, int64_t st, int32_t nsc, const double4 gx,
+                                             const double* L, double4* buf, const NearShare& share,
+                                             const int32_t* __restrict__ nsrc, const int32_t* __restrict__ beg,
+                                             const int32_t* __restrict__ cnt, const double4* __restrict__ pos,
+                                             const NearOut& out, double eps2) {
+  const int K = targets_per_lane(ntc);
+  if (K == 1)
+    near_block<1, MIXED, SOFT>(lane, tb, ntc, st, nsc, gx, L, buf, share, nsrc, beg, cnt, pos, out, eps2);
+  else if (K == 2)
+    near_block<2, MIXED, SOFT>(lane, tb, ntc, st, nsc, gx, L, buf, share, nsrc, beg, cnt, pos, out, eps2);
+  else
+    near_block<kTGMax, MIXED, SOFT>(lane, tb, ntc, st, nsc, gx, L, buf, share, nsrc, beg, cnt, pos, out, eps2);
+}
+
+// Lane steps (in instructions) one wave takes over nsp sources with ntc targets.
+__device__ inline int64_t near_cost(int ntc, int64_t nsp) {
+  const int K = targets_per_lane(ntc);
+  const int nsl = 64 / ((ntc + K - 1) / K);
+  return nsp * (19 * K + 3) / nsl;
+}
+
+// One segment of one target block's list; the block itself has seg = 0.
+struct NearUnit {
+  int32_t X, tb, seg, nseg;
+  int32_t slot;  // first partial sum of the block (segment-major, ntc each)
+};
+
+// Cutting the long lists.  A list is cut when it costs more than two shares, a
+// share being the phase's whole cost over NearPlan::shares (a quarter of what one of
+// 4096 waves in flight gets at 16384) and at least kMinShare, below which a
+// segment's own start and end outweigh its work (about 3000 instructions, 5 us).
+// A block of c > 2 shares gets at most 3/2 c segments, and a leaf's blocks (all
+// cut like its first, the dearest) cost at least half of what that counts, so
+// there are at most 3 shares' worth of segments; a leaf whose partial sums
+// have no room is left whole.
+constexpr int64_t kMinShare = 4000;
+struct NearPlan {
+  NearUnit* units;
+  NearUnit* groups;    // the cut blocks
+  uint8_t* cut;        // per leaf: its blocks are in units
+  NearPart* parts;
+  unsigned long long* words;  // [0] interactions, [2] cost, [3] units, [4] groups, [5] partial sums
+  int64_t shares, max_parts;
+};
+
+__device__ inline int64_t wave_total(int64_t v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+
+// one thread per target leaf: interactions and cost of the phase
+__global__ void __launch_bounds__(kBS) k_near_cost(int32_t nleaves, const int32_t* __restrict__ leaves, int32_t c_lo,
+                                                   const int32_t* __restrict__ nch, const int32_t* __restrict__ cnt,
+                                                   const int64_t* __restrict__ parts,
+                                                   unsigned long long* __restrict__ words) {
+  const int32_t li = blockIdx.x * kBS + threadIdx.x;
+  int64_t inter = 0, cost = 0;
+  if (li < nleaves) {
+    const int32_t X = leaves ? leaves[li] : c_lo + li;
+    if (leaves || nch[X] == 0) {
+      const int32_t nt = cnt[X];
+      const int64_t nsp = parts[X];
+      inter = nt * (nsp - 1);
+      for (int32_t b = 0; b < nt; b += 64) cost += near_cost(min(64, nt - b), nsp);
+    }
+  }
+  inter = wave_total(inter);
+  cost = wave_total(cost);
+  __shared__ int64_t s[2][kWaves];
+  if ((threadIdx.x & 63) == 0) {
+    s[0][threadIdx.x >> 6] = inter;
+    s[1][threadIdx.x >> 6] = cost;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    int64_t v = 0;
+    for (int q = 0; q < kWaves; ++q) v += s[threadIdx.x][q];
+    if (v) atomicAdd(&words[2 * threadIdx.x], (unsigned long long)v);
+  }
+}
+
+// one thread per target leaf: cut or not; the wave writes its leaves' units
+__global__ void __launch_bounds__(kBS) k_near_cut(int32_t nleaves, const int32_t* __restrict__ leaves, int32_t c_lo,
+                                                  const int32_t* __restrict__ nch, const int32_t* __restrict__ beg,
+                                                  const int32_t* __restrict__ cnt, const int64_t* __restrict__ parts,
+                                                  NearPlan plan) {
+  const int32_t li = blockIdx.x * kBS + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int64_t share = max(kMinShare, (int64_t)plan.words[2] / plan.shares);
+  int32_t X = 0, nt = 0, nblk = 0, unit0 = 0, group0 = 0, slot0 = 0;
+  bool cut = false;
+  if (li < nleaves) {
+    X = leaves ? leaves[li] : c_lo + li;
+    if (leaves || nch[X] == 0) {
+      nt = cnt[X];
+      const int64_t nsp = parts[X];
+      nblk = (nt + 63) / 64;
+      // one length for all blocks of a leaf: the first is the largest
+      const int64_t c0 = near_cost(min(64, nt), nsp);
+      if (c0 > 2 * share) {
+        const int64_t nseg = (c0 + share - 1) / share;
+        const int64_t np = nseg * nt;
+        // partial sums first: a leaf they have no room for stays whole
+        const unsigned long long at = atomicAdd(&plan.words[5], (unsigned long long)np);
+        if ((int64_t)at + np <= plan.max_parts) {
+          cut = true;
+          slot0 = (int32_t)at;
+          unit0 = (int32_t)atomicAdd(&plan.words[3], (unsigned long long)(nseg * nblk));
+          group0 = (int32_t)atomicAdd(&plan.words[4], (unsigned long long)nblk);
+        }
+      }
+      plan.cut[li] = cut ? 1 : 0;
+    }
+  }
+  for (uint64_t m = __ballot(cut); m; m &= m - 1) {
+    const int o = __ffsll((unsigned long long)m) - 1;
+    const int32_t x = __shfl(X, o, 64), n = __shfl(nt, o, 64), nb = __shfl(nblk, o, 64), u0 = __shfl(unit0, o, 64),
+                  g0 = __shfl(group0, o, 64), s0 = __shfl(slot0, o, 64);
+    const int64_t c0 = near_cost(min(64, n), parts[x]);
+    const int32_t nseg = (int32_t)((c0 + share - 1) / share);
+    for (int32_t j = lane; j < nseg * nb; j += 64) {
+      const int32_t b = j / nseg;
+      const NearUnit u{x, beg[x] + 64 * b, j % nseg, nseg, s0 + 64 * b * nseg};
+      plan.units[u0 + j] = u;
+      if (u.seg == 0) plan.groups[g0 + b] = u;
+    }
+  }
+}
+
+// blocks that run segments, ahead of the blocks of whole leaves
+constexpr int kUnitBlocks = 1024;
 
 // leaves == nullptr: the targets are the leaves among cells [c_lo, c_lo + nleaves)
 template <bool MIXED, bool SOFT>
@@ -328,40 +556,110 @@ __global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(4))) k
                                               const double4* __restrict__ pos, const double4* __restrict__ geo,
                                               const double* __restrict__ loc, const int64_t* __restrict__ nstart,
                                               const int32_t* __restrict__ ncount, const int32_t* __restrict__ nsrc,
-                                              const int32_t* __restrict__ perm, double G, double* __restrict__ ax,
-                                              double* __restrict__ ay, double* __restrict__ az, double* __restrict__ pot,
-                                              unsigned long long* __restrict__ inter, double eps2) {
+                                              const int64_t* __restrict__ parts, NearOut out, NearPlan plan,
+                                              double eps2) {
   const int lane = threadIdx.x & 63;
-  const int32_t li = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6)));
-  if (li >= nleaves) return;
-  const int32_t X = uniform(leaves ? leaves[li] : c_lo + li);
-  if (!leaves && uniform(nch[X]) != 0) return;
-  const int32_t b = uniform(beg[X]), nt = uniform(cnt[X]);
-  const int64_t st = nstart[X];
-  const int32_t nsc = uniform(ncount[X]);
-  const double4 gx = geo[X];
-  const double* L = loc + (int64_t)X * kLoc;
   // FP64 staging holds kCap double4 per wave; the mixed path puts 2 kCap
   // float4 offsets in the same bytes
   __shared__ double4 lds[kWaves][kCap];
   double4* buf = lds[threadIdx.x >> 6];
-  int64_t nsrc_particles = 0;  // source particles of this leaf's list (lane 0)
-  for (int32_t tb = b; tb < b + nt; tb += 64) {
-    const int ntc = min(64, b + nt - tb);
-    const int K = targets_per_lane(ntc);
-    int64_t nsp;
-    if (K == 1)
-      nsp = near_block<1, MIXED, SOFT>(lane, tb, ntc, st, nsc, gx, L, buf, nsrc, beg, cnt, pos, perm, G, ax, ay, az,
-                                       pot, eps2);
-    else if (K == 2)
-      nsp = near_block<2, MIXED, SOFT>(lane, tb, ntc, st, nsc, gx, L, buf, nsrc, beg, cnt, pos, perm, G, ax, ay, az,
-                                       pot, eps2);
-    else
-      nsp = near_block<kTGMax, MIXED, SOFT>(lane, tb, ntc, st, nsc, gx, L, buf, nsrc, beg, cnt, pos, perm, G, ax, ay,
-                                            az, pot, eps2);
-    if (tb == b) nsrc_particles = nsp;
+  static_assert(kSkip * sizeof(int32_t) <= kCap * sizeof(double4), "skip buffer");
+  // this wave's work: segments u, u + kUnitBlocks kWaves, ... or the target
+  // blocks of one leaf (one call site for both: the code is the same)
+  const bool seg = blockIdx.x < kUnitBlocks;
+  int32_t u = 0, nu = 0, X = 0, tb = 0;
+  if (seg) {
+    u = uniform((int32_t)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
+    nu = uniform((int32_t)plan.words[3]);
+  } else {
+    const int32_t li = uniform((int32_t)(xcd_block(blockIdx.x - kUnitBlocks, gridDim.x - kUnitBlocks) * kWaves + (threadIdx.x >> 6)));
+    if (li >= nleaves) return;
+    X = uniform(leaves ? leaves[li] : c_lo + li);
+    if (!leaves && uniform(nch[X]) != 0) return;
+    if (plan.cut && uniform((int32_t)plan.cut[li])) return;
+    tb = uniform(beg[X]);
   }
-  if (lane == 0) atomicAdd(inter, (unsigned long long)((int64_t)nt * nsrc_particles - nt));
+  for (;;) {
+    NearShare share{0, INT64_MAX, nullptr};
+    if (seg) {
+      if (u >= nu) return;
+      const NearUnit& un = plan.units[u];
+      X = uniform(un.X);
+      tb = uniform(un.tb);
+      const int64_t nsp = parts[X], q = uniform(un.seg), nseg = uniform(un.nseg);
+      share.lo = nsp * q / nseg;
+      share.hi = nsp * (q + 1) / nseg;
+    }
+    const int32_t end = uniform(beg[X]) + uniform(cnt[X]);
+    const int ntc = min(64, end - tb);
+    if (seg) share.part = plan.parts + uniform(plan.units[u].slot) + (int64_t)uniform(plan.units[u].seg) * ntc;
+    const double4 gx = geo[X];
+    const double* L = loc + (int64_t)X * kLoc;
+    near_targets<MIXED, SOFT>(lane, tb, ntc, nstart[X], uniform(ncount[X]), gx, L, buf, share, nsrc, beg, cnt, pos, out,
+                              eps2);
+    if (!seg) {
+      tb += 64;
+      if (tb >= end) return;
+      continue;
+    }
+    u += kUnitBlocks * kWaves;
+  }
+}
+
+// One wave per cut target block: lanes (target t, row j) add segments j, j +
+// nj, ..., then the rows in order, and end the targets.
+constexpr int kJoinBlocks = 256;
+template <bool MIXED>
+__global__ void __launch_bounds__(kBS) k_near_join(const int32_t* __restrict__ beg, const int32_t* __restrict__ cnt,
+                                                   const double4* __restrict__ pos, const double4* __restrict__ geo,
+                                                   const double* __restrict__ loc, NearOut out, NearPlan plan) {
+  const int lane = threadIdx.x & 63;
+  const int32_t ng = (int32_t)plan.words[4];
+  for (int32_t g = uniform((int32_t)(blockIdx.x * kWaves + (threadIdx.x >> 6))); g < ng; g += kJoinBlocks * kWaves) {
+    const NearUnit un = plan.groups[g];
+    const int32_t X = uniform(un.X), tb = uniform(un.tb), nseg = uniform(un.nseg);
+    const int ntc = min(64, uniform(beg[X]) + uniform(cnt[X]) - tb);
+    const NearPart* __restrict__ part = plan.parts + uniform(un.slot);
+    const int nj = 64 / ntc, t = lane % ntc, j = lane / ntc;
+    double f[4] = {0.0, 0.0, 0.0, 0.0};
+    float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (j < nj) {
+#pragma unroll 4
+      for (int32_t q = j; q < nseg; q += nj) {
+        const NearPart& p = part[(int64_t)q * ntc + t];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          if (MIXED) {
+            comp_add(f[d], c[d], p.f[d]);
+            c[d] += p.c[d];
+          } else {
+            f[d] += p.f[d];
+          }
+        }
+      }
+    }
+    for (int r = 1; r < nj; ++r) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const double v = __shfl(f[d], t + r * ntc, 64);
+        const float w = MIXED ? __shfl(c[d], t + r * ntc, 64) : 0.0f;
+        if (j == 0) {
+          if (MIXED) {
+            comp_add(f[d], c[d], v);
+            c[d] += w;
+          } else {
+            f[d] += v;
+          }
+        }
+      }
+    }
+    if (MIXED) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) f[d] += (double)c[d];
+    }
+    if (j == 0)
+      near_finish(pos[tb + t], geo[X], loc + (int64_t)X * kLoc, out.perm[tb + t], out, f[0], f[1], f[2], f[3]);
+  }
 }
 
 }  // namespace
@@ -371,13 +669,46 @@ void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doub
   if (count <= 0) return;
   ++c.near_launches;
   const bool mixed = c.opt.precision == AMFMM_MIXED, soft = c.opt.softening > 0.0;
+  // room for the cut lists' segments and partial sums (fewer shares where
+  // memory is the caller's arena); without it every list stays whole
+  NearPlan plan{};
+  plan.shares = c.arena ? 2048 : 16384;
+  plan.max_parts = plan.shares * 3 / 2 * std::min(64, c.opt.n_crit);
+  const size_t units = 4 * (size_t)plan.shares, pb = sizeof(NearPart) * (size_t)plan.max_parts;
+  const size_t ub = sizeof(NearUnit) * units, gb = ub;
+  char* w = nullptr;
+  try {
+    w = (char*)ensure(c, c.near_plan, pb + ub + gb + (size_t)count);
+  } catch (const Error& e) {
+    if (e.code != AMFMM_E_OOM) throw;
+  }
+  if (w) {
+    plan.parts = (NearPart*)w;
+    plan.units = (NearUnit*)(w + pb);
+    plan.groups = (NearUnit*)(w + pb + ub);
+    plan.cut = (uint8_t*)(w + pb + ub + gb);
+  }
+  plan.words = (unsigned long long*)c.counters.p;
+  const int32_t* nch = as<int32_t>(c.c_nchild);
+  const int32_t* beg = as<int32_t>(c.c_begin);
+  const int32_t* cnt = as<int32_t>(c.c_count);
+  const int64_t* parts = (const int64_t*)c.near_parts.p;
+  zero_u64(c, plan.words + 2, 4);
+  hipLaunchKernelGGL(k_near_cost, dim3(blocks_for(count, kBS)), dim3(kBS), 0, c.stream, count, leaves, c_lo, nch, cnt,
+                     parts, plan.words);
+  if (plan.cut)
+    hipLaunchKernelGGL(k_near_cut, dim3(blocks_for(count, kBS)), dim3(kBS), 0, c.stream, count, leaves, c_lo, nch, beg,
+                       cnt, parts, plan);
   auto kern = mixed ? (soft ? k_near<true, true> : k_near<true, false>)
                     : (soft ? k_near<false, true> : k_near<false, false>);
-  hipLaunchKernelGGL(kern, dim3(blocks_for(count, kWaves)), dim3(kBS), 0, c.stream, count, leaves, c_lo,
-                     as<int32_t>(c.c_nchild), as<int32_t>(c.c_begin), as<int32_t>(c.c_count), (const double4*)c.pos4.p,
-                     (const double4*)c.geo.p, (const double*)c.loc.p, (const int64_t*)c.near_start.p,
-                     (const int32_t*)c.near_count.p, (const int32_t*)c.near_src.p, as<int32_t>(c.perm), c.opt.G, ax,
-                     ay, az, pot, (unsigned long long*)c.counters.p, c.opt.softening * c.opt.softening);
+  const NearOut out{as<int32_t>(c.perm), c.opt.G, ax, ay, az, pot};
+  hipLaunchKernelGGL(kern, dim3(kUnitBlocks + blocks_for(count, kWaves)), dim3(kBS), 0, c.stream, count, leaves, c_lo,
+                     nch, beg, cnt, (const double4*)c.pos4.p, (const double4*)c.geo.p, (const double*)c.loc.p,
+                     (const int64_t*)c.near_start.p, (const int32_t*)c.near_count.p, (const int32_t*)c.near_src.p,
+                     parts, out, plan, c.opt.softening * c.opt.softening);
+  if (plan.cut)
+    hipLaunchKernelGGL(mixed ? k_near_join<true> : k_near_join<false>, dim3(kJoinBlocks), dim3(kBS), 0, c.stream, beg,
+                       cnt, (const double4*)c.pos4.p, (const double4*)c.geo.p, (const double*)c.loc.p, out, plan);
   AMFMM_HIP(hipGetLastError());
   if (c.opt.order != 3) order_l2p(c, leaves, c_lo, count, ax, ay, az, pot);
 }
