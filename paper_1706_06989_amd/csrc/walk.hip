@@ -28,6 +28,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 
 #include "device_math.h"
 #include "internal.h"
@@ -52,11 +53,12 @@ struct alignas(16) WalkRec {
 struct WalkCell {
   double gx, gy, gz, gw, m, gmin;
   int32_t ch0, nch, par, next, count, k2, k3;
+  double mmin;  // smallest leaf mass below, where it was fetched with the record
 };
 
 struct TreeView {
   const WalkRec* rec;
-  double theta;
+  double theta, theta2;
   double abs_tol;    // bound on the rounding of any centre of mass (absolute)
   int mode;          // 0: opening angle theta; 1: error estimate; 2: learned; 3: multipole estimate
   double eps;        // modes 1-3: accepted error per pair, relative to each cell's field
@@ -68,18 +70,15 @@ struct TreeView {
   const float* lmodel; // mode 2, in the kernels: the network's LDS copy (lds_model_index layout)
 };
 
-__device__ inline WalkCell load_cell(const WalkRec* __restrict__ r, int32_t c) {
-  const double2* p = reinterpret_cast<const double2*>(r + c);
-  const int4* q = reinterpret_cast<const int4*>(reinterpret_cast<const char*>(r + c) + 48);
+// the cell of a record's four 16-byte pieces
+__device__ inline WalkCell unpack_cell(const double2 p0, const double2 p1, const double2 p2, const int4 v, int32_t c) {
   WalkCell w;
-  const double2 p0 = p[0], p1 = p[1], p2 = p[2];
   w.gx = p0.x;
   w.gy = p0.y;
   w.gz = p1.x;
   w.gw = p1.y;
   w.m = p2.x;
   w.gmin = p2.y;
-  const int4 v = q[0];
   w.ch0 = v.x;
   w.par = v.y;
   w.count = v.z;
@@ -90,15 +89,44 @@ __device__ inline WalkCell load_cell(const WalkRec* __restrict__ r, int32_t c) {
   return w;
 }
 
+__device__ inline WalkCell load_cell(const WalkRec* __restrict__ r, int32_t c) {
+  const double2* p = reinterpret_cast<const double2*>(r + c);
+  return unpack_cell(p[0], p[1], p[2], reinterpret_cast<const int4*>(p)[3], c);
+}
+
+__device__ inline double uniform_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// a record every lane of the wave needs, in scalar registers
+__device__ inline WalkCell load_cell_uniform(const WalkRec* __restrict__ r, int32_t c) {
+  WalkCell w = load_cell(r, c);
+  w.gx = uniform_f64(w.gx);
+  w.gy = uniform_f64(w.gy);
+  w.gz = uniform_f64(w.gz);
+  w.gw = uniform_f64(w.gw);
+  w.m = uniform_f64(w.m);
+  w.gmin = uniform_f64(w.gmin);
+  w.ch0 = uniform(w.ch0);
+  w.nch = uniform(w.nch);
+  w.count = uniform(w.count);
+  w.k2 = uniform(w.k2);
+  w.k3 = uniform(w.k3);
+  return w;
+}
+
 // Which decisions a kernel carries besides modes 0 and 1: the network's
 // (mode 2) or the multipole estimate's (mode 3); kernels of the other modes
 // stay free of their code and registers.
 enum : int { kExtBase = 0, kExtLearned = 2, kExtMultipole = 3 };
 
 // The rules for a pair that is not accepted: near field, or which cell opens.
-template <int EXT>
+// (root: sqrt(d2), where the decision needed it anyway: not in modes 0 and 1.)
+template <int EXT, bool HASMIN = false>
 __device__ inline int open_rule(const TreeView& t, int32_t X, const WalkCell& a, int32_t Y, const WalkCell& b,
-                                double d) {
+                                double d2, double root) {
   const int mode = EXT == kExtBase ? t.mode : EXT;
   const bool lx = a.nch == 0, ly = b.nch == 0;
   if (lx && ly) return kNear;
@@ -108,6 +136,7 @@ __device__ inline int open_rule(const TreeView& t, int32_t X, const WalkCell& a,
     // leaf X and the walk would pair X with every leaf under Y: record Y once
     // as a near-field source (its whole particle range).  The margin makes the
     // test safe against rounding of d and of the centres.
+    const double d = EXT == kExtBase ? sqrt(d2) : root;
     const double cut = mode == 0 ? t.theta : t.theta_max;
     if ((d + b.gw) * (1.0 + 1e-12) + t.abs_tol < a.gw / cut) return kNear;
     if (mode != 0) {
@@ -122,7 +151,7 @@ __device__ inline int open_rule(const TreeView& t, int32_t X, const WalkCell& a,
       const double D = (d + b.gw + t.abs_tol) * (1.0 + 1e-9);
       const double D2 = D * D;
       const double lim = (mode == 2 ? kGateHi : 1.0) * t.eps * a.gmin;
-      if ((a.gw * a.gw * a.gw) * t.mmin[Y] > lim * (D2 * D2 * D)) return kNear;
+      if ((a.gw * a.gw * a.gw) * (HASMIN ? b.mmin : t.mmin[Y]) > lim * (D2 * D2 * D)) return kNear;
     }
     return kSplitY;
   }
@@ -135,11 +164,39 @@ __device__ inline int open_rule(const TreeView& t, int32_t X, const WalkCell& a,
 // The walk's decision on pair (X, Y).  Mode 2 with f given: a pair the
 // network has to decide returns kAsk with its features in f and the
 // threshold in *thr (the caller runs the network for the wave and finishes
-// with open_rule); without f the lane runs the network itself.  *dist: the
-// centre distance, for open_rule.
-template <int EXT>
+// with open_rule); without f the lane runs the network itself.  *dist2: the
+// squared centre distance, for open_rule.
+//
+// Mode 0 is stated with d = sqrt(d2) and r / theta, each rounded: some 35
+// instructions of a pair's FP64 work.  It is first decided without either, up
+// to a margin far above the rounding of both forms; a pair within the margin
+// (or near the low end of the exponent range, where the margin means nothing)
+// takes the stated form, so the decision is the stated one always.
+constexpr double kTiny = 1e-280;
+
+// The multipole estimate's terms that hang on one cell alone (each rounded as
+// in multipole_bracket), in scalar registers for the cell that a whole wave
+// holds: left to the compiler they sit in eight pairs of vector registers and
+// are spilled.
+struct XTerms {
+  double r2, p1, q5, p3, c2, q4, es;  // R^2, w1 R^3, w5 R^4, w3 k3 R^3, w2 k2, w4 R^4, eps s
+};
+
+__device__ inline XTerms x_terms(const TreeView& t, const WalkCell& a) {
+  const double r2 = a.gw * a.gw;
+  return XTerms{uniform_f64(r2),
+                uniform_f64(kMw1 * (r2 * a.gw)),
+                uniform_f64(kMw5 * (r2 * r2)),
+                uniform_f64((kMw3 * (a.k3 / kMq)) * (r2 * a.gw)),
+                uniform_f64(kMw2 * (a.k2 / kMq)),
+                uniform_f64(kMw4 * (r2 * r2)),
+                uniform_f64(t.eps * a.gmin)};
+}
+
+template <int EXT, bool HASMIN = false>
 __device__ inline int decide(const TreeView& t, int32_t X, const WalkCell& a, int32_t Y, const WalkCell& b,
-                             float* f = nullptr, float* thr = nullptr, double* dist = nullptr) {
+                             float* f = nullptr, float* thr = nullptr, double* dist2 = nullptr,
+                             const XTerms* x = nullptr) {
   // the learned and multipole kernels serve only their own mode: a constant
   const int mode = EXT == kExtBase ? t.mode : EXT;
   const double dx = a.gx - b.gx, dy = a.gy - b.gy, dz = a.gz - b.gz;
@@ -147,11 +204,18 @@ __device__ inline int decide(const TreeView& t, int32_t X, const WalkCell& a, in
   const double r = a.gw + b.gw;
   // one root per pair, shared by the acceptance tests and the leaf rule below
   // (lanes of a wave take both paths)
-  const double d = sqrt(d2);
-  if (dist) *dist = d;
+  const double d = EXT == kExtBase ? 0.0 : sqrt(d2);
+  if (dist2) *dist2 = d2;
   if (mode == 0) {
-    const double rhs = r / t.theta;
-    if (d > 0.0 && d >= rhs) return kAccept;
+    // d >= r / theta against d2 theta^2 >= r^2: both sides round to within
+    // 1e-15 of the exact values
+    const double u = d2 * t.theta2, v = r * r, w = 1e-14 * v;
+    bool accept = u >= v + w && u > kTiny;
+    if (!accept && !(u <= v - w && v > kTiny)) {
+      const double root = sqrt(d2);
+      accept = root > 0.0 && root >= r / t.theta;
+    }
+    if (accept) return kAccept;
   } else if (EXT == kExtBase || mode == 1) {
     // The force error of a quadrupole-order pair scales as M_other r^3 / d^5
     // with r = R_A + R_B; accept when that estimate stays below eps times the
@@ -166,12 +230,22 @@ __device__ inline int decide(const TreeView& t, int32_t X, const WalkCell& a, in
     }
   } else if (EXT == kExtMultipole) {
     // mode 3: (P_A d + Q_A) M_B <= eps s_A d^6 and the same for B, in product
-    // form (one root, no division)
+    // form (one root, no division; deciding with an approximate d first costs
+    // as much in margins and registers as the root)
     if (d2 > 0.0 && r * r <= t.theta_max2 * d2) {
       const double d6 = (d2 * d2) * d2;
-      const double ea = multipole_bracket(a.gw, b.gw, b.k2, b.k3, d) * b.m;
-      const double eb = multipole_bracket(b.gw, a.gw, a.k2, a.k3, d) * a.m;
-      if (ea <= (t.eps * a.gmin) * d6 && eb <= (t.eps * b.gmin) * d6) return kAccept;
+      if (x) {
+        // the same operations, the terms of a alone from x
+        const double s2 = b.gw * b.gw, s3 = s2 * b.gw, s4 = s2 * s2;
+        const double pa = ((kMw3 * (b.k3 / kMq)) * s3 + (kMw2 * (b.k2 / kMq)) * (s2 * a.gw)) + x->p1;
+        const double pb = (x->p3 + x->c2 * (x->r2 * b.gw)) + kMw1 * s3;
+        const double ea = (pa * d + (kMw4 * s4 + x->q5)) * b.m, eb = (pb * d + (x->q4 + kMw5 * s4)) * a.m;
+        if (ea <= x->es * d6 && eb <= (t.eps * b.gmin) * d6) return kAccept;
+      } else {
+        const double ea = multipole_bracket(a.gw, b.gw, b.k2, b.k3, d) * b.m;
+        const double eb = multipole_bracket(b.gw, a.gw, a.k2, a.k3, d) * a.m;
+        if (ea <= (t.eps * a.gmin) * d6 && eb <= (t.eps * b.gmin) * d6) return kAccept;
+      }
     }
   } else {
     // mode 2: the multipole estimate, the network deciding where it is close
@@ -191,15 +265,14 @@ __device__ inline int decide(const TreeView& t, int32_t X, const WalkCell& a, in
       }
     }
   }
-  return open_rule<EXT>(t, X, a, Y, b, d);
+  return open_rule<EXT, HASMIN>(t, X, a, Y, b, d2, d);
 }
 
 // Visits the pairs of entry (X, Y) in depth-first order (children of Y in
 // octant order) and calls f(kind, Y', particles of Y') for each decision: the
 // terminal ones and the opened ones (kSplitY, Y itself first).
 template <int EXT, typename F>
-__device__ inline void traverse(const TreeView& t, int32_t X, int32_t Y, F&& f) {
-  const WalkCell a = load_cell(t.rec, X);
+__device__ inline void traverse(const TreeView& t, int32_t X, const WalkCell& a, const XTerms* x, int32_t Y, F&& f) {
   if (X == Y) {
     if (a.nch == 0) {
       f(kNear, X, a.count);
@@ -211,7 +284,7 @@ __device__ inline void traverse(const TreeView& t, int32_t X, int32_t Y, F&& f) 
   int32_t cur = Y;
   WalkCell b = load_cell(t.rec, cur);
   for (;;) {
-    int d = decide<EXT>(t, X, a, cur, b);
+    const int d = decide<EXT>(t, X, a, cur, b, nullptr, nullptr, nullptr, x);
     if (d == kSplitY) {
       f(kSplitY, cur, b.count);
       cur = b.ch0;
@@ -349,11 +422,20 @@ __device__ inline int64_t wave_sum64(int64_t v) {
 
 constexpr int kQ = 1024;  // per-wave LDS work queue (power of two)
 
-// orders this wave's queue writes (LDS or global) before its lanes read them
+// orders this wave's queue writes before its lanes read them: one wave's LDS
+// operations run in order, writes to a queue in global memory have to be
+// waited for
+template <bool GQ>
 __device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  if (GQ) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
 }
 
 // Staging of a level's terminal pairs.  Every chunk owns a window of each
@@ -413,9 +495,8 @@ struct EmitDst {
   // STAGE
   const StageLayout* sl;
   int32_t* win[3];
-  int64_t wcap[3];
-  int64_t chunk;
-  int64_t* lreg;  // this wave's spill region offsets in LDS (3 x kRegions)
+  int32_t wcap[3];
+  int64_t* ksec;  // this chunk's spill region offsets (3 x kRegions)
   int wsh;        // spill_shift of window w in bits 8w..8w+7
 };
 
@@ -431,9 +512,9 @@ enum : int { kStage = 0, kEmit = 1 };
 // candidate pairs, taken from the frontier or the queue, self pairs included)
 // in td, (STAGE) the particles behind its near entries in ts, and (STAGE)
 // whether it ran out of room.
-template <int PASS, int EXT, typename Q>
+template <int PASS, int EXT, bool GQ, bool DBG>
 __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& cx, const int32_t* __restrict__ fy,
-                                 int64_t b, int32_t n, Q qbuf, int32_t qcap, int64_t& tm, int64_t& tp, int64_t& tq,
+                                 int64_t b, int32_t n, int32_t* qbuf, int32_t qcap, int64_t& tm, int64_t& tp, int64_t& tq,
                                  int64_t& td, int64_t& ts, EmitDst dst, unsigned long long* dbg) {
   const int32_t qmask = qcap - 1;
   const int lane = threadIdx.x & 63;
@@ -442,35 +523,41 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
   MlpLane ml{};
   if (EXT == kExtLearned) ml = mlp_lane(t.lmodel);
   int32_t head = 0, tail = 0, fpos = 0;
-  int64_t fo = dst.fo, no = dst.no, B = dst.B0;
-  int64_t parts = 0;  // STAGE: this lane's near particles
+  // positions in this chunk's outputs (sources of one cell are disjoint, so
+  // they stay below 2^31)
+  int32_t fo = 0, no = 0, B = 0;
+  int32_t* const out_far = PASS == kEmit ? dst.far_src + dst.fo : dst.win[0];
+  int32_t* const out_near = PASS == kEmit ? dst.near_src + dst.no : dst.win[1];
+  int32_t parts = 0;  // STAGE: this lane's near particles
   unsigned long long dsteps = 0, ddeep = 0, dpairs = 0, dask = 0, daskw = 0;
   int32_t nreg[3] = {0, 0, 0};  // STAGE: spill regions held (wave-uniform)
   bool ovf = false;              // STAGE: out of room; writes stop
-  auto stage_put = [&](int w, int64_t f, int32_t v) {
+  // a position past its window (or any, out of room)
+  auto stage_put = [&](int w, int32_t f, int32_t v) {
     if (!ovf) {
       if (f < dst.wcap[w]) {
         dst.win[w][f] = v;
       } else {
         int64_t off;
         const int j = spill_region(f - dst.wcap[w], (dst.wsh >> (8 * w)) & 0xff, &off);
-        dst.sl->spill[w][dst.lreg[w * kRegions + j] + off] = v;
+        dst.sl->spill[w][dst.ksec[w * kRegions + j] + off] = v;
       }
     }
   };
-  auto put_far = [&](int64_t f, int32_t v) {
-    if (PASS == kEmit) dst.far_src[f] = v;
+  auto put_far = [&](int32_t f, int32_t v) {
+    if (PASS == kEmit) out_far[f] = v;
     else stage_put(0, f, v);
   };
-  auto put_near = [&](int64_t g, int32_t v) {
-    if (PASS == kEmit) dst.near_src[g] = v;
+  auto put_near = [&](int32_t g, int32_t v) {
+    if (PASS == kEmit) out_near[g] = v;
     else stage_put(1, g, v);
   };
-  auto put_split = [&](int64_t r, int32_t v) {
+  auto put_split = [&](int32_t r, int32_t v) {
     if (PASS == kEmit) {
       for (int32_t c = 0; c < cx.nch; ++c) {
-        dst.fy_n[dst.nb + c * dst.S + r] = v;
-        if (dst.fx_n) dst.fx_n[dst.nb + c * dst.S + r] = cx.ch0 + c - dst.c0n;
+        const int64_t at = dst.nb + c * dst.S + dst.B0 + r;
+        dst.fy_n[at] = v;
+        if (dst.fx_n) dst.fx_n[at] = cx.ch0 + c - dst.c0n;
       }
     } else {
       stage_put(2, r, v);
@@ -493,35 +580,57 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
         ovf = true;
         break;
       }
-      if (lane == 0) {
-        dst.lreg[w * kRegions + nreg[w]] = (int64_t)base;
-        dst.sl->ksec[(3 * dst.chunk + w) * kRegions + nreg[w]] = (int64_t)base;
-      }
+      if (lane == 0) dst.ksec[w * kRegions + nreg[w]] = (int64_t)base;
       ++nreg[w];
     }
   };
-  while (head < tail || fpos < n) {
-    int32_t Y = -1;
+  XTerms xt{};
+  if (EXT == kExtMultipole) xt = x_terms(t, cx);
+  const XTerms* const xp = EXT == kExtMultipole ? &xt : nullptr;
+  // The next 64 pairs, from the queue, else from the frontier (whose entries
+  // are fetched one block ahead), and their records and (X a leaf) smallest
+  // leaf masses on the way.  Called as soon as a step's opened pairs are
+  // queued, so that they travel while the step's terminal pairs are written:
+  // the pass is bound by the latency of these loads (61 % of the wave time
+  // waited before) and by the caches they miss in.  Fetching four lanes to a
+  // record through LDS measured slower (294 against 274 ms a pass at 16.8M
+  // particles), five waves a SIMD too (338 against 309: more misses).
+  const bool leafx = EXT != kExtBase && cx.nch == 0;
+  int32_t ahead = lane < n ? fy[b + lane] : -1;
+  double mmin = 0.0;
+  double2 rec[4];  // the record on its way
+  auto next = [&]() {
+    int32_t y = -1;
     if (head < tail) {
       const int k = min(64, tail - head);
-      if (lane < k) Y = qbuf[(head + lane) & qmask];
+      if (lane < k) y = qbuf[(head + lane) & qmask];
       head += k;
     } else {
-      const int k = min(64, n - fpos);
-      if (lane < k) Y = fy[b + fpos + lane];
-      fpos += k;
+      y = ahead;
+      fpos += 64;
+      ahead = fpos + lane < n ? fy[b + fpos + lane] : -1;
     }
-    wave_sync();  // queue slots just read may be reused by this step's pushes
+    const double2* src = reinterpret_cast<const double2*>(t.rec + (y < 0 ? 0 : y));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rec[i] = src[i];
+    if (leafx) mmin = t.mmin[y < 0 ? 0 : y];
+    return y;
+  };
+  int32_t Y = -1;
+  bool more = n > 0;
+  if (more) Y = next();
+  while (more) {
     td += __popcll(__ballot(Y >= 0));
     int32_t m = 0, p = 0, q = 0, push = 0, ych0 = 0;
     const bool self = Y >= 0 && Y == X;
-    WalkCell cy{};
+    WalkCell cy = unpack_cell(rec[0], rec[1], rec[2], __builtin_bit_cast(int4, rec[3]), Y);
+    cy.mmin = mmin;
     int d = -1;
     float f[kFeat], thr = 0.0f;
-    double dist = 0.0;
+    double dist2 = 0.0;
     if (Y >= 0 && !self) {
-      cy = load_cell(t.rec, Y);
-      d = EXT == kExtLearned ? decide<EXT>(t, X, cx, Y, cy, f, &thr, &dist) : decide<EXT>(t, X, cx, Y, cy);
+      d = EXT == kExtLearned ? decide<EXT, EXT != kExtBase>(t, X, cx, Y, cy, f, &thr, &dist2)
+                             : decide<EXT, EXT != kExtBase>(t, X, cx, Y, cy, nullptr, nullptr, nullptr, xp);
     }
     if (EXT == kExtLearned) {
       // Pairs for the network are decided by the whole wave (every lane
@@ -530,7 +639,7 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
       const bool ask = d == kAsk;
       float mine = 0.0f;
       const uint64_t asked = __ballot(ask);
-      if (dbg) {
+      if (DBG) {
         dask += __popcll(asked);
         daskw += asked != 0;
       }
@@ -542,7 +651,7 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
         const float y = mlp_infer_wave(t.lmodel, ml, g);
         if (lane == L) mine = y;
       }
-      if (ask) d = mine <= thr ? kAccept : open_rule<EXT>(t, X, cx, Y, cy, dist);
+      if (ask) d = mine <= thr ? kAccept : open_rule<EXT, EXT != kExtBase>(t, X, cx, Y, cy, dist2, sqrt(dist2));
     }
     if (self) {
       if (cx.nch == 0) p = 1;
@@ -559,23 +668,37 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
     int32_t ptot;
     const int32_t poff = wave_excl_scan(push, &ptot);
     const int32_t freeq = qcap - (tail - head);
-    const bool fits = poff + push <= freeq;
-    const uint64_t over = __ballot(push > 0 && !fits);
-    const int32_t pushed = over ? __shfl(poff, __ffsll((unsigned long long)over) - 1, 64) : ptot;
-    if (push > 0 && fits)
-      for (int32_t j = 0; j < push; ++j) qbuf[(tail + poff + j) & qmask] = ych0 + j;
+    bool deep = false;  // queue full: this lane descends
+    int32_t pushed = ptot;
+    if (__builtin_expect(ptot > freeq, 0)) {
+      const bool fits = poff + push <= freeq;
+      deep = push > 0 && !fits;
+      pushed = __shfl(poff, __ffsll((unsigned long long)__ballot(deep)) - 1, 64);
+    }
+    if (push > 0 && !deep) {
+      const int32_t at = (tail + poff) & qmask;
+      if (__builtin_expect(at + 8 <= qcap, 1)) {
+#pragma unroll
+        for (int32_t j = 0; j < 8; ++j)
+          if (j < push) qbuf[at + j] = ych0 + j;
+      } else {
+        for (int32_t j = 0; j < push; ++j) qbuf[(at + j) & qmask] = ych0 + j;
+      }
+    }
     tail += pushed;
-    wave_sync();
-    const bool deep = push > 0 && !fits;  // queue full: descend in this lane
-    if (dbg) {
-      const uint64_t dm = __ballot(deep), ym = __ballot(Y >= 0);
+    wave_sync<GQ>();
+    const int32_t yc = Y;  // this step's cell
+    more = head < tail || fpos < n;
+    if (more) Y = next();
+    if (DBG) {
+      const uint64_t dm = __ballot(deep), ym = __ballot(yc >= 0);
       dsteps += 1;
       ddeep += __popcll(dm);
       dpairs += __popcll(ym);
     }
     int32_t nd = 0;  // decisions inside a descent
-    if (deep)
-      traverse<EXT>(t, X, Y, [&](int d, int32_t, int32_t cnt) {
+    if (__builtin_expect(deep, 0))
+      traverse<EXT>(t, X, cx, xp, yc, [&](int d, int32_t, int32_t cnt) {
         m += d == kAccept;
         p += d == kNear;
         q += d == kSplitX;
@@ -584,62 +707,75 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
       });
     else if (PASS == kStage && p)
       parts += self ? cx.count : cy.count;
-    if (__ballot(deep)) {
+    if (__builtin_expect(__ballot(deep) != 0, 0)) {
       // candidate pairs decided inside descents (the entry's own, decided
       // again first, is counted already)
       int32_t ndt;
       (void)wave_excl_scan(deep ? nd - 1 : 0, &ndt);
       td += ndt;
     }
-    int32_t Tm, Tp, Tq, om, op, oq;
-    if (__ballot(deep || self) == 0) {
+    if (__builtin_expect(__ballot(deep || self) == 0, 1)) {
       // no descent and no self pair: every lane holds at most one terminal
       // pair, so the offsets are counts of lanes below
       const uint64_t bm = __ballot(m != 0), bp = __ballot(p != 0), bq = __ballot(q != 0);
-      om = lanes_below(bm);
-      op = lanes_below(bp);
-      oq = lanes_below(bq);
-      Tm = __popcll(bm);
-      Tp = __popcll(bp);
-      Tq = __popcll(bq);
-    } else {
-      om = wave_excl_scan(m, &Tm);
-      op = wave_excl_scan(p, &Tp);
-      oq = wave_excl_scan(q, &Tq);
+      const int32_t Tm = __popcll(bm), Tp = __popcll(bp), Tq = __popcll(bq);
+      const int32_t f = fo + lanes_below(bm), g = no + lanes_below(bp), r = B + lanes_below(bq);
+      fo += Tm;
+      no += Tp;
+      B += Tq;
+      if (__builtin_expect(PASS == kEmit || (fo <= dst.wcap[0] && no <= dst.wcap[1] && B <= dst.wcap[2]), 1)) {
+        // inside the windows (the rule: they hold more than is expected)
+        if (m) out_far[f] = yc;
+        if (p) out_near[g] = yc;
+        if (q) {
+          if (PASS == kEmit) put_split(r, yc);
+          else dst.win[2][r] = yc;
+        }
+      } else {
+        reserve(0, fo);
+        reserve(1, no);
+        reserve(2, B);
+        wave_sync<true>();  // new region offsets before they are read
+        if (m) stage_put(0, f, yc);
+        if (p) stage_put(1, g, yc);
+        if (q) stage_put(2, r, yc);
+      }
+      continue;
     }
-    if (PASS == kStage) {
-      reserve(0, fo + Tm);
-      reserve(1, no + Tp);
-      reserve(2, B + Tq);
-      wave_sync();  // new region offsets in LDS before they are read
-    }
-    if (deep) {
-      int64_t f = fo + om, g = no + op, bb = B + oq;
-      traverse<EXT>(t, X, Y, [&](int d, int32_t Z, int32_t) {
-        if (d == kAccept) put_far(f++, Z);
-        else if (d == kNear) put_near(g++, Z);
-        else if (d == kSplitX) put_split(bb++, Z);
-      });
-    } else if (self) {
-      if (p) put_near(no + op, X);
-      for (int32_t j = 0; j < q; ++j) put_split(B + oq + j, cx.ch0 + j);
-    } else if (m) {
-      put_far(fo + om, Y);
-    } else if (p) {
-      put_near(no + op, Y);
-    } else if (q) {
-      put_split(B + oq, Y);
-    }
+    int32_t Tm, Tp, Tq;
+    int32_t f1 = fo + wave_excl_scan(m, &Tm), g1 = no + wave_excl_scan(p, &Tp), r1 = B + wave_excl_scan(q, &Tq);
     fo += Tm;
     no += Tp;
     B += Tq;
+    if (PASS == kStage) {
+      reserve(0, fo);
+      reserve(1, no);
+      reserve(2, B);
+      wave_sync<true>();
+    }
+    if (deep) {
+      traverse<EXT>(t, X, cx, xp, yc, [&](int d, int32_t Z, int32_t) {
+        if (d == kAccept) put_far(f1++, Z);
+        else if (d == kNear) put_near(g1++, Z);
+        else if (d == kSplitX) put_split(r1++, Z);
+      });
+    } else if (self) {
+      if (p) put_near(g1, X);
+      for (int32_t j = 0; j < q; ++j) put_split(r1 + j, cx.ch0 + j);
+    } else if (m) {
+      put_far(f1, yc);
+    } else if (p) {
+      put_near(g1, yc);
+    } else if (q) {
+      put_split(r1, yc);
+    }
   }
-  tm = fo - dst.fo;
-  tp = no - dst.no;
-  tq = B - dst.B0;
+  tm = fo;
+  tp = no;
+  tq = B;
   if (PASS == kStage) ts = wave_sum64(parts);
 
-  if (dbg && (threadIdx.x & 63) == 0) {
+  if (DBG && (threadIdx.x & 63) == 0) {
     atomicAdd(&dbg[0], dsteps);
     atomicAdd(&dbg[1], ddeep);
     atomicAdd(&dbg[2], dpairs);
@@ -694,21 +830,43 @@ struct ChunkCounts {
   int32_t* kov;
 };
 
-template <int EXT>
-__global__ void __launch_bounds__(kBS) k_walk_stage(TreeView t, int32_t c0, int32_t nl, int64_t kn, int32_t chunk,
+// Siblings are handed the same frontier entries, so the waves of a workgroup
+// take the same chunk of neighbouring siblings rather than neighbouring chunks
+// of one cell: what one wave fetches, the others find in their CU's cache.
+// The k-th wave's cell i and chunk become its place in this order, a
+// permutation inside each group of siblings (all of which have the same number
+// of chunks).  Short chunks end before the two extra dependent loads pay.
+constexpr int32_t kSiblingChunk = 64;
+
+__device__ inline int64_t sibling_order(const TreeView& t, int32_t c0, int32_t nl, const int64_t* __restrict__ cbase,
+                                        int64_t k, int32_t& i) {
+  const int32_t p = load_cell(t.rec, c0 + i).par;
+  if (p < 0) return k;
+  const WalkCell P = load_cell(t.rec, p);
+  // (a batch's range of cells may begin or end inside a group)
+  const int32_t first = max(P.ch0 - c0, 0), last = min(P.ch0 - c0 + P.nch, nl);
+  const int64_t b = cbase[first];
+  const int32_t q = (int32_t)(k - b), m = last - first;
+  i = first + q % m;
+  return cbase[i] + q / m;
+}
+
+// GQ: the work queues are in global memory (gq, qcap entries per chunk), else in LDS
+template <int EXT, bool GQ, bool DBG>
+__global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(EXT == kExtLearned ? 1 : 4)))
+k_walk_stage(TreeView t, int32_t c0, int32_t nl, int64_t kn, int32_t chunk,
                                                     const int32_t* __restrict__ kcell, const int64_t* __restrict__ cbase,
                                                     const int64_t* __restrict__ gbeg, const int32_t* __restrict__ gcnt,
                                                     const int32_t* __restrict__ fy, const StageLayout* __restrict__ sl,
                                                     ChunkCounts out, unsigned long long* __restrict__ nov,
                                                     int32_t* __restrict__ gq, int32_t qcap, unsigned long long* dbg) {
-  __shared__ int32_t queue[kBS / 64][kQ];
-  __shared__ int64_t regions[kBS / 64][3 * kRegions];
+  __shared__ int32_t queue[GQ ? 1 : kBS / 64][GQ ? 1 : kQ];
   __shared__ float model[EXT == kExtLearned ? AMFMM_MLP_MODEL : 1];
   if (EXT == kExtLearned) t.lmodel = stage_model(t.model, model);
   const int lane = threadIdx.x & 63;
   // wave-uniform (readfirstlane): the cell's record and bookkeeping are
   // loaded once per wave into scalar registers
-  const int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kBS / 64) + (threadIdx.x >> 6)));
+  int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kBS / 64) + (threadIdx.x >> 6)));
   if (k >= kn) return;
   if (k >= cbase[nl]) {
     if (lane == 0) {
@@ -717,26 +875,28 @@ __global__ void __launch_bounds__(kBS) k_walk_stage(TreeView t, int32_t c0, int3
     }
     return;
   }
-  const int32_t i = kcell[k];
+  int32_t i = uniform(kcell[k]);
+  if (chunk >= kSiblingChunk) k = sibling_order(t, c0, nl, cbase, k, i);
   const int32_t X = c0 + i;
-  const WalkCell cx = load_cell(t.rec, X);
+  const WalkCell cx = load_cell_uniform(t.rec, X);
   const int64_t e0 = (k - cbase[i]) * chunk;
   const int32_t n = (int32_t)min<int64_t>(chunk, gcnt[i] - e0);
   const int64_t e = gbeg[i] + e0;
-  EmitDst dst{0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, sl, {}, {}, k, regions[threadIdx.x >> 6]};
+  EmitDst dst{0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, sl, {}, {}, sl->ksec + 3 * kRegions * k};
 #pragma unroll
   for (int w = 0; w < 3; ++w) {
     const int64_t lo = stage_lo(*sl, w, e, k);
     dst.win[w] = sl->win[w] + lo;
-    dst.wcap[w] = stage_lo(*sl, w, e + n, k + 1) - lo;
+    const int64_t cap = stage_lo(*sl, w, e + n, k + 1) - lo;
+    dst.wcap[w] = (int32_t)min<int64_t>(cap, INT32_MAX / 2);  // (a longer one would not fit the device)
     dst.wsh |= spill_shift(dst.wcap[w]) << (8 * w);
   }
   int64_t tm = 0, tp = 0, tq = 0, td = 0, ts = 0;
-  bool over;
-  if (gq)
-    over = wave_walk<kStage, EXT>(t, X, cx, fy, e, n, gq + k * qcap, qcap, tm, tp, tq, td, ts, dst, dbg);
-  else
-    over = wave_walk<kStage, EXT>(t, X, cx, fy, e, n, queue[threadIdx.x >> 6], kQ, tm, tp, tq, td, ts, dst, dbg);
+  const bool over =
+      GQ ? wave_walk<kStage, EXT, true, DBG>(t, X, cx, fy, e, n, gq + k * qcap, qcap, tm, tp, tq,
+                                             td, ts, dst, dbg)
+         : wave_walk<kStage, EXT, false, DBG>(t, X, cx, fy, e, n, queue[threadIdx.x >> 6], kQ, tm,
+                                              tp, tq, td, ts, dst, dbg);
   if (lane == 0) {
     out.km[k] = tm;
     out.kp[k] = tp;
@@ -889,12 +1049,12 @@ __global__ void __launch_bounds__(kBS) k_walk_emit(TreeView t, int32_t c0, int64
   const int64_t S = ex.q[cbase[i + 1]] - ex.q[cbase[i]];
   int64_t tm = 0, tp = 0, tq = 0, td = 0, ts = 0;
   EmitDst dst{far_base + ex.m[k], near_base + ex.p[k], ex.r[cbase[i]], S, far_src, near_src, fy_n, fx_n, c0n,
-              ex.q[k] - ex.q[cbase[i]], nullptr, {}, {}, k, nullptr};
+              ex.q[k] - ex.q[cbase[i]], nullptr, {}, {}, nullptr};
   if (gq)
-    wave_walk<kEmit, EXT>(t, X, cx, fy, gbeg[i] + e0, n, gq + k * qcap, qcap, tm, tp, tq, td, ts, dst,
+    wave_walk<kEmit, EXT, true, false>(t, X, cx, fy, gbeg[i] + e0, n, gq + k * qcap, qcap, tm, tp, tq, td, ts, dst,
                           nullptr);
   else
-    wave_walk<kEmit, EXT>(t, X, cx, fy, gbeg[i] + e0, n, queue[threadIdx.x >> 6], kQ, tm, tp, tq, td, ts, dst,
+    wave_walk<kEmit, EXT, false, false>(t, X, cx, fy, gbeg[i] + e0, n, queue[threadIdx.x >> 6], kQ, tm, tp, tq, td, ts, dst,
                           nullptr);
 }
 
@@ -1038,7 +1198,7 @@ static size_t stage_layout(Ctx& c, int lev, int64_t F, int64_t kn, const double*
 
 int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32_t>& lo,
                     const std::vector<int32_t>& hi, int64_t& far_base, int64_t& near_base) {
-  TreeView t{(const WalkRec*)c.walkrec.p, c.theta, c.walk_abs_tol, c.walk_mode, c.opt.error_tol,
+  TreeView t{(const WalkRec*)c.walkrec.p, c.theta, c.theta * c.theta, c.walk_abs_tol, c.walk_mode, c.opt.error_tol,
              c.opt.theta_max, c.opt.theta_max * c.opt.theta_max, (const float*)c.model.p, c.opt.learned_min_work,
              c.walk_mode != 0 ? (const double*)c.gmin.p + 3 * (size_t)c.ncells : nullptr, nullptr};
   static const bool debug_env = getenv("AMFMM_DEBUG_WALK") != nullptr;
@@ -1145,9 +1305,16 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
       AMFMM_HIP(hipEventRecord(e0, c.stream));
     }
     mark(c, kPhWalkPass);
-    hipLaunchKernelGGL(ext == kExtLearned     ? k_walk_stage<kExtLearned>
-                       : ext == kExtMultipole ? k_walk_stage<kExtMultipole>
-                                              : k_walk_stage<kExtBase>,
+    auto stage_kernel = [&](auto in_global, auto with_dbg) {
+      constexpr bool Q = decltype(in_global)::value, D = decltype(with_dbg)::value;
+      return ext == kExtLearned     ? k_walk_stage<kExtLearned, Q, D>
+             : ext == kExtMultipole ? k_walk_stage<kExtMultipole, Q, D>
+                                    : k_walk_stage<kExtBase, Q, D>;
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    hipLaunchKernelGGL(gq ? (debug ? stage_kernel(yes, yes) : stage_kernel(yes, no))
+                          : (debug ? stage_kernel(no, yes) : stage_kernel(no, no)),
                        dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, nl, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
                        (const int32_t*)gcnt, fy, (const StageLayout*)sl_dev, kc, nov, gq, qcap, dbg);
     ++c.pass_launches;
