@@ -786,6 +786,12 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
 }
 constexpr int kChunkMax = 4096;               // frontier entries per wave: at most this many,
 constexpr int64_t kWavesPerLevel = 1 << 17;   // aiming at about this many waves per level
+// FP64, where the order of a cell's pairs is free (see walk_levels): chunks long
+// enough to fill the lanes.  At 131072 waves a level of 10^5 particles has one
+// to nine entries in each (11 lanes of 64 busy); 131072 / 32768 / 8192 waves:
+// the pass takes 0.94 / 0.54 / 0.42 ms at 100003 particles, 2.66 / 1.59 / 1.33 at
+// 2^20, 10.4 / 9.5 / 9.4 at 2^22 (theta 0.35).
+constexpr int64_t kWavesPerLevel64 = 1 << 13;
 constexpr int64_t kGlobalQueueBytes = int64_t(1) << 31;  // global work queues of a level: at most this many bytes,
 constexpr int32_t kGlobalQueueMax = 1 << 18;  // at most this many entries per wave, used when at least 4 kQ
 
@@ -1219,6 +1225,14 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
   // global work queues: at most kGlobalQueueBytes, an eighth of an arena (both
   // a quarter of that in the second attempt of an arena's solve)
   const int64_t queue_limit = c.arena ? (int64_t)(fr / (c.arena_tight ? 32 : 8)) : kGlobalQueueBytes;
+  // FP64 sums do not depend on the order of a cell's pairs beyond rounding;
+  // mixed ones add FP32 blocks of neighbouring list entries, so there the
+  // chunks (and with them the order) stay as they are whatever is fastest
+  const bool ordered = c.opt.precision != AMFMM_FP64;
+  const int64_t waves = ordered ? kWavesPerLevel : kWavesPerLevel64;
+  auto chunk_of = [&](int64_t entries) {
+    return (int32_t)std::min<int64_t>(kChunkMax, std::max<int64_t>(1, (entries + waves - 1) / waves));
+  };
   double prev[3];
   bool have_prev = false;
   int64_t cand = 0;  // candidate pairs, counted once the levels are done (a batch over budget is walked again)
@@ -1231,7 +1245,7 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     const size_t L = (size_t)nl + 1;
     // enough waves to fill the chip (small frontiers: one entry per wave),
     // few enough that dispatch does not dominate
-    const int32_t chunk = (int32_t)std::min<int64_t>(kChunkMax, std::max<int64_t>(1, (F + kWavesPerLevel - 1) / kWavesPerLevel));
+    const int32_t chunk = chunk_of(F);
     int64_t *gbeg, *gbeg_n;
     int32_t *gcnt, *gcnt_n;
     group_ptrs(c, c.grp_cur, &gbeg, &gcnt);
@@ -1250,10 +1264,12 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
       AMFMM_HIP(hipGetLastError());
       scan_i64(c, ScanSet<int64_t>{{nck}, {nck + L}}, 1, nl);
       cbase = nck + L;
-      if (chunk > 1) {
+      if (chunk > 1 && ordered) {
         AMFMM_HIP(hipMemcpyAsync(tot_host, cbase + nl, sizeof(int64_t), hipMemcpyDeviceToHost, c.stream));
         sync(c);
         kn = tot_host[0];
+      } else if (chunk > 1) {
+        kn = std::min(F, F / chunk + nl);
       }
       int32_t* map = (int32_t*)ensure(c, c.fx, sizeof(int32_t) * (kn + 1));
       hipLaunchKernelGGL(k_chunk_map, dim3(blocks_for(kn, kBS)), dim3(kBS), 0, c.stream, nl, cbase, kn, map);
@@ -1268,13 +1284,15 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     int64_t* tot = w + 13 * K;
     const int32_t* fy = as<int32_t>(c.fy);
     const unsigned kgrid = blocks_for(kn, kBS / 64);
-    // few chunks: a larger work queue per wave, in global memory
+    // few chunks: a larger work queue per wave, in global memory (a chunk's
+    // queue never holds more than the tree's cells)
     int32_t* gq = nullptr;
     int32_t qcap = kQ;
-    {
+    if (c.ncells > kQ) {
       int64_t g = kGlobalQueueMax;
       while (g > 4 * kQ && (int64_t)sizeof(int32_t) * g * kn > queue_limit) g >>= 1;
       if ((int64_t)sizeof(int32_t) * g * kn <= queue_limit) {
+        while (g / 2 >= c.ncells) g >>= 1;
         qcap = (int32_t)g;
         gq = (int32_t*)ensure_top(c, c.gqueue, sizeof(int32_t) * (size_t)kn * qcap);
       }
@@ -1359,7 +1377,7 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
                                               sizeof(int32_t) * near_base);
     int32_t* fy_n = (int32_t*)ensure(c, c.fy2, sizeof(int32_t) * (Fn + 1));
     // the next level's cells with its entries, where each will be a chunk
-    c.frontier_mapped = Fn <= kWavesPerLevel;
+    c.frontier_mapped = chunk_of(Fn) == 1;
     int32_t* fx_n = c.frontier_mapped ? (int32_t*)ensure(c, c.fx2, sizeof(int32_t) * (Fn + 1)) : nullptr;
     if (novh < kn)
       hipLaunchKernelGGL(k_walk_compact, dim3(blocks_for(kn, kBS / 64)), dim3(kBS), 0, c.stream, t, c0, kn, chunk,
