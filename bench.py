@@ -32,7 +32,7 @@ FP64 one: times, errors, residuals), `order4` (the same step at expansion
 order 4, the appendix's general order, with its own tolerance and leaf size:
 time, error, balances; outside the timed region, the headline stays the
 quadrupole-order solve with the configuration's n_crit = 25) and the median
-of the per-step HIP-event totals.
+of the per-step device-clock totals.
 """
 import argparse
 import hashlib
@@ -284,12 +284,12 @@ def main():
         torch.cuda.synchronize()
         print(f"# warmup {i} done", file=sys.stderr, flush=True)
     phases, pphases = {}, {}
-    step_ms = []  # per step: the solves' HIP-event totals (pilot + solve)
+    step_ms = []  # per step: the solves' device-clock totals (pilot + solve)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for i in range(a.steps):
         step()
-        ph = solver.get_phase_times()  # HIP events on the solver's stream
+        ph = solver.get_phase_times()  # device clock at the phase changes
         for k, v in ph.items():
             phases[k] = phases.get(k, 0.0) + v
         pt = 0.0
@@ -327,7 +327,7 @@ def main():
 
     # Roofline of the step's three large kernels; the one with the most time is
     # the dominant kernel (the top-level object), the others sit beside it.
-    # Each is bracketed by HIP events on the library's stream (a phase holds
+    # Each is bracketed by device clock values (a phase holds
     # exactly that kernel's launches), so phase time / launches is the average
     # launch duration.
     cfg_key = {"n": a.n, "criterion": a.criterion, "eps": a.eps if field else None,

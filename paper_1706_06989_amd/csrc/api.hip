@@ -178,17 +178,36 @@ static DevBuf* all_bufs(Ctx& c, int i) {
   return i < nv ? v[i] : nullptr;
 }
 
+static __global__ void k_take_time(unsigned long long* word) { take_time(word); }
+
 void mark(Ctx& c, int phase) {
-  if (c.arena) return;  // the allocation-free solve creates no events
-  if (c.ev_used == c.ev_pool.size()) {
-    hipEvent_t e;
-    AMFMM_HIP(hipEventCreate(&e));
-    c.ev_pool.push_back(e);
-    c.ev_phase.push_back(0);
+  if (c.arena) return;  // the allocation-free solve records no times
+  if (!c.st_pending) {
+    if (c.st_phase.size() + 1 >= (size_t)kMaxStamps) return;  // (one left for the end)
+    c.st_phase.push_back(phase);
   }
-  AMFMM_HIP(hipEventRecord(c.ev_pool[c.ev_used], c.stream));
-  c.ev_phase[c.ev_used] = phase;
-  ++c.ev_used;
+  c.st_phase.back() = phase;
+  c.st_pending = true;
+}
+
+unsigned long long* clock_word(Ctx& c) {
+  if (!c.st_pending) return nullptr;
+  c.st_pending = false;
+  return c.stamps + c.st_phase.size() - 1;
+}
+
+void end_timeline(Ctx& c) {
+  if (c.arena) return;
+  if (!c.st_pending) c.st_phase.push_back(kPhEnd);
+  c.st_phase.back() = kPhEnd;
+  c.st_pending = false;
+  hipLaunchKernelGGL(k_take_time, dim3(1), dim3(1), 0, c.stream, c.stamps + c.st_phase.size() - 1);
+  AMFMM_HIP(hipGetLastError());
+}
+
+// a later call goes on with the timeline that an earlier one has ended
+static void continue_timeline(Ctx& c) {
+  if (!c.st_phase.empty() && c.st_phase.back() == kPhEnd) c.st_phase.pop_back();
 }
 
 // Scratch of the allocation-free solve: one array in the library's code
@@ -361,7 +380,18 @@ int amfmm_create(const amfmm_options* opt, void* stream, amfmm_ctx** out) {
     delete ctx;
     return AMFMM_E_HIP;
   }
+  int khz = 0;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, ctx->c.device) == hipSuccess && khz > 0)
+    ctx->c.clock_khz = khz;
+  else
+    (void)hipGetLastError();
+  if (hipMalloc((void**)&ctx->c.stamps, amfmm::kMaxStamps * sizeof(unsigned long long)) != hipSuccess) {
+    (void)hipGetLastError();
+    delete ctx;
+    return AMFMM_E_HIP;
+  }
   if (hipHostMalloc((void**)&ctx->c.pinned, amfmm::kPinWords * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+    (void)hipFree(ctx->c.stamps);
     delete ctx;
     return AMFMM_E_HIP;
   }
@@ -369,6 +399,7 @@ int amfmm_create(const amfmm_options* opt, void* stream, amfmm_ctx** out) {
     (void)amfmm::device_scratch(ctx->c.device);  // the allocation-free solve's array on this device
   } catch (const Error&) {
     (void)hipHostFree(ctx->c.pinned);
+    (void)hipFree(ctx->c.stamps);
     delete ctx;
     return AMFMM_E_HIP;
   }
@@ -381,7 +412,7 @@ int amfmm_destroy(amfmm_ctx* ctx) {
   Ctx& c = ctx->c;
   (void)hipStreamSynchronize(c.stream);
   for (int i = 0; amfmm::all_bufs(c, i); ++i) amfmm::release(c, *amfmm::all_bufs(c, i));
-  for (auto& e : c.ev_pool) (void)hipEventDestroy(e);
+  if (c.stamps) (void)hipFree(c.stamps);
   if (c.pinned) (void)hipHostFree(c.pinned);
   delete ctx;
   return AMFMM_OK;
@@ -480,7 +511,8 @@ static int build_tree_impl(Ctx& c, int64_t n, const double* x, const double* y, 
   if (n < 1 || n >= (int64_t)INT32_MAX) return fail(c, AMFMM_E_INVALID, "n must be in [1, 2^31)");
   if (!x || !y || !z || !m) return fail(c, AMFMM_E_INVALID, "null input pointer");
   c.have_tree = c.have_moments = c.have_lists = false;
-  c.ev_used = 0;
+  c.st_phase.clear();
+  c.st_pending = false;
   amfmm::mark(c, amfmm::kPhValidate);
   amfmm::bbox_start(c, x, y, z, m, n);
   amfmm::mark(c, amfmm::kPhSort);
@@ -489,39 +521,45 @@ static int build_tree_impl(Ctx& c, int64_t n, const double* x, const double* y, 
   const int st = amfmm::build_levels(c);
   if (st == AMFMM_E_NONFINITE) return fail(c, st, "non-finite position or mass");
   if (st != AMFMM_OK) return fail(c, st, "masses must be positive");
-  amfmm::mark(c, amfmm::kPhEnd);
   c.have_tree = true;
   return AMFMM_OK;
 }
 
 int amfmm_build_tree(amfmm_ctx* ctx, int64_t n, const double* x, const double* y, const double* z,
                      const double* m) {
-  return guarded(ctx, [&](Ctx& c) -> int { return build_tree_impl(c, n, x, y, z, m); });
+  return guarded(ctx, [&](Ctx& c) -> int {
+    const int st = build_tree_impl(c, n, x, y, z, m);
+    if (!st) amfmm::end_timeline(c);
+    return st;
+  });
 }
 
 static int moments_impl(Ctx& c) {
   if (!c.have_tree) return fail(c, AMFMM_E_STATE, "compute_moments needs build_tree");
-  if (c.ev_used) --c.ev_used;  // continue the timeline of the tree build
+  amfmm::continue_timeline(c);
   amfmm::mark(c, amfmm::kPhMoments);
   amfmm::upward_pass(c);
   if (c.opt.order != 3) amfmm::order_upward(c);
   amfmm::far_prepare(c);
-  amfmm::mark(c, amfmm::kPhEnd);
   return AMFMM_OK;
 }
 
 int amfmm_compute_moments(amfmm_ctx* ctx) {
-  return guarded(ctx, [&](Ctx& c) -> int { return moments_impl(c); });
+  return guarded(ctx, [&](Ctx& c) -> int {
+    const int st = moments_impl(c);
+    if (!st) amfmm::end_timeline(c);
+    return st;
+  });
 }
 
 static int walk_impl(Ctx& c, double theta) {
   if (!(theta > 0.0 && theta <= 1.0)) return fail(c, AMFMM_E_INVALID, "theta must lie in (0, 1]");
   if (!c.have_moments) return fail(c, AMFMM_E_STATE, "walk needs compute_moments");
-  if (c.ev_used) --c.ev_used;
+  amfmm::continue_timeline(c);
   amfmm::mark(c, amfmm::kPhWalk);
   amfmm::dual_walk(c, theta);
   c.near_pairs_valid = false;
-  amfmm::mark(c, amfmm::kPhEnd);
+  amfmm::end_timeline(c);
   c.batched = false;
   c.far_evals = c.n_far;
   return AMFMM_OK;
@@ -545,16 +583,16 @@ static void evaluate_all(Ctx& c, double* ax, double* ay, double* az, double* pot
   mark(c, kPhFar);
   far_field(c, 0, c.ncells);
   mark(c, kPhPush);
-  for (int l = 1; l <= c.depth; ++l) push_down(c, c.level_start[l], c.level_start[l + 1]);
+  push_down_all(c);
   mark(c, kPhNear);
   near_field(c, (const int32_t*)c.leaves.p, 0, c.nleaves, ax, ay, az, pot);
-  mark(c, kPhEnd);
+  end_timeline(c);
 }
 
 static int evaluate_impl(Ctx& c, double* ax, double* ay, double* az, double* pot) {
   if (!c.have_lists) return fail(c, AMFMM_E_STATE, "evaluate needs walk");
   if (!ax || !ay || !az) return fail(c, AMFMM_E_INVALID, "null output pointer");
-  if (c.ev_used) --c.ev_used;
+  amfmm::continue_timeline(c);
   zero_counters(c);
   evaluate_all(c, ax, ay, az, pot);
   return AMFMM_OK;
@@ -717,7 +755,7 @@ static void solve_batched(Ctx& c, double theta, double* ax, double* ay, double* 
     for (int l = Ls; l <= c.depth; ++l) near_field(c, nullptr, blo[l], bhi[l] - blo[l], ax, ay, az, pot);
     x0 = x1;
   }
-  mark(c, kPhEnd);
+  end_timeline(c);
   c.have_lists = false;  // lists of the last batch only: not kept
   c.batched = true;
 }
@@ -734,7 +772,6 @@ static int solve_impl(Ctx& c, int64_t n, const double* x, const double* y, const
     int st = build_tree_impl(c, n, x, y, z, m);
     if (st) return st;
     if ((st = moments_impl(c))) return st;
-    if (c.ev_used) --c.ev_used;
     zero_counters(c);
     const double need = list_bytes_per_particle(theta) * (double)n;
     const size_t budget = list_budget(c);
@@ -847,7 +884,8 @@ int amfmm_solve_gravity_noalloc(amfmm_ctx* ctx, int64_t n, const double* x, cons
     } saved(c);
     c.arena = amfmm::device_scratch(c.device);
     c.arena_cap = amfmm::kNoAllocBytes;
-    c.ev_used = 0;
+    c.st_phase.clear();
+    c.st_pending = false;
     // a solve that runs out of room is run once more with the walk's transient
     // buffers held small (more of its chunks are then walked twice)
     for (c.arena_tight = false;; c.arena_tight = true) {
@@ -1036,16 +1074,14 @@ int amfmm_get_lists(amfmm_ctx* ctx, int32_t* far_ab, int32_t* near_ab) {
 int amfmm_get_phase_times(amfmm_ctx* ctx, double* ms, int32_t cap) {
   return guarded(ctx, [&](Ctx& c) -> int {
     if (!ms || cap < 0) return fail(c, AMFMM_E_INVALID, "bad arguments");
-    AMFMM_HIP(hipStreamSynchronize(c.stream));
+    // (a phase that no kernel has started yet is left out)
+    const size_t words = c.st_phase.size() - (c.st_pending ? 1 : 0);
+    const auto w = fetch<unsigned long long>(c, c.stamps, words);
     double t[amfmm::kPhEnd + 1] = {};
-    for (size_t i = 0; i + 1 < c.ev_used; ++i) {
-      float v = 0.f;
-      if (hipEventElapsedTime(&v, c.ev_pool[i], c.ev_pool[i + 1]) != hipSuccess) {
-        (void)hipGetLastError();
-        v = 0.f;
-      }
-      const int ph = c.ev_phase[i];
-      if (ph >= 0 && ph < amfmm::kPhEnd) t[ph] += v;
+    for (size_t i = 0; i + 1 < words; ++i) {
+      const int ph = c.st_phase[i];
+      // (blocks of two kernels may start in either order)
+      if (ph >= 0 && ph < amfmm::kPhEnd && w[i + 1] > w[i]) t[ph] += (double)(w[i + 1] - w[i]) / (double)c.clock_khz;
     }
     // [0..7] phases (the walk including its pass), [8] total, [9] walk pass
     const double pass = t[amfmm::kPhWalkPass];

@@ -97,7 +97,9 @@ template <int VARIANT>
 __global__ void __launch_bounds__(kBS) k_far_rec(int32_t c_lo, int32_t nc, const FarRec* __restrict__ rec,
                                                  const int64_t* __restrict__ fstart,
                                                  const int32_t* __restrict__ fcount,
-                                                 const int32_t* __restrict__ fsrc, double* __restrict__ loc) {
+                                                 const int32_t* __restrict__ fsrc, double* __restrict__ loc,
+                                                 unsigned long long* clock) {
+  take_time(clock);
   const int lane = threadIdx.x & 63;
   const int32_t Xi = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6)));
   if (Xi >= nc) return;
@@ -153,7 +155,9 @@ __global__ void __launch_bounds__(kBS) k_far_rec(int32_t c_lo, int32_t nc, const
 template <int VARIANT, bool MIXED>
 __global__ void __launch_bounds__(kBS) k_far(int32_t c_lo, int32_t nc, const double4* __restrict__ geo, const double* __restrict__ mom,
                                              const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount,
-                                             const int32_t* __restrict__ fsrc, double* __restrict__ loc, double eps2) {
+                                             const int32_t* __restrict__ fsrc, double* __restrict__ loc, double eps2,
+                                             unsigned long long* clock) {
+  take_time(clock);
   const int lane = threadIdx.x & 63;
   const int32_t Xi = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6)));
   if (Xi >= nc) return;
@@ -220,12 +224,9 @@ __global__ void __launch_bounds__(kBS) k_far(int32_t c_lo, int32_t nc, const dou
   }
 }
 
-// loc[child] += Taylor shift of loc[parent] to the child's centre
-__global__ void __launch_bounds__(kBS) k_l2l(int32_t c0, int32_t nl, const int32_t* __restrict__ par,
-                                             const double4* __restrict__ geo, double* __restrict__ loc) {
-  int32_t i = blockIdx.x * kBS + threadIdx.x;
-  if (i >= nl) return;
-  const int32_t c = c0 + i;
+// loc[c] += Taylor shift of its parent's coefficients to its centre
+__device__ inline void l2l_cell(int32_t c, const int32_t* __restrict__ par, const double4* __restrict__ geo,
+                                double* loc) {
   const int32_t P = par[c];
   const double4 gc = geo[c], gp = geo[P];
   const double d[3] = {gc.x - gp.x, gc.y - gp.y, gc.z - gp.z};
@@ -270,14 +271,40 @@ __global__ void __launch_bounds__(kBS) k_l2l(int32_t c0, int32_t nl, const int32
   for (int i2 = 0; i2 < 3; ++i2) o[20 + i2] += L[20 + i2];
 }
 
-__global__ void k_zero_u64_n(unsigned long long* p, int n) {
+__global__ void __launch_bounds__(kBS) k_l2l(int32_t c0, int32_t nl, const int32_t* __restrict__ par,
+                                             const double4* __restrict__ geo, double* loc, unsigned long long* clock) {
+  take_time(clock);
+  const int32_t i = blockIdx.x * kBS + threadIdx.x;
+  if (i < nl) l2l_cell(c0 + i, par, geo, loc);
+}
+
+// The top levels, downwards, in one block: a launch each (3 us) costs as much
+// as their work while a level is at most a few hundred cells.
+constexpr int kTopBS = 512;
+struct TopLevels {
+  int32_t n;  // levels 1 .. n-1
+  int32_t start[kMaxLevel + 2];
+};
+
+__global__ void __launch_bounds__(kTopBS) k_l2l_top(TopLevels t, const int32_t* __restrict__ par,
+                                                    const double4* __restrict__ geo, double* loc,
+                                                    unsigned long long* clock) {
+  take_time(clock);
+  for (int l = 1; l < t.n; ++l) {
+    for (int32_t c = t.start[l] + threadIdx.x; c < t.start[l + 1]; c += kTopBS) l2l_cell(c, par, geo, loc);
+    __syncthreads();
+  }
+}
+
+__global__ void k_zero_u64_n(unsigned long long* p, int n, unsigned long long* clock) {
+  take_time(clock);
   if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
 }
 
 }  // namespace
 
-void zero_u64(Ctx& c, unsigned long long* p, int n) {
-  hipLaunchKernelGGL(k_zero_u64_n, dim3(1), dim3(64), 0, c.stream, p, n);
+void zero_u64(Ctx& c, unsigned long long* p, int n, unsigned long long* clock) {
+  hipLaunchKernelGGL(k_zero_u64_n, dim3(1), dim3(64), 0, c.stream, p, n, clock);
   AMFMM_HIP(hipGetLastError());
 }
 
@@ -310,14 +337,14 @@ void far_field(Ctx& c, int32_t c_lo, int32_t c_hi) {
     ++c.far_launches;
     hipLaunchKernelGGL(c.opt.variant == AMFMM_TC ? k_far_rec<AMFMM_TC> : k_far_rec<AMFMM_UC>, grid, dim3(kBS), 0,
                        c.stream, c_lo, nc, (const FarRec*)c.farrec.p, (const int64_t*)c.far_start.p,
-                       (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc);
+                       (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc, clock_word(c));
     AMFMM_HIP(hipGetLastError());
     return;
   }
   auto args = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(kBS), 0, c.stream, c_lo, nc, (const double4*)c.geo.p, (const double*)c.mom.p,
                        (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc,
-                       c.opt.softening * c.opt.softening);
+                       c.opt.softening * c.opt.softening, clock_word(c));
   };
   ++c.far_launches;
   const bool mixed = c.opt.precision == AMFMM_MIXED;
@@ -329,6 +356,20 @@ void far_field(Ctx& c, int32_t c_lo, int32_t c_hi) {
   AMFMM_HIP(hipGetLastError());
 }
 
+void push_down_all(Ctx& c) {
+  int l = 1;
+  if (c.opt.order == 3 && c.depth >= 1) {
+    TopLevels top{};
+    for (top.n = 1; top.n <= c.depth && c.level_start[top.n + 1] - c.level_start[top.n] <= kTopBS;) ++top.n;
+    std::copy(c.level_start.begin(), c.level_start.end(), top.start);
+    hipLaunchKernelGGL(k_l2l_top, dim3(1), dim3(kTopBS), 0, c.stream, top, as<int32_t>(c.c_parent),
+                       (const double4*)c.geo.p, as<double>(c.loc), clock_word(c));
+    AMFMM_HIP(hipGetLastError());
+    l = top.n;
+  }
+  for (; l <= c.depth; ++l) push_down(c, c.level_start[l], c.level_start[l + 1]);
+}
+
 void push_down(Ctx& c, int32_t c_lo, int32_t c_hi) {
   const int32_t nl = c_hi - c_lo;
   if (nl <= 0) return;
@@ -337,7 +378,7 @@ void push_down(Ctx& c, int32_t c_lo, int32_t c_hi) {
     return;
   }
   hipLaunchKernelGGL(k_l2l, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, c_lo, nl, as<int32_t>(c.c_parent),
-                     (const double4*)c.geo.p, as<double>(c.loc));
+                     (const double4*)c.geo.p, as<double>(c.loc), clock_word(c));
   AMFMM_HIP(hipGetLastError());
 }
 

@@ -129,11 +129,12 @@ struct Ctx {
   int hint_mode = -1;
   double theta = 0.5;
   bool have_tree = false, have_moments = false, have_lists = false;
-  // timing: events recorded at phase changes; the time between two marks
-  // belongs to the phase of the first
-  std::vector<hipEvent_t> ev_pool;
-  std::vector<int> ev_phase;
-  size_t ev_used = 0;
+  // timing: device clock values taken by the first kernel of each phase; the
+  // time between two belongs to the phase of the first
+  unsigned long long* stamps = nullptr;  // kMaxStamps device words
+  std::vector<int> st_phase;             // phase of every word taken so far
+  bool st_pending = false;               // the last word waits for its kernel
+  int clock_khz = 100000;
   // allocation-free solve: while arena is set, every device buffer is carved
   // from [arena, arena + arena_cap) (a static device array) instead of being
   // allocated (first fit over the free blocks, released blocks merged with
@@ -171,7 +172,7 @@ struct ScanSet {
   const T* in[kScanMax];
   T* out[kScanMax];
 };
-void scan_i64(Ctx& c, const ScanSet<int64_t>& set, int count, int64_t n);
+void scan_i64(Ctx& c, const ScanSet<int64_t>& set, int count, int64_t n, unsigned long long* clock = nullptr);
 
 // ---- sort.hip ----
 // stable LSD radix sort of (key, value) pairs by the low `bits` bits of key;
@@ -214,12 +215,13 @@ void order_push_down(Ctx& c, int32_t c_lo, int32_t c_hi);
 void order_l2p(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, double* ax, double* ay, double* az,
                double* pot);
 void push_down(Ctx& c, int32_t c_lo, int32_t c_hi);  // cells of one level
+void push_down_all(Ctx& c);                         // every level, downwards
 // leaves != nullptr: the first `count` leaves of that list; else the leaves
 // among cells [c_lo, c_lo + count)
 void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, double* ax, double* ay, double* az,
                 double* pot);
 // fills n (<= 64) device words with zero (a kernel, so it can sit in a graph)
-void zero_u64(Ctx& c, unsigned long long* p, int n);
+void zero_u64(Ctx& c, unsigned long long* p, int n, unsigned long long* clock = nullptr);
 
 // ---- mlp.hip ----
 // features (8 floats) and labels (log2 error factor) of cell pairs (device)
@@ -253,7 +255,19 @@ void balance(Ctx& c, int64_t n, const double* x, const double* y, const double* 
 // kPhWalkPass: the walk's one pass over the pairs (its staging kernel), a part
 // of the walk that is also reported on its own
 enum Phase { kPhValidate = 0, kPhSort, kPhTree, kPhMoments, kPhWalk, kPhFar, kPhPush, kPhNear, kPhWalkPass, kPhEnd };
-void mark(Ctx& c, int phase);  // records an event; phase kPhEnd closes the timeline
+// A phase starts: the next kernel given clock_word(c) writes the device clock
+// there as it starts (a phase whose kernels are not launched takes no time).
+// An event per phase costs 3.7 us on the stream, and a solve of ten levels had
+// 28 of them.
+constexpr int kMaxStamps = 1 << 15;  // beyond, the last phase takes the rest
+void mark(Ctx& c, int phase);
+unsigned long long* clock_word(Ctx& c);
+void end_timeline(Ctx& c);  // the last phase ends here
+#ifdef __HIPCC__
+__device__ inline void take_time(unsigned long long* word) {
+  if (word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *word = wall_clock64();
+}
+#endif
 
 inline unsigned blocks_for(int64_t n, int threads) {
   return (unsigned)((n + threads - 1) / threads);

@@ -45,7 +45,9 @@ __device__ inline void add_about(double* M2, double* M3, double mu, double x, do
 __global__ void __launch_bounds__(kBS) k_leaf_moments(const double4* __restrict__ pos, const int32_t* __restrict__ leaves,
                                                       int32_t nleaves, const int32_t* __restrict__ beg,
                                                       const int32_t* __restrict__ cnt, double4* __restrict__ geo,
-                                                      double* __restrict__ mom, double4* __restrict__ msum) {
+                                                      double* __restrict__ mom, double4* __restrict__ msum,
+                                                      unsigned long long* clock) {
+  take_time(clock);
   int32_t i = blockIdx.x * kBS + threadIdx.x;
   if (i >= nleaves) return;
   int32_t c = leaves[i];
@@ -291,7 +293,8 @@ void upward_pass(Ctx& c) {
   const int32_t* beg = as<int32_t>(c.c_begin);
   const int32_t* cnt = as<int32_t>(c.c_count);
   hipLaunchKernelGGL(k_leaf_moments, dim3(blocks_for(c.nleaves, kBS)), dim3(kBS), 0, c.stream,
-                     (const double4*)c.pos4.p, as<int32_t>(c.leaves), c.nleaves, beg, cnt, geo, mom, msum);
+                     (const double4*)c.pos4.p, as<int32_t>(c.leaves), c.nleaves, beg, cnt, geo, mom, msum,
+                     clock_word(c));
   AMFMM_HIP(hipGetLastError());
   TopLevels top{};
   while (top.n <= c.depth && c.level_start[top.n + 1] - c.level_start[top.n] <= kTopCells) ++top.n;

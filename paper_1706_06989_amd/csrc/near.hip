@@ -693,7 +693,7 @@ void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doub
   const int32_t* beg = as<int32_t>(c.c_begin);
   const int32_t* cnt = as<int32_t>(c.c_count);
   const int64_t* parts = (const int64_t*)c.near_parts.p;
-  zero_u64(c, plan.words + 2, 4);
+  zero_u64(c, plan.words + 2, 4, clock_word(c));
   hipLaunchKernelGGL(k_near_cost, dim3(blocks_for(count, kBS)), dim3(kBS), 0, c.stream, count, leaves, c_lo, nch, cnt,
                      parts, plan.words);
   if (plan.cut)

@@ -381,7 +381,9 @@ __global__ void __launch_bounds__(kBS) k_mono_up(int32_t c0, int32_t nl, const i
 __global__ void __launch_bounds__(kBS) k_far_order(int32_t c_lo, int32_t nc, const double4* __restrict__ geo,
                                                    const double* __restrict__ mono, const int64_t* __restrict__ fstart,
                                                    const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc,
-                                                   double* __restrict__ locg, double* __restrict__ loc, double eps2) {
+                                                   double* __restrict__ locg, double* __restrict__ loc, double eps2,
+                                                   unsigned long long* clock) {
+  take_time(clock);
   const int lane = threadIdx.x & 63;
   const int32_t Xi = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6)));
   if (Xi >= nc) return;
@@ -473,7 +475,9 @@ __global__ void __launch_bounds__(kBS) k_corr_order(int32_t c_lo, int32_t nc, co
 // L'_alpha = sum_gamma L_(alpha+gamma) d^gamma / gamma!, d = Z_child - Z_parent;
 // g_c adds (one thread per child)
 __global__ void __launch_bounds__(kBS) k_l2l_order(int32_t c0, int32_t nl, const int32_t* __restrict__ par,
-                                                   const double4* __restrict__ geo, double* __restrict__ locg) {
+                                                   const double4* __restrict__ geo, double* __restrict__ locg,
+                                                   unsigned long long* clock) {
+  take_time(clock);
   const int32_t i = blockIdx.x * kBS + threadIdx.x;
   if (i >= nl) return;
   const int32_t c = c0 + i;
@@ -572,7 +576,7 @@ void order_far(Ctx& c, int32_t c_lo, int32_t c_hi, double* loc) {
   hipLaunchKernelGGL(k_far_order, dim3(blocks_for(nc, kWaves)), dim3(kBS), 0, c.stream, c_lo, nc,
                      (const double4*)c.geo.p, (const double*)c.mono.p, (const int64_t*)c.far_start.p,
                      (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, locg, loc,
-                     c.opt.softening * c.opt.softening);
+                     c.opt.softening * c.opt.softening, clock_word(c));
   AMFMM_HIP(hipGetLastError());
   if (c.opt.variant != AMFMM_UC) {
     hipLaunchKernelGGL(k_corr_order, dim3(blocks_for(nc, kWaves)), dim3(kBS), 0, c.stream, c_lo, nc,
@@ -587,7 +591,7 @@ void order_push_down(Ctx& c, int32_t c_lo, int32_t c_hi) {
   const int32_t nl = c_hi - c_lo;
   if (nl <= 0) return;
   hipLaunchKernelGGL(k_l2l_order, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, c_lo, nl,
-                     as<int32_t>(c.c_parent), (const double4*)c.geo.p, as<double>(c.locg));
+                     as<int32_t>(c.c_parent), (const double4*)c.geo.p, as<double>(c.locg), clock_word(c));
   AMFMM_HIP(hipGetLastError());
 }
 

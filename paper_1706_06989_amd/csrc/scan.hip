@@ -45,7 +45,9 @@ __device__ T block_excl_scan(T v, T* tot) {
 
 // block sums of every array of the set (blockIdx.y)
 template <typename T>
-__global__ void __launch_bounds__(kBS) k_reduce(ScanSet<T> set, int64_t n, T* __restrict__ bsum) {
+__global__ void __launch_bounds__(kBS) k_reduce(ScanSet<T> set, int64_t n, T* __restrict__ bsum,
+                                                unsigned long long* clock) {
+  take_time(clock);
   const T* __restrict__ in = set.in[blockIdx.y];
   const int64_t base = (int64_t)blockIdx.x * kChunk;
   T s = 0;
@@ -62,7 +64,9 @@ __global__ void __launch_bounds__(kBS) k_reduce(ScanSet<T> set, int64_t n, T* __
 // scans one chunk per block of every array of the set; the block's offset is
 // the sum of the block sums before it; writes out[0..n) and out[n] = total
 template <typename T>
-__global__ void __launch_bounds__(kBS) k_scan_chunk(ScanSet<T> set, int64_t n, const T* __restrict__ bsum) {
+__global__ void __launch_bounds__(kBS) k_scan_chunk(ScanSet<T> set, int64_t n, const T* __restrict__ bsum,
+                                                    unsigned long long* clock) {
+  take_time(clock);
   __shared__ T tile[kChunk];
   const T* in = set.in[blockIdx.y];
   T* out = set.out[blockIdx.y];
@@ -106,7 +110,7 @@ __global__ void k_zero_heads(ScanSet<T> set) {
 }
 
 template <typename T>
-void scan_impl(Ctx& c, const ScanSet<T>& set, int count, int64_t n) {
+void scan_impl(Ctx& c, const ScanSet<T>& set, int count, int64_t n, unsigned long long* clock = nullptr) {
   if (n <= 0) {
     hipLaunchKernelGGL(k_zero_heads<T>, dim3(1), dim3(count), 0, c.stream, set);
     AMFMM_HIP(hipGetLastError());
@@ -115,8 +119,9 @@ void scan_impl(Ctx& c, const ScanSet<T>& set, int count, int64_t n) {
   const int64_t nb = (n + kChunk - 1) / kChunk;
   T* bsum = (T*)ensure(c, c.scratch, sizeof(T) * (size_t)(nb * count));
   const dim3 grid((unsigned)nb, (unsigned)count);
-  if (nb > 1) hipLaunchKernelGGL(k_reduce<T>, grid, dim3(kBS), 0, c.stream, set, n, bsum);
-  hipLaunchKernelGGL(k_scan_chunk<T>, grid, dim3(kBS), 0, c.stream, set, n, (const T*)bsum);
+  if (nb > 1) hipLaunchKernelGGL(k_reduce<T>, grid, dim3(kBS), 0, c.stream, set, n, bsum, clock);
+  hipLaunchKernelGGL(k_scan_chunk<T>, grid, dim3(kBS), 0, c.stream, set, n, (const T*)bsum,
+                     nb > 1 ? nullptr : clock);
   AMFMM_HIP(hipGetLastError());
 }
 
@@ -125,6 +130,8 @@ void scan_impl(Ctx& c, const ScanSet<T>& set, int count, int64_t n) {
 void scan_i32(Ctx& c, const int32_t* in, int32_t* out, int64_t n) {
   scan_impl<int32_t>(c, ScanSet<int32_t>{{in}, {out}}, 1, n);
 }
-void scan_i64(Ctx& c, const ScanSet<int64_t>& set, int count, int64_t n) { scan_impl<int64_t>(c, set, count, n); }
+void scan_i64(Ctx& c, const ScanSet<int64_t>& set, int count, int64_t n, unsigned long long* clock) {
+  scan_impl<int64_t>(c, set, count, n, clock);
+}
 
 }  // namespace amfmm

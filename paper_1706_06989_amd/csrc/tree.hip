@@ -23,7 +23,9 @@ __device__ inline bool finite(double v) { return __builtin_isfinite(v); }
 // mass that is not positive (one pass over the inputs for both).
 __global__ void __launch_bounds__(kBS) k_bbox_partial(const double* __restrict__ x, const double* __restrict__ y,
                                                       const double* __restrict__ z, const double* __restrict__ m,
-                                                      int64_t n, double* __restrict__ part) {
+                                                      int64_t n, double* __restrict__ part,
+                                                      unsigned long long* clock) {
+  take_time(clock);
   double v6[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
   int bad = 0, badm = 0;
   for (int64_t i = (int64_t)blockIdx.x * kBS + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBS) {
@@ -93,7 +95,9 @@ __device__ inline uint64_t spread3(uint64_t v) {
 
 __global__ void __launch_bounds__(kBS) k_keys(const double* __restrict__ x, const double* __restrict__ y,
                                               const double* __restrict__ z, int64_t n, const double* __restrict__ box,
-                                              uint64_t* __restrict__ keys, int32_t* __restrict__ idx) {
+                                              uint64_t* __restrict__ keys, int32_t* __restrict__ idx,
+                                              unsigned long long* clock) {
+  take_time(clock);
   int64_t i = (int64_t)blockIdx.x * kBS + threadIdx.x;
   if (i >= n) return;
   const double lo[3] = {box[0], box[1], box[2]};
@@ -150,7 +154,8 @@ __device__ inline int shared_levels(uint64_t a, uint64_t b) {
 // cells of level l that start in the tile, hist[(2 l + 1) * nblk + blk] the leaves
 __global__ void __launch_bounds__(kTile) k_tree_levels(const uint64_t* __restrict__ keys, int32_t n, int n_crit,
                                                        uint16_t* __restrict__ info, int32_t* __restrict__ hist,
-                                                       int nblk) {
+                                                       int nblk, unsigned long long* clock) {
+  take_time(clock);
   // windows' levels + 1 of particles [tile - n_crit, tile + kTile) (0: none),
   // then their running maxima; n_crit is at most 4096
   __shared__ uint8_t w[2][kTile + 4096];
@@ -321,7 +326,8 @@ void bbox_start(Ctx& c, const double* x, const double* y, const double* z, const
   int nb = (int)std::min<int64_t>(kBBoxBlocks, (n + kBS - 1) / kBS);
   double* part = (double*)ensure(c, c.scratch2, sizeof(double) * 8 * (size_t)nb);
   double* box = (double*)ensure(c, c.bbox, sizeof(double) * 8);
-  hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(kBS), 0, c.stream, x, y, z, m, n, part);
+  hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(kBS), 0, c.stream, x, y, z, m, n, part,
+                     clock_word(c));
   hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kBS), 0, c.stream, (const double*)part, nb, box,
                      (double*)(c.pinned + kPinBox));
   AMFMM_HIP(hipGetLastError());
@@ -335,7 +341,7 @@ void build_keys_sort(Ctx& c, const double* x, const double* y, const double* z, 
   int32_t* p2 = (int32_t*)ensure(c, c.perm2, sizeof(int32_t) * n);
   double4* pos = (double4*)ensure(c, c.pos4, sizeof(double4) * n);
   hipLaunchKernelGGL(k_keys, dim3(blocks_for(n, kBS)), dim3(kBS), 0, c.stream, x, y, z, n,
-                     (const double*)c.bbox.p, keys, perm);
+                     (const double*)c.bbox.p, keys, perm, clock_word(c));
   AMFMM_HIP(hipGetLastError());
   radix_sort(c, keys, perm, k2, p2, n, 3 * kMaxLevel);
   hipLaunchKernelGGL(k_gather, dim3(blocks_for(n, kBS)), dim3(kBS), 0, c.stream, x, y, z, m, n,
@@ -353,7 +359,7 @@ int build_levels(Ctx& c) {
   uint16_t* info = (uint16_t*)(tot + rows);
   int64_t* host = c.pinned + kPinTree;
   hipLaunchKernelGGL(k_tree_levels, dim3(nblk), dim3(kTile), 0, c.stream, (const uint64_t*)c.keys.p, n, c.opt.n_crit,
-                     info, hist, nblk);
+                     info, hist, nblk, clock_word(c));
   hipLaunchKernelGGL(k_tree_scan, dim3((unsigned)rows), dim3(kTile), 0, c.stream, hist, nblk, tot, host);
   AMFMM_HIP(hipGetLastError());
   sync(c);

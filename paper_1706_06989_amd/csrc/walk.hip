@@ -309,7 +309,8 @@ __global__ void __launch_bounds__(kBS) k_pack_cells(int32_t nc, const double4* _
                                                     const double* __restrict__ mom, const int32_t* __restrict__ ch0,
                                                     const int32_t* __restrict__ nch, const int32_t* __restrict__ par,
                                                     const int32_t* __restrict__ cnt, const double* __restrict__ gmin,
-                                                    WalkRec* __restrict__ rec) {
+                                                    WalkRec* __restrict__ rec, unsigned long long* clock) {
+  take_time(clock);
   int32_t c = blockIdx.x * kBS + threadIdx.x;
   if (c >= nc) return;
   WalkRec w;
@@ -385,7 +386,9 @@ __global__ void __launch_bounds__(kBS) k_gscale(int32_t nc, const int32_t* __res
 // smallest leaf mass below every cell (leaves: their mass; parents: the
 // smallest over their children), for the subtree near-field test
 __global__ void __launch_bounds__(kBS) k_mmin_leaves(const int32_t* __restrict__ leaves, int32_t nleaves,
-                                                     const double* __restrict__ mom, double* __restrict__ mmin) {
+                                                     const double* __restrict__ mom, double* __restrict__ mmin,
+                                                     unsigned long long* clock) {
+  take_time(clock);
   int32_t i = blockIdx.x * kBS + threadIdx.x;
   if (i >= nleaves) return;
   const int32_t c = leaves[i];
@@ -865,7 +868,9 @@ k_walk_stage(TreeView t, int32_t c0, int32_t nl, int64_t kn, int32_t chunk,
                                                     const int64_t* __restrict__ gbeg, const int32_t* __restrict__ gcnt,
                                                     const int32_t* __restrict__ fy, const StageLayout* __restrict__ sl,
                                                     ChunkCounts out, unsigned long long* __restrict__ nov,
-                                                    int32_t* __restrict__ gq, int32_t qcap, unsigned long long* dbg) {
+                                                    int32_t* __restrict__ gq, int32_t qcap, unsigned long long* dbg,
+                                                    unsigned long long* clock) {
+  take_time(clock);
   __shared__ int32_t queue[GQ ? 1 : kBS / 64][GQ ? 1 : kQ];
   __shared__ float model[EXT == kExtLearned ? AMFMM_MLP_MODEL : 1];
   if (EXT == kExtLearned) t.lmodel = stage_model(t.model, model);
@@ -1064,7 +1069,8 @@ __global__ void __launch_bounds__(kBS) k_walk_emit(TreeView t, int32_t c0, int64
                           nullptr);
 }
 
-__global__ void k_walk_init(int64_t* gbeg, int32_t* gcnt, int32_t* fy, int32_t* fx) {
+__global__ void k_walk_init(int64_t* gbeg, int32_t* gcnt, int32_t* fy, int32_t* fx, unsigned long long* clock) {
+  take_time(clock);
   gbeg[0] = 0;
   gbeg[1] = 1;
   gcnt[0] = 1;
@@ -1073,7 +1079,8 @@ __global__ void k_walk_init(int64_t* gbeg, int32_t* gcnt, int32_t* fy, int32_t* 
 }
 
 // a level's staging layout and its cleared counters
-__global__ void k_walk_level(StageLayout v, StageLayout* out, unsigned long long* counters) {
+__global__ void k_walk_level(StageLayout v, StageLayout* out, unsigned long long* counters, unsigned long long* clock) {
+  take_time(clock);
   if (threadIdx.x < 16) counters[threadIdx.x] = 0ull;
   if (threadIdx.x == 0) *out = v;
 }
@@ -1094,7 +1101,7 @@ void walk_prepare(Ctx& c, double theta) {
     double* g = gm + nc;
     double* mm = g + nc;
     hipLaunchKernelGGL(k_mmin_leaves, dim3(blocks_for(c.nleaves, kBS)), dim3(kBS), 0, c.stream,
-                       as<int32_t>(c.leaves), c.nleaves, (const double*)c.mom.p, mm);
+                       as<int32_t>(c.leaves), c.nleaves, (const double*)c.mom.p, mm, clock_word(c));
     for (int l = c.depth - 1; l >= 0; --l) {
       const int32_t c0 = c.level_start[l], nl = c.level_start[l + 1] - c0;
       hipLaunchKernelGGL(k_mmin_up, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, c0, nl,
@@ -1114,7 +1121,7 @@ void walk_prepare(Ctx& c, double theta) {
   }
   hipLaunchKernelGGL(k_pack_cells, dim3(blocks_for(nc, kBS)), dim3(kBS), 0, c.stream, nc, (const double4*)c.geo.p,
                      (const double*)c.mom.p, as<int32_t>(c.c_child0), as<int32_t>(c.c_nchild),
-                     as<int32_t>(c.c_parent), as<int32_t>(c.c_count), gmin, rec);
+                     as<int32_t>(c.c_parent), as<int32_t>(c.c_count), gmin, rec, clock_word(c));
   AMFMM_HIP(hipGetLastError());
   ensure(c, c.far_start, sizeof(int64_t) * nc);
   ensure(c, c.far_count, sizeof(int32_t) * nc);
@@ -1149,7 +1156,7 @@ void walk_start(Ctx& c) {
   int32_t* gcnt;
   group_ptrs(c, 0, &gbeg, &gcnt);
   c.grp_cur = 0;
-  hipLaunchKernelGGL(k_walk_init, dim3(1), dim3(1), 0, c.stream, gbeg, gcnt, as<int32_t>(c.fy), as<int32_t>(c.fx));
+  hipLaunchKernelGGL(k_walk_init, dim3(1), dim3(1), 0, c.stream, gbeg, gcnt, as<int32_t>(c.fy), as<int32_t>(c.fx), clock_word(c));
   AMFMM_HIP(hipGetLastError());
   c.frontier = 1;
   c.frontier_mapped = true;
@@ -1315,7 +1322,7 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     unsigned long long* dbg = debug ? (unsigned long long*)(tot + 12) : nullptr;
     StageLayout* sl_dev = (StageLayout*)(tot + 20);
     static_assert(20 + sizeof(StageLayout) / sizeof(int64_t) <= 48, "walk totals");
-    hipLaunchKernelGGL(k_walk_level, dim3(1), dim3(64), 0, c.stream, sl, sl_dev, nov);
+    hipLaunchKernelGGL(k_walk_level, dim3(1), dim3(64), 0, c.stream, sl, sl_dev, nov, clock_word(c));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (debug) {
       AMFMM_HIP(hipEventCreate(&e0));
@@ -1334,13 +1341,13 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     hipLaunchKernelGGL(gq ? (debug ? stage_kernel(yes, yes) : stage_kernel(yes, no))
                           : (debug ? stage_kernel(no, yes) : stage_kernel(no, no)),
                        dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, nl, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
-                       (const int32_t*)gcnt, fy, (const StageLayout*)sl_dev, kc, nov, gq, qcap, dbg);
+                       (const int32_t*)gcnt, fy, (const StageLayout*)sl_dev, kc, nov, gq, qcap, dbg, clock_word(c));
     ++c.pass_launches;
     mark(c, kPhWalk);
     AMFMM_HIP(hipGetLastError());
     if (debug) AMFMM_HIP(hipEventRecord(e1, c.stream));
     scan_i64(c, ScanSet<int64_t>{{kc.km, kc.kp, kc.kq, kc.kr, kc.kd, kc.ks}, {e, e + K, e + 2 * K, e + 3 * K, e + 4 * K, e + 5 * K}},
-             6, kn);
+             6, kn, clock_word(c));
     hipLaunchKernelGGL(k_walk_cells, dim3(blocks_for(nl, kBS)), dim3(kBS), 0, c.stream, t, c0, nl, c0n, cbase, ex, kn,
                        far_base, near_base, (int64_t*)c.far_start.p, (int32_t*)c.far_count.p,
                        (int64_t*)c.near_start.p, (int32_t*)c.near_count.p, (int64_t*)c.near_parts.p, gbeg_n, gcnt_n,
