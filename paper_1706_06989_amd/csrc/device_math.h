@@ -80,6 +80,45 @@ __device__ inline void far_coeffs(const T R[3], T M, const T Q2[6], T* acc, T ep
   for (int u = 0; u < 10; ++u) acc[10 + u] = fma(M, D3[u], acc[10 + u]);
 }
 
+// far_coeffs at the plain -1/R in FP64 for a traceless quadrupole: the terms of
+// its trace vanish (D_ll = 0), so they need not be formed
+__device__ inline void far_coeffs_traceless(const double R[3], double M, const double Q2[6], double* acc) {
+  const double r2 = fma(R[0], R[0], fma(R[1], R[1], R[2] * R[2]));
+  const double ri = rsqrt_f64(r2);
+  const double ri2 = ri * ri;
+  const double t1 = ri * ri2;
+  const double t2 = -3.0 * t1 * ri2;
+  const double t3 = -5.0 * t2 * ri2;
+  const double QR[3] = {fma(Q2[0], R[0], fma(Q2[1], R[1], Q2[2] * R[2])),
+                        fma(Q2[1], R[0], fma(Q2[3], R[1], Q2[4] * R[2])),
+                        fma(Q2[2], R[0], fma(Q2[4], R[1], Q2[5] * R[2]))};
+  const double hRQR = 0.5 * fma(R[0], QR[0], fma(R[1], QR[1], R[2] * QR[2]));
+  const double m1 = M * t1, m2 = M * t2, m3 = M * t3;
+  acc[0] += fma(-M, ri, t2 * hRQR);
+  const double a1 = fma(t3, hRQR, m1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) acc[1 + k] += fma(a1, R[k], t2 * QR[k]);
+  // M D_kl = m1 delta + m2 R_k R_l, M D_klm = m3 R_k R_l R_m + m2 (delta R)
+  const double x = m2 * R[0], y = m2 * R[1], z = m2 * R[2];
+  acc[4] += fma(x, R[0], m1);
+  acc[5] = fma(x, R[1], acc[5]);
+  acc[6] = fma(x, R[2], acc[6]);
+  acc[7] += fma(y, R[1], m1);
+  acc[8] = fma(y, R[2], acc[8]);
+  acc[9] += fma(z, R[2], m1);
+  const double xx = m3 * R[0] * R[0], yy = m3 * R[1] * R[1], zz = m3 * R[2] * R[2];
+  acc[10] += fma(xx, R[0], 3.0 * x);
+  acc[11] += fma(xx, R[1], y);
+  acc[12] += fma(xx, R[2], z);
+  acc[13] += fma(yy, R[0], x);
+  acc[14] = fma(m3 * R[0] * R[1], R[2], acc[14]);
+  acc[15] += fma(zz, R[0], x);
+  acc[16] += fma(yy, R[1], 3.0 * y);
+  acc[17] += fma(yy, R[2], z);
+  acc[18] += fma(zz, R[1], y);
+  acc[19] += fma(zz, R[2], 3.0 * z);
+}
+
 // Q_jkl D_ijkl (TC) or Q_jkl D'_ijkl (TCO) of the correction, FP64, with
 // Q = M_X,jkl M_Y - M_X M_Y,jkl; adds to F[3].  In the radial-factor form of
 // far_coeffs (softened for eps2 > 0).
@@ -195,6 +234,12 @@ __device__ inline uint32_t xcd_block(uint32_t b, uint32_t nb) {
 template <typename T>
 __device__ inline T uniform(T v) {
   return (T)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+__device__ inline double uniform_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
 // Taylor polynomial of a cell's coefficients (kLoc layout) at offset x:

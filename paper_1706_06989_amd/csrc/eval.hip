@@ -15,15 +15,15 @@
 // R_l + R_i Q_jkk R_j) + 3 t2 Q_ikk with t2 = -3/R^5, t3 = 15/R^7, t4 =
 // -105/R^9.  Eq. 8 keeps only 3 t3 Q_ikl R_k R_l + 3 t2 Q_ikk.
 //
-// One wave per target cell, lanes over its sources, fixed-order butterfly
-// reduction (deterministic).  Mixed precision: R = Z_X - Z_Y is formed in FP64
+// One wave per target cell, lanes over its sources, fixed-order reduction
+// (deterministic).  Mixed precision: R = Z_X - Z_Y is formed in FP64
 // and rounded, the coefficient terms are FP32 and each lane adds at most
 // kFarFlush of them in FP32 before an FP64 flush; the correction (which
-// cancels M_X,jkl M_Y against M_X M_Y,jkl) stays FP64.  For UC and TC the
-// mixed path reads each source from one 128-byte record (one cache line
-// instead of three): Z and M in FP64, the traceless octupole (7 components,
-// FP64; D_ijkl is traceless, so the correction needs no more) and the
-// quadrupole in FP32.
+// cancels M_X,jkl M_Y against M_X M_Y,jkl) stays FP64.  UC and TC of the plain
+// -1/R read each source from one 128-byte record (k_far_rec), the rest from the
+// cells' arrays (k_far).
+#include <type_traits>
+
 #include "device_math.h"
 #include "internal.h"
 
@@ -33,49 +33,65 @@ namespace {
 constexpr int kBS = 256;
 constexpr int kWaves = kBS / 64;
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // sources per lane summed in FP32 before an FP64 flush (mixed path)
 constexpr int kFarFlush = 8;
 
-// far-field source record of the mixed UC/TC path: 128 bytes, one cache line
+// Far-field source records of UC and TC at the plain -1/R: 128 bytes, one cache
+// line.  The derivatives are traceless in every index pair, so the traceless
+// octupole (7 components: xxx xxy xxz xyy xyz yyy yyz; xzz, yzz, zzz follow) is
+// all the correction needs.  At FP64 the quadrupole is traceless too (5
+// components: xx xy xz yy yz); mixed precision keeps all six, rounded to FP32
+// as they are used.
 struct alignas(128) FarRec {
   double z[3], m;
-  double o[7];  // traceless octupole: xxx xxy xxz xyy xyz yyy yyz (xzz, yzz, zzz follow)
-  float q[6];   // quadrupole xx xy xz yy yz zz
+  double o[7];
+  float q[6];
   float pad[4];
 };
-static_assert(sizeof(FarRec) == 128, "far record");
+struct alignas(128) FarRec64 {
+  double z[3], m;
+  double o[7];
+  double q[5];
+};
+static_assert(sizeof(FarRec) == 128 && sizeof(FarRec64) == 128, "far record");
 
+template <bool MIXED>
 __global__ void __launch_bounds__(kBS) k_pack_far(int32_t nc, const double4* __restrict__ geo,
-                                                  const double* __restrict__ mom, FarRec* __restrict__ rec) {
+                                                  const double* __restrict__ mom, void* __restrict__ out) {
   const int32_t c = blockIdx.x * kBS + threadIdx.x;
   if (c >= nc) return;
   const double4 g = geo[c];
   const double* mo = mom + (int64_t)c * kMom;
   double T[10];
   octupole_traceless(mo + 7, T);
-  FarRec r;
-  r.z[0] = g.x;
-  r.z[1] = g.y;
-  r.z[2] = g.z;
-  r.m = mo[0];
-  r.o[0] = T[0];
-  r.o[1] = T[1];
-  r.o[2] = T[2];
-  r.o[3] = T[3];
-  r.o[4] = T[4];
-  r.o[5] = T[6];
-  r.o[6] = T[7];
+  const double o[7] = {T[0], T[1], T[2], T[3], T[4], T[6], T[7]};
+  auto common = [&](auto& r) {
+    r.z[0] = g.x;
+    r.z[1] = g.y;
+    r.z[2] = g.z;
+    r.m = mo[0];
 #pragma unroll
-  for (int u = 0; u < 6; ++u) r.q[u] = (float)mo[1 + u];
+    for (int u = 0; u < 7; ++u) r.o[u] = o[u];
+  };
+  if (MIXED) {
+    FarRec r;
+    common(r);
 #pragma unroll
-  for (int u = 0; u < 4; ++u) r.pad[u] = 0.0f;
-  rec[c] = r;
+    for (int u = 0; u < 6; ++u) r.q[u] = (float)mo[1 + u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) r.pad[u] = 0.0f;
+    ((FarRec*)out)[c] = r;
+  } else {
+    FarRec64 r;
+    common(r);
+    const double tr = (mo[1] + mo[4] + mo[6]) / 3.0;
+    r.q[0] = mo[1] - tr;
+    r.q[1] = mo[2];
+    r.q[2] = mo[3];
+    r.q[3] = mo[4] - tr;
+    r.q[4] = mo[5];
+    ((FarRec64*)out)[c] = r;
+  }
 }
 
 // the full traceless octupole of a record
@@ -92,64 +108,147 @@ __device__ inline void record_octupole(const double o[7], double T[10]) {
   T[9] = -o[2] - o[6];
 }
 
-// Mixed UC/TC far field from the records (see k_far)
-template <int VARIANT>
-__global__ void __launch_bounds__(kBS) k_far_rec(int32_t c_lo, int32_t nc, const FarRec* __restrict__ rec,
-                                                 const int64_t* __restrict__ fstart,
-                                                 const int32_t* __restrict__ fcount,
-                                                 const int32_t* __restrict__ fsrc, double* __restrict__ loc,
-                                                 unsigned long long* clock) {
+// Sums of 24 values over the wave: each exchange sends the half of the values
+// that the other lane goes on with, 24 -> 12 -> 6 -> 3, so 21 exchanges and nine
+// plain ones take the place of 144.  Lane l ends with the totals of values
+// first, first + 1, first + 2, first = 12 bit5 + 6 bit4 + 3 bit3 of l.  The
+// additions of one value pair lanes as a butterfly over 32, 16, ..., 1 does.
+__device__ inline void wave_sum24(double v[24], int lane, double out[3]) {
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int off = 32 >> s, half = 12 >> s;
+    const bool hi = lane & off;
+#pragma unroll
+    for (int k = 0; k < half; ++k) {
+      const double send = hi ? v[k] : v[k + half], keep = hi ? v[k + half] : v[k];
+      v[k] = keep + __shfl_xor(send, off, 64);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    out[k] = v[k];
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) out[k] += __shfl_xor(out[k], off, 64);
+  }
+}
+
+// a target's coefficients and corrections (F: times cf) from every lane's sums
+__device__ inline void store_local(double* __restrict__ o, const double acc[20], const double F[3], double cf, int lane) {
+  double v[24], t[3];
+#pragma unroll
+  for (int u = 0; u < 20; ++u) v[u] = acc[u];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) v[20 + i] = F[i];
+  v[23] = 0.0;
+  wave_sum24(v, lane, t);
+  const int first = 12 * ((lane >> 5) & 1) + 6 * ((lane >> 4) & 1) + 3 * ((lane >> 3) & 1), k = lane & 7;
+  if (k < 3) {
+    const double s = k == 0 ? t[0] : (k == 1 ? t[1] : t[2]);
+    o[first + k] = first + k >= 20 ? cf * s : s;
+  }
+}
+
+// Far field of UC and TC from the records (see k_far).  What bounds it is the
+// vector cache, which answers one 64-byte request a cycle: a lane loading its
+// own record takes eight requests (0.93 a cycle measured; at FP64, from two
+// arrays, eleven).  Eight neighbouring lanes fetch one record instead, straight
+// to the wave's 8 KB of LDS (16 bytes a lane, two requests a record), and each
+// lane reads its own there, slot q of record r holding piece q ^ (r mod 8)
+// (conflict-free); the next 64 records travel while this lane computes.
+// 4M two spheres at theta 0.35, FP64: 13.3 -> 5.7 ms; 16.8M at the benchmark's
+// tolerance, mixed: 256 -> 155 ms.
+// (mixed TC at four waves a SIMD spills 18 registers: 167 ms)
+template <int VARIANT, bool MIXED>
+__global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(MIXED && VARIANT ? 3 : 4)))
+k_far_rec(int32_t c_lo, int32_t nc, const void* __restrict__ recs, const int64_t* __restrict__ fstart,
+          const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, double* __restrict__ loc,
+          unsigned long long* clock) {
   take_time(clock);
+  using Rec = typename std::conditional<MIXED, FarRec, FarRec64>::type;
+  const Rec* __restrict__ rec = (const Rec*)recs;
+  __shared__ double2 lds[kWaves][64 * 8];
   const int lane = threadIdx.x & 63;
   const int32_t Xi = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6)));
   if (Xi >= nc) return;
   const int32_t X = c_lo + Xi;
-  const int32_t cnt = fcount[X];
-  const int64_t st = fstart[X];
-  const FarRec& rx = rec[X];
-  const double gx[3] = {rx.z[0], rx.z[1], rx.z[2]};
-  const double MX = rx.m;
+  const int32_t cnt = uniform(fcount[X]);
+  const int32_t* __restrict__ src = fsrc + fstart[X];
+  double2* buf = lds[threadIdx.x >> 6];
+  const Rec& rx = rec[X];
+  // the target's side in scalar registers
+  const double gx[3] = {uniform_f64(rx.z[0]), uniform_f64(rx.z[1]), uniform_f64(rx.z[2])};
+  const double MX = uniform_f64(rx.m);
   double OX[10];
-  if (VARIANT) record_octupole(rx.o, OX);
+  if (VARIANT) {
+    record_octupole(rx.o, OX);
+#pragma unroll
+    for (int u = 0; u < 10; ++u) OX[u] = uniform_f64(OX[u]);
+  }
   double acc[20], F[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int u = 0; u < 20; ++u) acc[u] = 0.0;
-  for (int64_t j0 = lane; j0 < cnt; j0 += 64 * kFarFlush) {
-    float a32[20];
+  // lanes past the end fetch the target's own record and do not use it
+  auto fetch = [&](int32_t y) {
 #pragma unroll
-    for (int u = 0; u < 20; ++u) a32[u] = 0.0f;
-    const int64_t j1 = j0 + 64 * kFarFlush < cnt ? j0 + 64 * kFarFlush : cnt;
-    for (int64_t j = j0; j < j1; j += 64) {
-      const FarRec& ry = rec[fsrc[st + j]];
-      const double R[3] = {gx[0] - ry.z[0], gx[1] - ry.z[1], gx[2] - ry.z[2]};
-      const double M = ry.m;
-      const float Rf[3] = {(float)R[0], (float)R[1], (float)R[2]};
-      float Q2f[6];
+    for (int i = 0; i < 8; ++i) {
+      const int r = 8 * i + (lane >> 3);
+      const double2* from = (const double2*)(rec + __shfl(y, r, 64)) + ((lane & 7) ^ (r & 7));
+      __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)from,
+                                       (__attribute__((address_space(3))) void*)(buf + 64 * i), 16, 0, 0);
+    }
+  };
+  int32_t ahead = lane + 64 < cnt ? src[lane + 64] : X;
+  if (cnt > 0) fetch(lane < cnt ? src[lane] : X);
+  float a32[20];
 #pragma unroll
-      for (int u = 0; u < 6; ++u) Q2f[u] = ry.q[u];
-      far_coeffs<float>(Rf, (float)M, Q2f, a32, 0.0f);
+  for (int u = 0; u < 20; ++u) a32[u] = 0.0f;
+  int batch = 0;
+  for (int32_t j0 = 0; j0 < cnt; j0 += 64) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    double2 p[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) p[q] = buf[8 * lane + (q ^ (lane & 7))];
+    // every lane's record is in registers before the next ones arrive
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (j0 + 64 < cnt) {
+      fetch(ahead);
+      const int32_t j2 = j0 + 128 + lane;
+      ahead = j2 < cnt ? src[j2] : X;
+    }
+    if (j0 + lane < cnt) {
+      const double R[3] = {gx[0] - p[0].x, gx[1] - p[0].y, gx[2] - p[1].x};
+      const double M = p[1].y;
+      const double o7[7] = {p[2].x, p[2].y, p[3].x, p[3].y, p[4].x, p[4].y, p[5].x};
+      if (MIXED) {
+        const float2 q01 = __builtin_bit_cast(float2, p[5].y), q23 = __builtin_bit_cast(float2, p[6].x),
+                     q45 = __builtin_bit_cast(float2, p[6].y);
+        const float Rf[3] = {(float)R[0], (float)R[1], (float)R[2]};
+        const float Q2f[6] = {q01.x, q01.y, q23.x, q23.y, q45.x, q45.y};
+        far_coeffs<float>(Rf, (float)M, Q2f, a32, 0.0f);
+      } else {
+        const double Q2[6] = {p[5].y, p[6].x, p[6].y, p[7].x, p[7].y, -p[5].y - p[7].x};
+        far_coeffs_traceless(R, M, Q2, acc);
+      }
       if (VARIANT) {
         double O3[10];
-        record_octupole(ry.o, O3);
+        record_octupole(o7, O3);
         far_correction_traceless(R, MX, OX, M, O3, F);
       }
     }
+    if (MIXED && ++batch == kFarFlush) {
+      batch = 0;
+#pragma unroll
+      for (int u = 0; u < 20; ++u) {
+        acc[u] += (double)a32[u];
+        a32[u] = 0.0f;
+      }
+    }
+  }
+  if (MIXED) {
 #pragma unroll
     for (int u = 0; u < 20; ++u) acc[u] += (double)a32[u];
   }
-#pragma unroll
-  for (int u = 0; u < 20; ++u) acc[u] = wave_sum(acc[u]);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) F[i] = wave_sum(F[i]);
-  if (lane == 0) {
-    double* o = loc + (int64_t)X * kLoc;
-    const double cf = -1.0 / (6.0 * MX);
-#pragma unroll
-    for (int u = 0; u < 20; ++u) o[u] = acc[u];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) o[20 + i] = VARIANT ? cf * F[i] : 0.0;
-    o[23] = 0.0;
-  }
+  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -1.0 / (6.0 * MX) : 0.0, lane);
 }
 
 template <int VARIANT, bool MIXED>
@@ -209,19 +308,7 @@ __global__ void __launch_bounds__(kBS) k_far(int32_t c_lo, int32_t nc, const dou
       for (int u = 0; u < 20; ++u) acc[u] += (double)a32[u];
     }
   }
-#pragma unroll
-  for (int u = 0; u < 20; ++u) acc[u] = wave_sum(acc[u]);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) F[i] = wave_sum(F[i]);
-  if (lane == 0) {
-    double* o = loc + (int64_t)X * kLoc;
-    const double cf = -1.0 / (6.0 * MX);
-#pragma unroll
-    for (int u = 0; u < 20; ++u) o[u] = acc[u];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) o[20 + i] = VARIANT ? cf * F[i] : 0.0;
-    o[23] = 0.0;
-  }
+  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -1.0 / (6.0 * MX) : 0.0, lane);
 }
 
 // loc[c] += Taylor shift of its parent's coefficients to its centre
@@ -308,16 +395,17 @@ void zero_u64(Ctx& c, unsigned long long* p, int n, unsigned long long* clock) {
   AMFMM_HIP(hipGetLastError());
 }
 
-// the 128-byte records carry traceless octupoles, enough for the correction
-// of the plain -1/R only (mixed UC and TC)
+// the 128-byte records carry traceless moments, enough for UC and TC of the
+// plain -1/R (the derivatives of a softened one, and eq. 8's tensor, are not
+// traceless)
 static bool use_records(const Ctx& c) {
-  return c.opt.precision == AMFMM_MIXED && c.opt.variant != AMFMM_TCO && c.opt.softening == 0.0 && c.opt.order == 3;
+  return c.opt.variant != AMFMM_TCO && c.opt.softening == 0.0 && c.opt.order == 3;
 }
 
 void far_prepare(Ctx& c) {
   if (!use_records(c) || c.ncells <= 0) return;
-  FarRec* rec = (FarRec*)ensure(c, c.farrec, sizeof(FarRec) * (size_t)c.ncells);
-  hipLaunchKernelGGL(k_pack_far, dim3(blocks_for(c.ncells, kBS)), dim3(kBS), 0, c.stream, c.ncells,
+  void* rec = ensure(c, c.farrec, sizeof(FarRec) * (size_t)c.ncells);
+  hipLaunchKernelGGL(c.opt.precision == AMFMM_MIXED ? k_pack_far<true> : k_pack_far<false>, dim3(blocks_for(c.ncells, kBS)), dim3(kBS), 0, c.stream, c.ncells,
                      (const double4*)c.geo.p, (const double*)c.mom.p, rec);
   AMFMM_HIP(hipGetLastError());
 }
@@ -335,9 +423,12 @@ void far_field(Ctx& c, int32_t c_lo, int32_t c_hi) {
   dim3 grid(blocks_for(nc, kWaves));
   if (use_records(c)) {
     ++c.far_launches;
-    hipLaunchKernelGGL(c.opt.variant == AMFMM_TC ? k_far_rec<AMFMM_TC> : k_far_rec<AMFMM_UC>, grid, dim3(kBS), 0,
-                       c.stream, c_lo, nc, (const FarRec*)c.farrec.p, (const int64_t*)c.far_start.p,
-                       (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc, clock_word(c));
+    const bool tc = c.opt.variant == AMFMM_TC;
+    auto kern = c.opt.precision == AMFMM_MIXED ? (tc ? k_far_rec<AMFMM_TC, true> : k_far_rec<AMFMM_UC, true>)
+                                               : (tc ? k_far_rec<AMFMM_TC, false> : k_far_rec<AMFMM_UC, false>);
+    hipLaunchKernelGGL(kern, grid, dim3(kBS), 0, c.stream, c_lo, nc, (const void*)c.farrec.p,
+                       (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc,
+                       clock_word(c));
     AMFMM_HIP(hipGetLastError());
     return;
   }

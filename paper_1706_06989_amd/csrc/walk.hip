@@ -94,12 +94,6 @@ __device__ inline WalkCell load_cell(const WalkRec* __restrict__ r, int32_t c) {
   return unpack_cell(p[0], p[1], p[2], reinterpret_cast<const int4*>(p)[3], c);
 }
 
-__device__ inline double uniform_f64(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 // a record every lane of the wave needs, in scalar registers
 __device__ inline WalkCell load_cell_uniform(const WalkRec* __restrict__ r, int32_t c) {
   WalkCell w = load_cell(r, c);
