@@ -20,6 +20,7 @@ namespace amfmm {
 namespace {
 
 constexpr int kBS = 256;
+constexpr int kUB = 64;           // threads per workgroup over the parameters
 constexpr int kLabelSample = 64;  // sampled particles per cell for a label
 constexpr int kRows = 64;         // training rows per workgroup
 constexpr int kLd = kHid + 1;     // LDS row stride (floats) of the 64-wide tiles
@@ -178,6 +179,7 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   __shared__ float H1[kRows][kLd];  // hidden 1, later dL/dz1
   __shared__ float H2[kRows][kLd];  // hidden 2, later dL/dz2
   __shared__ float W2[kHid][kLd];   // BF16-rounded, W2[k][j]
+  __shared__ float w3[kHid];        // BF16-rounded
   __shared__ float dys[kRows], ls[kRows];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int lr = lane & 15, lq = lane >> 4;
@@ -190,21 +192,34 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
     Xs[r][i] = bf16r(fmaf(f, P[kNA + i], P[kNB + i]));
   }
   for (int idx = t; idx < kHid * kHid; idx += kBS) W2[idx / kHid][idx % kHid] = bf16r(P[kW2 + idx]);
-  __syncthreads();
-  // layer 1 (vector units)
-  for (int idx = t; idx < kRows * kHid; idx += kBS) {
-    const int r = idx / kHid, j = idx % kHid;
-    float s = P[kB1 + j];
+  if (t < kHid) w3[t] = bf16r(P[kW3 + t]);
+  // layer 1 (vector units): a thread keeps its hidden unit's weights
+  {
+    const int j = t % kHid;
+    float w1[kFeat];
 #pragma unroll
-    for (int i = 0; i < kFeat; ++i) s = fmaf(bf16r(P[kW1 + kFeat * j + i]), Xs[r][i], s);
-    H1[r][j] = bf16r(s > 0.0f ? s : 0.0f);
+    for (int i = 0; i < kFeat; ++i) w1[i] = bf16r(P[kW1 + kFeat * j + i]);
+    const float b1 = P[kB1 + j];
+    __syncthreads();
+#pragma unroll 4
+    for (int r = t / kHid; r < kRows; r += kBS / kHid) {
+      float s = b1;
+#pragma unroll
+      for (int i = 0; i < kFeat; ++i) s = fmaf(w1[i], Xs[r][i], s);
+      H1[r][j] = bf16r(s > 0.0f ? s : 0.0f);
+    }
   }
   __syncthreads();
   // layer 2: Z2 = H1 W2^T, BF16 products, FP32 accumulation; wave w takes rows
   // 16w..16w+15.  Operand layout of the 16x16x16 product: lane l supplies
   // A[l%16][4(l/16)+v] and B[4(l/16)+v][l%16]; it receives D[4(l/16)+v][l%16].
+  float b2[4];
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) b2[ct] = P[kB2 + 16 * ct + lr];
+#pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       bf16x4 a, b;
 #pragma unroll
@@ -217,18 +232,21 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int r = 16 * w + 4 * lq + v, k = 16 * ct + lr;
-      const float z = acc[v] + P[kB2 + k];
+      const float z = acc[v] + b2[ct];
       H2[r][k] = bf16r(z > 0.0f ? z : 0.0f);
     }
   }
   __syncthreads();
   // output, loss and its derivative
   if (t < kRows) {
+    const bool in = r0 + t < B;
+    const float label = in ? labels[(off + r0 + t) % n] : 0.0f;
     float y = P[kB3];
-    for (int k = 0; k < kHid; ++k) y = fmaf(bf16r(P[kW3 + k]), H2[t][k], y);
+#pragma unroll 16
+    for (int k = 0; k < kHid; ++k) y = fmaf(w3[k], H2[t][k], y);
     float dy = 0.0f, l = 0.0f;
-    if (r0 + t < B) {
-      const float res = labels[(off + r0 + t) % n] - y;
+    if (in) {
+      const float res = label - y;
       l = res < 0.0f ? (tau - 1.0f) * res : tau * res;
       dy = (res < 0.0f ? 1.0f - tau : -tau) * invB;
     }
@@ -239,14 +257,17 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   // gradients of the output layer (read H2 before it is overwritten)
   if (t >= 128 && t < 192) {
     float s = 0.0f;
+#pragma unroll 16
     for (int r = 0; r < kRows; ++r) s = fmaf(dys[r], H2[r][t - 128], s);
     g[kW3 + t - 128] = s;
   } else if (t == 192) {
     float s = 0.0f;
+#pragma unroll
     for (int r = 0; r < kRows; ++r) s += dys[r];
     g[kB3] = s;
   } else if (t == 193) {
     float s = 0.0f;
+#pragma unroll
     for (int r = 0; r < kRows; ++r) s += ls[r];
     lpart[blockIdx.x] = s;
   }
@@ -254,7 +275,7 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   // dL/dz2 in place of H2 (each element from its own value)
   for (int idx = t; idx < kRows * kHid; idx += kBS) {
     const int r = idx / kHid, k = idx % kHid;
-    H2[r][k] = H2[r][k] > 0.0f ? dys[r] * bf16r(P[kW3 + k]) : 0.0f;
+    H2[r][k] = H2[r][k] > 0.0f ? dys[r] * w3[k] : 0.0f;
   }
   __syncthreads();
   // dW2[k][j] = sum_r dz2[r][k] H1[r][j] (FP32 products); wave w takes k =
@@ -262,6 +283,7 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   // A[l%16][l/16] and B[l/16][l%16]; it receives D[4(l/16)+v][l%16].
   for (int ct = 0; ct < 4; ++ct) {
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
     for (int ks = 0; ks < kRows / 4; ++ks)
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(H2[4 * ks + lq][16 * w + lr], H1[4 * ks + lq][16 * ct + lr], acc,
                                                  0, 0, 0);
@@ -270,6 +292,7 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   }
   if (t >= 64 && t < 128) {
     float s = 0.0f;
+#pragma unroll 16
     for (int r = 0; r < kRows; ++r) s += H2[r][t - 64];
     g[kB2 + t - 64] = s;
   }
@@ -277,6 +300,7 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   // dz1 = (dz2 W2) masked by the ReLU, in place of H1 (element by element)
   for (int ct = 0; ct < 4; ++ct) {
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
     for (int ks = 0; ks < kHid / 4; ++ks)
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(H2[16 * w + lr][4 * ks + lq], W2[4 * ks + lq][16 * ct + lr], acc,
                                                  0, 0, 0);
@@ -291,6 +315,7 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   {
     const int j = t >> 2, i0 = 2 * (t & 3);
     float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll 16
     for (int r = 0; r < kRows; ++r) {
       s0 = fmaf(H1[r][j], Xs[r][i0], s0);
       s1 = fmaf(H1[r][j], Xs[r][i0 + 1], s1);
@@ -300,35 +325,55 @@ __global__ void __launch_bounds__(kBS) k_mlp_step(int64_t n, int64_t off, int64_
   }
   if (t < 64) {
     float s = 0.0f;
+#pragma unroll 16
     for (int r = 0; r < kRows; ++r) s += H1[r][t];
     g[kB1 + t] = s;
   }
 }
 
-// grad[p] = sum over workgroups of the partials, in workgroup order; the
-// loss (times invB) in grad[AMFMM_MLP_PARAMS]
-__global__ void __launch_bounds__(kBS) k_mlp_reduce(int32_t nblk, const float* __restrict__ part,
-                                                    const float* __restrict__ lpart, float invB,
-                                                    float* __restrict__ grad) {
-  const int p = blockIdx.x * kBS + threadIdx.x;
-  if (p > AMFMM_MLP_PARAMS) return;
+// sum over workgroups of parameter p's partials (p = AMFMM_MLP_PARAMS: of the
+// losses, times invB), in workgroup order; the loads run ahead of the adds
+__device__ inline float sum_partials(int p, int32_t nblk, const float* __restrict__ part,
+                                     const float* __restrict__ lpart, float invB) {
+  const bool loss = p == AMFMM_MLP_PARAMS;
+  const float* __restrict__ v = loss ? lpart : part + p;
+  const int64_t stride = loss ? 1 : AMFMM_MLP_PARAMS;
   float s = 0.0f;
-  if (p < AMFMM_MLP_PARAMS) {
-    for (int b = 0; b < nblk; ++b) s += part[(int64_t)b * AMFMM_MLP_PARAMS + p];
-  } else {
-    for (int b = 0; b < nblk; ++b) s += lpart[b];
-    s *= invB;
+  int32_t b = 0;
+  for (; b + 16 <= nblk; b += 16) {
+    float w[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) w[u] = v[(b + u) * stride];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += w[u];
   }
-  grad[p] = s;
+  for (; b < nblk; ++b) s += v[b * stride];
+  return loss ? s * invB : s;
 }
 
-// Adam (Kingma & Ba 2015) with bias corrections c1 = 1 - beta1^t, c2 = 1 - beta2^t
-__global__ void __launch_bounds__(kBS) k_mlp_adam(float* __restrict__ P, const float* __restrict__ grad,
-                                                  float* __restrict__ m, float* __restrict__ v, double lr, double b1,
-                                                  double b2, double eps, double c1, double c2) {
-  const int p = blockIdx.x * kBS + threadIdx.x;
-  if (p >= AMFMM_MLP_PARAMS) return;
-  const double g = grad[p];
+__global__ void __launch_bounds__(kUB) k_mlp_reduce(int32_t nblk, const float* __restrict__ part,
+                                                    const float* __restrict__ lpart, float invB,
+                                                    float* __restrict__ grad) {
+  const int p = blockIdx.x * kUB + threadIdx.x;
+  if (p <= AMFMM_MLP_PARAMS) grad[p] = sum_partials(p, nblk, part, lpart, invB);
+}
+
+// The reduction with the Adam update (Kingma & Ba 2015) of its parameter, bias
+// corrections c1 = 1 - beta1^t, c2 = 1 - beta2^t; the loss to *loss.  (As two
+// kernels, and with weights re-read for every row, a step of 4096 rows took 39
+// us; now 21.)
+__global__ void __launch_bounds__(kUB) k_mlp_update(int32_t nblk, const float* __restrict__ part,
+                                                    const float* __restrict__ lpart, float invB, float* __restrict__ loss,
+                                                    float* __restrict__ P, float* __restrict__ m, float* __restrict__ v,
+                                                    double lr, double b1, double b2, double eps, double c1, double c2) {
+  const int p = blockIdx.x * kUB + threadIdx.x;
+  if (p > AMFMM_MLP_PARAMS) return;
+  const float s = sum_partials(p, nblk, part, lpart, invB);
+  if (p == AMFMM_MLP_PARAMS) {
+    *loss = s;
+    return;
+  }
+  const double g = s;
   const double mi = b1 * m[p] + (1.0 - b1) * g;
   const double vi = b2 * v[p] + (1.0 - b2) * g * g;
   m[p] = (float)mi;
@@ -340,21 +385,17 @@ void check_pairs(Ctx& c) {
   if (!c.have_moments) throw Error(AMFMM_E_STATE, "pair features and labels need amfmm_compute_moments");
 }
 
-// one gradient evaluation over batch rows off .. off+B-1 (mod n); the result
-// (AMFMM_MLP_PARAMS gradients, then the loss) in c.mlp_grad
-float* mlp_step(Ctx& c, int64_t n, int64_t off, int64_t B, const float* feats, const float* labels, const float* P,
-                double tau) {
+// forward and backward over batch rows off .. off+B-1 (mod n): partial
+// gradients and losses of each workgroup in c.mlp_part
+int32_t mlp_step(Ctx& c, int64_t n, int64_t off, int64_t B, const float* feats, const float* labels, const float* P,
+                 double tau, float** part, float** lpart) {
   const int32_t nblk = (int32_t)((B + kRows - 1) / kRows);
-  float* part = (float*)ensure(c, c.mlp_part, sizeof(float) * ((size_t)nblk * AMFMM_MLP_PARAMS + nblk));
-  float* lpart = part + (size_t)nblk * AMFMM_MLP_PARAMS;
-  float* grad = (float*)ensure(c, c.mlp_grad, sizeof(float) * (AMFMM_MLP_PARAMS + 1));
-  const float invB = (float)(1.0 / (double)B);
-  hipLaunchKernelGGL(k_mlp_step, dim3(nblk), dim3(kBS), 0, c.stream, n, off, B, feats, labels, P, (float)tau, invB,
-                     part, lpart);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(blocks_for(AMFMM_MLP_PARAMS + 1, kBS)), dim3(kBS), 0, c.stream, nblk,
-                     (const float*)part, (const float*)lpart, invB, grad);
+  *part = (float*)ensure(c, c.mlp_part, sizeof(float) * ((size_t)nblk * AMFMM_MLP_PARAMS + nblk));
+  *lpart = *part + (size_t)nblk * AMFMM_MLP_PARAMS;
+  hipLaunchKernelGGL(k_mlp_step, dim3(nblk), dim3(kBS), 0, c.stream, n, off, B, feats, labels, P, (float)tau,
+                     (float)(1.0 / (double)B), *part, *lpart);
   AMFMM_HIP(hipGetLastError());
-  return grad;
+  return nblk;
 }
 
 }  // namespace
@@ -398,7 +439,12 @@ void mlp_predict(Ctx& c, int64_t n, const float* model, const float* feats, floa
 
 double mlp_grad(Ctx& c, int64_t n, const float* model, const float* feats, const float* labels, double tau,
                 float* grad) {
-  const float* g = mlp_step(c, n, 0, n, feats, labels, model, tau);
+  float *part, *lpart;
+  const int32_t nblk = mlp_step(c, n, 0, n, feats, labels, model, tau, &part, &lpart);
+  float* g = (float*)ensure(c, c.mlp_grad, sizeof(float) * (AMFMM_MLP_PARAMS + 1));
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(blocks_for(AMFMM_MLP_PARAMS + 1, kUB)), dim3(kUB), 0, c.stream, nblk,
+                     (const float*)part, (const float*)lpart, (float)(1.0 / (double)n), g);
+  AMFMM_HIP(hipGetLastError());
   AMFMM_HIP(hipMemcpyAsync(grad, g, sizeof(float) * AMFMM_MLP_PARAMS, hipMemcpyDeviceToDevice, c.stream));
   float loss = 0.0f;
   AMFMM_HIP(hipMemcpyAsync(&loss, g + AMFMM_MLP_PARAMS, sizeof(float), hipMemcpyDeviceToHost, c.stream));
@@ -409,17 +455,19 @@ double mlp_grad(Ctx& c, int64_t n, const float* model, const float* feats, const
 double mlp_train(Ctx& c, int64_t n, const float* feats, const float* labels, float* model, float* am, float* av,
                  int64_t step0, int32_t steps, int32_t batch, double lr, double tau) {
   const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
-  const float* g = nullptr;
+  float* g = (float*)ensure(c, c.mlp_grad, sizeof(float) * (AMFMM_MLP_PARAMS + 1));
   for (int32_t s = 0; s < steps; ++s) {
     const int64_t st = step0 + s;
-    g = mlp_step(c, n, (st * (int64_t)batch) % n, batch, feats, labels, model, tau);
+    float *part, *lpart;
+    const int32_t nblk = mlp_step(c, n, (st * (int64_t)batch) % n, batch, feats, labels, model, tau, &part, &lpart);
     const double c1 = 1.0 - std::pow(b1, (double)(st + 1)), c2 = 1.0 - std::pow(b2, (double)(st + 1));
-    hipLaunchKernelGGL(k_mlp_adam, dim3(blocks_for(AMFMM_MLP_PARAMS, kBS)), dim3(kBS), 0, c.stream, model, g, am, av,
-                       lr, b1, b2, eps, c1, c2);
+    hipLaunchKernelGGL(k_mlp_update, dim3(blocks_for(AMFMM_MLP_PARAMS + 1, kUB)), dim3(kUB), 0, c.stream, nblk,
+                       (const float*)part, (const float*)lpart, (float)(1.0 / (double)batch), g + AMFMM_MLP_PARAMS,
+                       model, am, av, lr, b1, b2, eps, c1, c2);
     AMFMM_HIP(hipGetLastError());
   }
   float loss = 0.0f;
-  if (g) {
+  if (steps > 0) {
     AMFMM_HIP(hipMemcpyAsync(&loss, g + AMFMM_MLP_PARAMS, sizeof(float), hipMemcpyDeviceToHost, c.stream));
     AMFMM_HIP(hipStreamSynchronize(c.stream));
   }
