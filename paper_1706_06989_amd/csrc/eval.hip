@@ -31,7 +31,6 @@ namespace amfmm {
 namespace {
 
 constexpr int kBS = 256;
-constexpr int kWaves = kBS / 64;
 
 // sources per lane summed in FP32 before an FP64 flush (mixed path)
 constexpr int kFarFlush = 8;
@@ -156,24 +155,23 @@ __device__ inline void store_local(double* __restrict__ o, const double acc[20],
 // lane reads its own there, slot q of record r holding piece q ^ (r mod 8)
 // (conflict-free); the next 64 records travel while this lane computes.
 // 4M two spheres at theta 0.35, FP64: 13.3 -> 5.7 ms; 16.8M at the benchmark's
-// tolerance, mixed: 256 -> 155 ms.
+// tolerance, mixed: 256 -> 155 ms.  One wave per workgroup, so that none waits
+// for a neighbour's longer list: 5.6 and 147 ms.
 // (mixed TC at four waves a SIMD spills 18 registers: 167 ms)
 template <int VARIANT, bool MIXED>
-__global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(MIXED && VARIANT ? 3 : 4)))
-k_far_rec(int32_t c_lo, int32_t nc, const void* __restrict__ recs, const int64_t* __restrict__ fstart,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MIXED && VARIANT ? 3 : 4)))
+k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict__ fstart,
           const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, double* __restrict__ loc,
           unsigned long long* clock) {
   take_time(clock);
   using Rec = typename std::conditional<MIXED, FarRec, FarRec64>::type;
   const Rec* __restrict__ rec = (const Rec*)recs;
-  __shared__ double2 lds[kWaves][64 * 8];
-  const int lane = threadIdx.x & 63;
-  const int32_t Xi = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6)));
-  if (Xi >= nc) return;
+  __shared__ double2 buf[64 * 8];
+  const int lane = threadIdx.x;
+  const int32_t Xi = (int32_t)xcd_block(blockIdx.x, gridDim.x);
   const int32_t X = c_lo + Xi;
   const int32_t cnt = uniform(fcount[X]);
   const int32_t* __restrict__ src = fsrc + fstart[X];
-  double2* buf = lds[threadIdx.x >> 6];
   const Rec& rx = rec[X];
   // the target's side in scalar registers
   const double gx[3] = {uniform_f64(rx.z[0]), uniform_f64(rx.z[1]), uniform_f64(rx.z[2])};
@@ -252,14 +250,13 @@ k_far_rec(int32_t c_lo, int32_t nc, const void* __restrict__ recs, const int64_t
 }
 
 template <int VARIANT, bool MIXED>
-__global__ void __launch_bounds__(kBS) k_far(int32_t c_lo, int32_t nc, const double4* __restrict__ geo, const double* __restrict__ mom,
+__global__ void __launch_bounds__(64) k_far(int32_t c_lo, const double4* __restrict__ geo, const double* __restrict__ mom,
                                              const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount,
                                              const int32_t* __restrict__ fsrc, double* __restrict__ loc, double eps2,
                                              unsigned long long* clock) {
   take_time(clock);
-  const int lane = threadIdx.x & 63;
-  const int32_t Xi = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6)));
-  if (Xi >= nc) return;
+  const int lane = threadIdx.x;
+  const int32_t Xi = (int32_t)xcd_block(blockIdx.x, gridDim.x);
   const int32_t X = c_lo + Xi;
   const int32_t cnt = fcount[X];
   const int64_t st = fstart[X];
@@ -420,20 +417,19 @@ void far_field(Ctx& c, int32_t c_lo, int32_t c_hi) {
     order_far(c, c_lo, c_hi, loc);
     return;
   }
-  dim3 grid(blocks_for(nc, kWaves));
   if (use_records(c)) {
     ++c.far_launches;
     const bool tc = c.opt.variant == AMFMM_TC;
     auto kern = c.opt.precision == AMFMM_MIXED ? (tc ? k_far_rec<AMFMM_TC, true> : k_far_rec<AMFMM_UC, true>)
                                                : (tc ? k_far_rec<AMFMM_TC, false> : k_far_rec<AMFMM_UC, false>);
-    hipLaunchKernelGGL(kern, grid, dim3(kBS), 0, c.stream, c_lo, nc, (const void*)c.farrec.p,
+    hipLaunchKernelGGL(kern, dim3(nc), dim3(64), 0, c.stream, c_lo, (const void*)c.farrec.p,
                        (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc,
                        clock_word(c));
     AMFMM_HIP(hipGetLastError());
     return;
   }
   auto args = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, dim3(kBS), 0, c.stream, c_lo, nc, (const double4*)c.geo.p, (const double*)c.mom.p,
+    hipLaunchKernelGGL(kern, dim3(nc), dim3(64), 0, c.stream, c_lo, (const double4*)c.geo.p, (const double*)c.mom.p,
                        (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc,
                        c.opt.softening * c.opt.softening, clock_word(c));
   };

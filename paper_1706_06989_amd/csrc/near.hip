@@ -2,7 +2,10 @@
 // fused with the evaluation of the far-field coefficients at each particle and
 // the scatter back to caller order.
 //
-// One wave per target leaf.  Each lane holds K targets in registers
+// One wave per target leaf, and per workgroup: lists differ, and four waves in
+// a workgroup hold its LDS and registers until the longest is done (one instead
+// of four: 262144 particles at the benchmark's tolerance 17.0 -> 12.8 ms, 16.8M
+// 196 -> 165, 4M two spheres at FP64 11.6 -> 10.2).  Each lane holds K targets in registers
 // (register blocking: one source load feeds K interactions) and a slice of
 // the sources; lanes = (target group g, slice s), 64 / groups slices per group
 // (any count: the partial sums of a group reduce over a fixed tree into its
@@ -613,11 +616,11 @@ __global__ void __launch_bounds__(kBS) k_near_cut(int32_t nleaves, const int32_t
 }
 
 // blocks that run segments, ahead of the blocks of whole leaves
-constexpr int kUnitBlocks = 1024;
+constexpr int kUnitBlocks = 4096;
 
 // leaves == nullptr: the targets are the leaves among cells [c_lo, c_lo + nleaves)
 template <bool MIXED, bool SOFT>
-__global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(4))) k_near(int32_t nleaves, const int32_t* __restrict__ leaves, int32_t c_lo,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_near(int32_t nleaves, const int32_t* __restrict__ leaves, int32_t c_lo,
                                               const int32_t* __restrict__ nch,
                                               const int32_t* __restrict__ beg, const int32_t* __restrict__ cnt,
                                               const double4* __restrict__ pos, const double4* __restrict__ geo,
@@ -625,21 +628,20 @@ __global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(4))) k
                                               const int32_t* __restrict__ ncount, const int32_t* __restrict__ nsrc,
                                               const int64_t* __restrict__ parts, NearOut out, NearPlan plan,
                                               double eps2) {
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x;
   // FP64 staging holds kCap double4 per wave; the mixed path puts 2 kCap
   // float4 offsets in the same bytes
-  __shared__ double4 lds[kWaves][kCap];
-  double4* buf = lds[threadIdx.x >> 6];
+  __shared__ double4 buf[kCap];
   static_assert(kSkip * sizeof(int32_t) <= kCap * sizeof(double4), "skip buffer");
-  // this wave's work: segments u, u + kUnitBlocks kWaves, ... or the target
+  // this wave's work: segments u, u + kUnitBlocks, ... or the target
   // blocks of one leaf (one call site for both: the code is the same)
   const bool seg = blockIdx.x < kUnitBlocks;
   int32_t u = 0, nu = 0, X = 0, tb = 0;
   if (seg) {
-    u = uniform((int32_t)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
+    u = (int32_t)blockIdx.x;
     nu = uniform((int32_t)plan.words[3]);
   } else {
-    const int32_t li = uniform((int32_t)(xcd_block(blockIdx.x - kUnitBlocks, gridDim.x - kUnitBlocks) * kWaves + (threadIdx.x >> 6)));
+    const int32_t li = (int32_t)xcd_block(blockIdx.x - kUnitBlocks, gridDim.x - kUnitBlocks);
     if (li >= nleaves) return;
     X = uniform(leaves ? leaves[li] : c_lo + li);
     if (!leaves && uniform(nch[X]) != 0) return;
@@ -669,7 +671,7 @@ __global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(4))) k
       if (tb >= end) return;
       continue;
     }
-    u += kUnitBlocks * kWaves;
+    u += kUnitBlocks;
   }
 }
 
@@ -769,7 +771,7 @@ void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doub
   auto kern = mixed ? (soft ? k_near<true, true> : k_near<true, false>)
                     : (soft ? k_near<false, true> : k_near<false, false>);
   const NearOut out{as<int32_t>(c.perm), c.opt.G, ax, ay, az, pot};
-  hipLaunchKernelGGL(kern, dim3(kUnitBlocks + blocks_for(count, kWaves)), dim3(kBS), 0, c.stream, count, leaves, c_lo,
+  hipLaunchKernelGGL(kern, dim3(kUnitBlocks + count), dim3(64), 0, c.stream, count, leaves, c_lo,
                      nch, beg, cnt, (const double4*)c.pos4.p, (const double4*)c.geo.p, (const double*)c.loc.p,
                      (const int64_t*)c.near_start.p, (const int32_t*)c.near_count.p, (const int32_t*)c.near_src.p,
                      parts, out, plan, c.opt.softening * c.opt.softening);

@@ -833,9 +833,10 @@ struct ChunkCounts {
   int32_t* kov;
 };
 
-// Siblings are handed the same frontier entries, so the waves of a workgroup
-// take the same chunk of neighbouring siblings rather than neighbouring chunks
-// of one cell: what one wave fetches, the others find in their CU's cache.
+// Siblings are handed the same frontier entries, so neighbouring waves take the
+// same chunk of neighbouring siblings rather than neighbouring chunks of one
+// cell: what one wave fetches, the others find in their XCD's cache (239 instead
+// of 275 ms a pass at 16.8M particles).
 // The k-th wave's cell i and chunk become its place in this order, a
 // permutation inside each group of siblings (all of which have the same number
 // of chunks).  Short chunks end before the two extra dependent loads pay.
@@ -854,9 +855,18 @@ __device__ inline int64_t sibling_order(const TreeView& t, int32_t c0, int32_t n
   return cbase[i] + q / m;
 }
 
+// Threads of a walking workgroup: one wave.  Chunks take very different times,
+// and a workgroup holds its registers and LDS until its last wave ends: with
+// four waves, 2.6 of the 4 each SIMD has room for were in flight; the pass at
+// 262144 / 4M / 16.8M particles took 12.5 / 9.4 / 276 ms, with one 10.9 / 8.6 /
+// 239.  (Four waves taking chunks from a shared counter: 13.4 / 10.1 / 259, the
+// loop costs registers.)  The learned rule's share a copy of the network.
+template <int EXT>
+constexpr int kWalkThreads = EXT == kExtLearned ? kBS : 64;
+
 // GQ: the work queues are in global memory (gq, qcap entries per chunk), else in LDS
 template <int EXT, bool GQ, bool DBG>
-__global__ void __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(EXT == kExtLearned ? 1 : 4)))
+__global__ void __launch_bounds__(kWalkThreads<EXT>) __attribute__((amdgpu_waves_per_eu(EXT == kExtLearned ? 1 : 4)))
 k_walk_stage(TreeView t, int32_t c0, int32_t nl, int64_t kn, int32_t chunk,
                                                     const int32_t* __restrict__ kcell, const int64_t* __restrict__ cbase,
                                                     const int64_t* __restrict__ gbeg, const int32_t* __restrict__ gcnt,
@@ -865,13 +875,13 @@ k_walk_stage(TreeView t, int32_t c0, int32_t nl, int64_t kn, int32_t chunk,
                                                     int32_t* __restrict__ gq, int32_t qcap, unsigned long long* dbg,
                                                     unsigned long long* clock) {
   take_time(clock);
-  __shared__ int32_t queue[GQ ? 1 : kBS / 64][GQ ? 1 : kQ];
+  __shared__ int32_t queue[GQ ? 1 : kWalkThreads<EXT> / 64][GQ ? 1 : kQ];
   __shared__ float model[EXT == kExtLearned ? AMFMM_MLP_MODEL : 1];
   if (EXT == kExtLearned) t.lmodel = stage_model(t.model, model);
   const int lane = threadIdx.x & 63;
   // wave-uniform (readfirstlane): the cell's record and bookkeeping are
   // loaded once per wave into scalar registers
-  int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kBS / 64) + (threadIdx.x >> 6)));
+  int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kWalkThreads<EXT> / 64) + (threadIdx.x >> 6)));
   if (k >= kn) return;
   if (k >= cbase[nl]) {
     if (lane == 0) {
@@ -1032,7 +1042,7 @@ __global__ void __launch_bounds__(kBS) k_walk_compact(TreeView t, int32_t c0, in
 // One wave per chunk whose staging overflowed: walk it again, writing its far
 // and near entries and its children's entries straight to their places.
 template <int EXT>
-__global__ void __launch_bounds__(kBS) k_walk_emit(TreeView t, int32_t c0, int64_t kn, int32_t chunk,
+__global__ void __launch_bounds__(kWalkThreads<EXT>) k_walk_emit(TreeView t, int32_t c0, int64_t kn, int32_t chunk,
                                                    const int32_t* __restrict__ kcell, const int64_t* __restrict__ cbase,
                                                    const int64_t* __restrict__ gbeg, const int32_t* __restrict__ gcnt,
                                                    const int32_t* __restrict__ fy, ChunkScans ex,
@@ -1041,10 +1051,10 @@ __global__ void __launch_bounds__(kBS) k_walk_emit(TreeView t, int32_t c0, int64
                                                    int32_t* __restrict__ near_src, int32_t* __restrict__ fy_n,
                                                    int32_t* __restrict__ fx_n, int32_t* __restrict__ gq,
                                                    int32_t qcap) {
-  __shared__ int32_t queue[kBS / 64][kQ];
+  __shared__ int32_t queue[kWalkThreads<EXT> / 64][kQ];
   __shared__ float model[EXT == kExtLearned ? AMFMM_MLP_MODEL : 1];
   if (EXT == kExtLearned) t.lmodel = stage_model(t.model, model);
-  const int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kBS / 64) + (threadIdx.x >> 6)));
+  const int64_t k = uniform((int32_t)(xcd_block(blockIdx.x, gridDim.x) * (kWalkThreads<EXT> / 64) + (threadIdx.x >> 6)));
   if (k >= kn || k >= cbase[nl] || !kov[k]) return;
   const int32_t i = kcell[k];
   const int32_t X = c0 + i;
@@ -1284,7 +1294,8 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     // [4] chunks out of room, [8..10] spill used, [12..16] debug counters, [20..] the staging layout
     int64_t* tot = w + 13 * K;
     const int32_t* fy = as<int32_t>(c.fy);
-    const unsigned kgrid = blocks_for(kn, kBS / 64);
+    const int wthreads = ext == kExtLearned ? kWalkThreads<kExtLearned> : kWalkThreads<kExtBase>;
+    const dim3 wgrid(blocks_for(kn, wthreads / 64)), wblock(wthreads);
     // few chunks: a larger work queue per wave, in global memory (a chunk's
     // queue never holds more than the tree's cells)
     int32_t* gq = nullptr;
@@ -1334,7 +1345,7 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
     constexpr std::false_type no{};
     hipLaunchKernelGGL(gq ? (debug ? stage_kernel(yes, yes) : stage_kernel(yes, no))
                           : (debug ? stage_kernel(no, yes) : stage_kernel(no, no)),
-                       dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, nl, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
+                       wgrid, wblock, 0, c.stream, t, c0, nl, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
                        (const int32_t*)gcnt, fy, (const StageLayout*)sl_dev, kc, nov, gq, qcap, dbg, clock_word(c));
     ++c.pass_launches;
     mark(c, kPhWalk);
@@ -1388,7 +1399,7 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
       hipLaunchKernelGGL(ext == kExtLearned     ? k_walk_emit<kExtLearned>
                          : ext == kExtMultipole ? k_walk_emit<kExtMultipole>
                                                 : k_walk_emit<kExtBase>,
-                         dim3(kgrid), dim3(kBS), 0, c.stream, t, c0, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
+                         wgrid, wblock, 0, c.stream, t, c0, kn, chunk, kcell, cbase, (const int64_t*)gbeg,
                          (const int32_t*)gcnt, fy, ex, (const int32_t*)kc.kov, nl, c0n, far_base, near_base, far_src,
                          near_src, fy_n, fx_n, gq, qcap);
     AMFMM_HIP(hipGetLastError());
