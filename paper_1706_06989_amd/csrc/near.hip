@@ -331,7 +331,10 @@ __device__ __forceinline__ void near_block(int lane, int32_t tb, int ntc, int64_
       // buffer's first words and taken into lanes before the copy overwrites
       // them), and a slot's entry is a count of the bits up to its own.  (A
       // search over the lanes' prefix sums took six dependent exchanges a
-      // slot.)  Two slots per lane and iteration, both loads in flight.
+      // slot.)  Slots past the fill, up to the next multiple of 64, get its
+      // last particle again: no lane is masked off (165 -> 154 ms at 16.8M
+      // particles).  Two slots per lane and iteration, both loads in flight.
+      static_assert(cap % 64 == 0, "whole groups of slots");
       const int32_t startx = inc - cl, delta = bl - startx;
       uint64_t* words = reinterpret_cast<uint64_t*>(buf);
       if (lane < cap / 64) words[lane] = 0ull;
@@ -341,31 +344,28 @@ __device__ __forceinline__ void near_block(int lane, int32_t tb, int ntc, int64_
       const uint64_t mine = words[lane < cap / 64 ? lane : 0];
       wave_sync();
       const uint32_t mine_lo = (uint32_t)mine, mine_hi = (uint32_t)(mine >> 32);
-      int32_t before = -1;
-      auto entry = [&](int grp) {
-        const uint32_t lo = __builtin_amdgcn_readlane(mine_lo, grp), hi = __builtin_amdgcn_readlane(mine_hi, grp);
-        const uint64_t m = ((uint64_t)hi << 32) | lo;
-        const int32_t e = before + (int32_t)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)) +
-                          (int32_t)((m >> lane) & 1);
+      int32_t before = -1;  // entries that start before the group, less one
+      auto source = [&](int32_t v0) {
+        const uint32_t lo = __builtin_amdgcn_readlane(mine_lo, v0 >> 6), hi = __builtin_amdgcn_readlane(mine_hi, v0 >> 6);
+        const uint64_t m = ((uint64_t)hi << 32) | lo, up = m >> 1;
+        // bits 0 .. lane of m
+        const int32_t e = (int32_t)__builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(up >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)up, before + (int32_t)(m & 1)));
         before += __popcll(m);
-        return e;
+        return (uint32_t)(__shfl(delta, e, 64) + min(v0 + lane, fill - 1));
       };
-      for (int32_t v0 = 0; v0 < fill; v0 += 128) {
-        const int32_t va = v0 + lane, vb = va + 64;
-        const int ea = entry(v0 >> 6), eb = v0 + 64 < fill ? entry((v0 >> 6) + 1) : 0;
-        const int32_t fa = __shfl(delta, ea, 64) + va, fb = __shfl(delta, eb, 64) + vb;
-        double4 pa = make_double4(0.0, 0.0, 0.0, 0.0), pb = pa;
-        if (va < fill) pa = pos[fa];
-        if (vb < fill) pb = pos[fb];
-        if (va < fill) {
-          if (MIXED) buf32[va] = offset32(pa, gx);
-          else buf[va] = pa;
-        }
-        if (vb < fill) {
-          if (MIXED) buf32[vb] = offset32(pb, gx);
-          else buf[vb] = pb;
-        }
+      auto put = [&](int32_t v, const double4 q) {
+        if (MIXED) buf32[v] = offset32(q, gx);
+        else buf[v] = q;
+      };
+      int32_t v0 = 0;
+      for (; v0 + 64 < fill; v0 += 128) {
+        const uint32_t fa = source(v0), fb = source(v0 + 64);
+        const double4 pa = pos[fa], pb = pos[fb];
+        put(v0 + lane, pa);
+        put(v0 + 64 + lane, pb);
       }
+      if (v0 < fill) put(v0 + lane, pos[source(v0)]);
       at += fill;
     } else {
       // a single leaf larger than the buffer (coincident points at the
