@@ -400,6 +400,7 @@ static bool use_records(const Ctx& c) {
 }
 
 void far_prepare(Ctx& c) {
+  if (c.opt.order != 3 && c.ncells > 0) order_pack(c);
   if (!use_records(c) || c.ncells <= 0) return;
   void* rec = ensure(c, c.farrec, sizeof(FarRec) * (size_t)c.ncells);
   hipLaunchKernelGGL(c.opt.precision == AMFMM_MIXED ? k_pack_far<true> : k_pack_far<false>, dim3(blocks_for(c.ncells, kBS)), dim3(kBS), 0, c.stream, c.ncells,

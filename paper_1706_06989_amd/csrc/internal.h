@@ -94,7 +94,7 @@ struct Ctx {
   DevBuf fx, fy, fx2, fy2, grp, walkrec, fsave, gsave, counters, gqueue;
   bool frontier_mapped = false;  // fx holds the cell of every frontier entry
   DevBuf stage;  // walk: per-chunk staging windows of one level's terminal pairs
-  DevBuf farrec; // far field, mixed UC/TC: 128-byte source record per cell
+  DevBuf farrec; // far field, UC/TC: source record per cell (128 bytes, order 4: 288)
   // walk: terminal pairs per frontier entry of every level (far, near, split-X
   // bases; -1 = unknown) from the last walk under the rule walk_ratio_key
   std::vector<double> walk_ratio;
@@ -210,6 +210,7 @@ void far_prepare(Ctx& c);
 void far_field(Ctx& c, int32_t c_lo, int32_t c_hi);
 // expansion order 4 (order.hip): moments, far field, push-down, evaluation at the particles
 void order_upward(Ctx& c);
+void order_pack(Ctx& c);
 void order_far(Ctx& c, int32_t c_lo, int32_t c_hi, double* loc);
 void order_push_down(Ctx& c, int32_t c_lo, int32_t c_hi);
 void order_l2p(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, double* ax, double* ay, double* az,
