@@ -172,34 +172,35 @@ __device__ inline void far_correction(const double R[3], double MX, const double
 }
 
 // The correction of eq. 7 (TC) from traceless octupoles (plain -1/R only: the
-// softened D_ijkl is not traceless): D_ijkl is traceless
-// in every pair of indices, so only the traceless part of Q = M_X,jkl M_Y -
-// M_X M_Y,jkl contributes, and with a traceless Q the closed form reduces to
-// t4 R_i (Q.RRR) + 3 t3 Q_ikl R_k R_l.  OXt, O3t: traceless octupoles (10
-// packed components); adds to F[3].
-__device__ inline void far_correction_traceless(const double R[3], double MX, const double OXt[10], double M,
-                                                const double O3t[10], double F[3]) {
+// softened D_ijkl is not traceless): D_ijkl is traceless in every pair of
+// indices, so only the traceless part of Q = M_X,jkl M_Y - M_X M_Y,jkl
+// contributes, and with a traceless Q the closed form reduces to -105/R^9 R_i
+// (Q.RRR) + 45/R^7 Q_ikl R_k R_l.  With the octupoles per mass (oX, oY: the seven
+// components xxx xxy xxz xyy xyz yyy yyz, see FarRec) Q = M_X M_Y (oX - oY), and
+// Q_xzz = -Q_xxx - Q_xyy and its like leave Q_ikl R_k R_l as sums over xx - zz,
+// yy - zz and the mixed products.  Adds Q_jkl D_ijkl / (45 M_X) to F[3]: 64
+// FP64 instructions, the root included (90 with all ten components and the two
+// mass products each; far field at 262144 particles, mixed: 3.9 -> 3.6 ms).
+__device__ inline void far_correction_traceless(const double R[3], const double oX[7], double M, const double oY[7],
+                                                double F[3]) {
   const double r2 = fma(R[0], R[0], fma(R[1], R[1], R[2] * R[2]));
   const double ri = rsqrt_f64(r2);
   const double ri2 = ri * ri;
-  const double t3 = 15.0 * ((ri * ri2) * ri2) * ri2;
-  const double t4 = -7.0 * t3 * ri2;
-  const double RR[6] = {R[0] * R[0], R[0] * R[1], R[0] * R[2], R[1] * R[1], R[1] * R[2], R[2] * R[2]};
-  double Q[10];
+  const double b = (M * ri) * (ri2 * ri2 * ri2);
+  const double xy = R[0] * R[1], xz = R[0] * R[2], yz = R[1] * R[2], zz = R[2] * R[2];
+  const double xx = fma(R[0], R[0], -zz), yy = fma(R[1], R[1], -zz);
+  const double xy2 = xy + xy, xz2 = xz + xz, yz2 = yz + yz;
+  double q[7];
 #pragma unroll
-  for (int u = 0; u < 10; ++u) Q[u] = fma(OXt[u], M, -MX * O3t[u]);
-  const double mult[6] = {1.0, 2.0, 2.0, 1.0, 2.0, 1.0};
-  double v[3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    double s = 0.0;
-#pragma unroll
-    for (int p = 0; p < 6; ++p) s = fma(mult[p] * Q[kT3[p][i]], RR[p], s);
-    v[i] = s;
-  }
+  for (int u = 0; u < 7; ++u) q[u] = oX[u] - oY[u];
+  const double xzz = q[0] + q[3], yzz = q[1] + q[5];  // (negated)
+  const double v[3] = {fma(q[0], xx, fma(q[3], yy, fma(q[1], xy2, fma(q[2], xz2, q[4] * yz2)))),
+                       fma(q[1], xx, fma(q[5], yy, fma(q[3], xy2, fma(q[4], xz2, q[6] * yz2)))),
+                       fma(q[2], xx, fma(q[6], yy, fma(q[4], xy2, fma(-xzz, xz2, -yzz * yz2))))};
   const double s = fma(R[0], v[0], fma(R[1], v[1], R[2] * v[2]));
+  const double a = (b * s) * ((-7.0 / 3.0) * ri2);
 #pragma unroll
-  for (int i = 0; i < 3; ++i) F[i] += fma(t4 * s, R[i], 3.0 * t3 * v[i]);
+  for (int i = 0; i < 3; ++i) F[i] = fma(a, R[i], fma(b, v[i], F[i]));
 }
 
 // traceless part of a packed symmetric octupole (xxx xxy xxz xyy xyz xzz yyy

@@ -38,7 +38,7 @@ constexpr int kFarFlush = 8;
 // Far-field source records of UC and TC at the plain -1/R: 128 bytes, one cache
 // line.  The derivatives are traceless in every index pair, so the traceless
 // octupole (7 components: xxx xxy xxz xyy xyz yyy yyz; xzz, yzz, zzz follow) is
-// all the correction needs.  At FP64 the quadrupole is traceless too (5
+// all the correction needs, here over the cell's mass (masses are positive).  At FP64 the quadrupole is traceless too (5
 // components: xx xy xz yy yz); mixed precision keeps all six, rounded to FP32
 // as they are used.
 struct alignas(128) FarRec {
@@ -63,12 +63,13 @@ __global__ void __launch_bounds__(kBS) k_pack_far(int32_t nc, const double4* __r
   const double* mo = mom + (int64_t)c * kMom;
   double T[10];
   octupole_traceless(mo + 7, T);
-  const double o[7] = {T[0], T[1], T[2], T[3], T[4], T[6], T[7]};
+  const double M = mo[0];
+  const double o[7] = {T[0] / M, T[1] / M, T[2] / M, T[3] / M, T[4] / M, T[6] / M, T[7] / M};
   auto common = [&](auto& r) {
     r.z[0] = g.x;
     r.z[1] = g.y;
     r.z[2] = g.z;
-    r.m = mo[0];
+    r.m = M;
 #pragma unroll
     for (int u = 0; u < 7; ++u) r.o[u] = o[u];
   };
@@ -91,20 +92,6 @@ __global__ void __launch_bounds__(kBS) k_pack_far(int32_t nc, const double4* __r
     r.q[4] = mo[5];
     ((FarRec64*)out)[c] = r;
   }
-}
-
-// the full traceless octupole of a record
-__device__ inline void record_octupole(const double o[7], double T[10]) {
-  T[0] = o[0];
-  T[1] = o[1];
-  T[2] = o[2];
-  T[3] = o[3];
-  T[4] = o[4];
-  T[5] = -o[0] - o[3];
-  T[6] = o[5];
-  T[7] = o[6];
-  T[8] = -o[1] - o[5];
-  T[9] = -o[2] - o[6];
 }
 
 // Sums of 24 values over the wave: each exchange sends the half of the values
@@ -156,8 +143,9 @@ __device__ inline void store_local(double* __restrict__ o, const double acc[20],
 // (conflict-free); the next 64 records travel while this lane computes.
 // 4M two spheres at theta 0.35, FP64: 13.3 -> 5.7 ms; 16.8M at the benchmark's
 // tolerance, mixed: 256 -> 155 ms.  One wave per workgroup, so that none waits
-// for a neighbour's longer list: 5.6 and 147 ms.
-// (mixed TC at four waves a SIMD spills 18 registers: 167 ms)
+// for a neighbour's longer list, and octupoles per mass: 5.2 and 145 ms.
+// (mixed TC at four waves a SIMD spills a register, whose reload waits for the
+// records on their way as well: 228 ms)
 template <int VARIANT, bool MIXED>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MIXED && VARIANT ? 3 : 4)))
 k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict__ fstart,
@@ -175,13 +163,9 @@ k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict
   const Rec& rx = rec[X];
   // the target's side in scalar registers
   const double gx[3] = {uniform_f64(rx.z[0]), uniform_f64(rx.z[1]), uniform_f64(rx.z[2])};
-  const double MX = uniform_f64(rx.m);
-  double OX[10];
-  if (VARIANT) {
-    record_octupole(rx.o, OX);
+  double oX[7];
 #pragma unroll
-    for (int u = 0; u < 10; ++u) OX[u] = uniform_f64(OX[u]);
-  }
+  for (int u = 0; u < 7; ++u) oX[u] = VARIANT ? uniform_f64(rx.o[u]) : 0.0;
   double acc[20], F[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int u = 0; u < 20; ++u) acc[u] = 0.0;
@@ -227,11 +211,7 @@ k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict
         const double Q2[6] = {p[5].y, p[6].x, p[6].y, p[7].x, p[7].y, -p[5].y - p[7].x};
         far_coeffs_traceless(R, M, Q2, acc);
       }
-      if (VARIANT) {
-        double O3[10];
-        record_octupole(o7, O3);
-        far_correction_traceless(R, MX, OX, M, O3, F);
-      }
+      if (VARIANT) far_correction_traceless(R, oX, M, o7, F);
     }
     if (MIXED && ++batch == kFarFlush) {
       batch = 0;
@@ -246,7 +226,7 @@ k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict
 #pragma unroll
     for (int u = 0; u < 20; ++u) acc[u] += (double)a32[u];
   }
-  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -1.0 / (6.0 * MX) : 0.0, lane);
+  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -45.0 / 6.0 : 0.0, lane);
 }
 
 template <int VARIANT, bool MIXED>
