@@ -204,8 +204,8 @@ int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32
 void group_arrays(Ctx& c, int64_t** gbeg, int32_t** gcnt);  // current level's groups
 
 // ---- eval.hip ----
-// mixed precision, UC and TC: one 128-byte source record per cell for the far
-// field (after the moments)
+// UC and TC of the plain -1/R, and order 4: the far field's source records, one
+// per cell (after the moments)
 void far_prepare(Ctx& c);
 void far_field(Ctx& c, int32_t c_lo, int32_t c_hi);
 // expansion order 4 (order.hip): moments, far field, push-down, evaluation at the particles

@@ -591,7 +591,8 @@ __device__ inline bool wave_walk(const TreeView& t, int32_t X, const WalkCell& c
   // the pass is bound by the latency of these loads (61 % of the wave time
   // waited before) and by the caches they miss in.  Fetching four lanes to a
   // record through LDS measured slower (294 against 274 ms a pass at 16.8M
-  // particles), five waves a SIMD too (338 against 309: more misses).
+  // particles, four waves a workgroup), five waves a SIMD too (338 against 309:
+  // more misses).
   const bool leafx = EXT != kExtBase && cx.nch == 0;
   int32_t ahead = lane < n ? fy[b + lane] : -1;
   double mmin = 0.0;
