@@ -277,7 +277,10 @@ int amfmm_mlp_train(amfmm_ctx* ctx, int64_t n, const float* feats, const float* 
  *   AMFMM_WALK_WINDOWS=f  scales the walk's staging windows by f in [0, 1]
  *                         (small values force the spill and re-walk paths);
  *   AMFMM_DEBUG_WALK      prints per-level walk statistics to stderr (adds a
- *                         synchronisation per level). */
+ *                         synchronisation per level);
+ *   AMFMM_DEBUG_NEAR      prints how many near-field lists were cut into
+ *                         segments to stderr (adds a synchronisation per call;
+ *                         not in an allocation-free solve). */
 
 /* ---- introspection (host buffers owned by the caller; synchronising) ---- */
 /* counts[0..11] = cells, depth, far-field pairs, near-field pairs (unordered,

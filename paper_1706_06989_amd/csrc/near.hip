@@ -33,6 +33,9 @@
 // holds them to far below FP64 resolution).  The slices of a target are
 // reduced the same way; the compensation is added back once, before L2P.
 // L2P and the output stay FP64.
+#include <cstdio>
+#include <cstdlib>
+
 #include "device_math.h"
 #include "internal.h"
 
@@ -188,7 +191,7 @@ __device__ inline float4 offset32(const double4 p, const double4 c) {
 // Targets per lane (1, 2 or 4) for a block of ntc <= 64 targets: the fewest
 // lane steps, a step over one source costing about 19 operations per target
 // and 3 of its own (ties: more targets per lane).
-__device__ inline int targets_per_lane(int ntc) {
+__host__ __device__ constexpr int targets_per_lane(int ntc) {
   int best = kTGMax, bnsl = 64 / ((ntc + kTGMax - 1) / kTGMax);
   for (int k = 2; k >= 1; k >>= 1) {
     const int nsl = 64 / ((ntc + k - 1) / k);
@@ -500,11 +503,20 @@ __device__ __forceinline__ void near_targets(int lane, int32_t tb, int ntc, int6
 }
 
 // Lane steps (in instructions) one wave takes over nsp sources with ntc targets.
-__device__ inline int64_t near_cost(int ntc, int64_t nsp) {
+__host__ __device__ constexpr int64_t near_cost(int ntc, int64_t nsp) {
   const int K = targets_per_lane(ntc);
   const int nsl = 64 / ((ntc + K - 1) / K);
   return nsp * (19 * K + 3) / nsl;
 }
+
+// 64 targets cost the least a target
+constexpr int64_t kCostUnit = 64 * 63 * 61 * 60;  // sources, to see past near_cost's rounding
+constexpr bool full_blocks_cost_least() {
+  for (int t = 1; t <= 64; ++t)
+    if (t * near_cost(64, kCostUnit) > 64 * near_cost(t, kCostUnit) + 64) return false;
+  return true;
+}
+static_assert(full_blocks_cost_least(), "room for partial sums");
 
 // One segment of one target block's list; the block itself has seg = 0.
 struct NearUnit {
@@ -518,8 +530,13 @@ struct NearUnit {
 // segment's own start and end outweigh its work (about 3000 instructions, 5 us).
 // A block of c > 2 shares gets at most 3/2 c segments, and a leaf's blocks (all
 // cut like its first, the dearest) cost at least half of what that counts, so
-// there are at most 3 shares' worth of segments; a leaf whose partial sums
-// have no room is left whole.
+// there are at most 3 shares' worth of segments.  A leaf's targets cost at least
+// as much each as those of a full block, so a leaf of t targets, cut like a block
+// of c, costs c t / 64 and gets 3/2 c t / share partial sums: 64 times 3/2 hold
+// the whole phase's (while no leaf holds more than n_crit particles, as above the
+// deepest level, n_crit of them do).  near_room adds what rounding down in the
+// costs and the share takes away, so that no request is refused: which lists are
+// cut, and with it how they are summed, depends on the lists alone.
 constexpr int64_t kMinShare = 4000;
 struct NearPlan {
   NearUnit* units;
@@ -588,7 +605,7 @@ __global__ void __launch_bounds__(kBS) k_near_cut(int32_t nleaves, const int32_t
       if (c0 > 2 * share) {
         const int64_t nseg = (c0 + share - 1) / share;
         const int64_t np = nseg * nt;
-        // partial sums first: a leaf they have no room for stays whole
+        // (always room: see near_room)
         const unsigned long long at = atomicAdd(&plan.words[5], (unsigned long long)np);
         if ((int64_t)at + np <= plan.max_parts) {
           cut = true;
@@ -613,6 +630,16 @@ __global__ void __launch_bounds__(kBS) k_near_cut(int32_t nleaves, const int32_t
       if (u.seg == 0) plan.groups[g0 + b] = u;
     }
   }
+}
+
+// Room for the cut lists' segments and partial sums (the bounds above).
+struct NearRoom {
+  size_t units, parts;
+};
+NearRoom near_room(const Ctx& c, int64_t shares) {
+  const double s = (double)shares * (1.0 + 1.0 / 512.0);
+  const int targets = c.depth < kMaxLevel ? std::min(64, c.opt.n_crit) : 64;
+  return NearRoom{(size_t)(3.0 * s) + 64, (size_t)(1.5 * targets * s) + 64};
 }
 
 // blocks that run segments, ahead of the blocks of whole leaves
@@ -742,9 +769,10 @@ void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doub
   // memory is the caller's arena); without it every list stays whole
   NearPlan plan{};
   plan.shares = c.arena ? 2048 : 16384;
-  plan.max_parts = plan.shares * 3 / 2 * std::min(64, c.opt.n_crit);
-  const size_t units = 4 * (size_t)plan.shares, pb = sizeof(NearPart) * (size_t)plan.max_parts;
-  const size_t ub = sizeof(NearUnit) * units, gb = ub;
+  const NearRoom room = near_room(c, plan.shares);
+  plan.max_parts = (int64_t)room.parts;
+  const size_t pb = sizeof(NearPart) * room.parts;
+  const size_t ub = sizeof(NearUnit) * room.units, gb = ub;
   char* w = nullptr;
   try {
     w = (char*)ensure(c, c.near_plan, pb + ub + gb + (size_t)count);
@@ -779,6 +807,13 @@ void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doub
     hipLaunchKernelGGL(mixed ? k_near_join<true> : k_near_join<false>, dim3(kJoinBlocks), dim3(kBS), 0, c.stream, beg,
                        cnt, (const double4*)c.pos4.p, (const double4*)c.geo.p, (const double*)c.loc.p, out, plan);
   AMFMM_HIP(hipGetLastError());
+  if (getenv("AMFMM_DEBUG_NEAR") && !c.arena) {
+    unsigned long long h[6];
+    AMFMM_HIP(hipMemcpyAsync(h, plan.words, sizeof(h), hipMemcpyDeviceToHost, c.stream));
+    sync(c);
+    fprintf(stderr, "near field: targets %d cut blocks %llu segments %llu of %zu partial sums %llu of %zu\n", count,
+            h[4], h[3], plan.cut ? room.units : 0, h[5], plan.cut ? room.parts : 0);
+  }
   if (c.opt.order != 3) order_l2p(c, leaves, c_lo, count, ax, ay, az, pot);
 }
 
