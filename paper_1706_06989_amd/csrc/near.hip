@@ -509,7 +509,7 @@ __host__ __device__ constexpr int64_t near_cost(int ntc, int64_t nsp) {
   return nsp * (19 * K + 3) / nsl;
 }
 
-// 64 targets cost the least a target
+// 64 targets cost the least a target, and what one target and source cost at most
 constexpr int64_t kCostUnit = 64 * 63 * 61 * 60;  // sources, to see past near_cost's rounding
 constexpr bool full_blocks_cost_least() {
   for (int t = 1; t <= 64; ++t)
@@ -517,6 +517,15 @@ constexpr bool full_blocks_cost_least() {
   return true;
 }
 static_assert(full_blocks_cost_least(), "room for partial sums");
+constexpr double most_cost() {
+  double v = 0.0;
+  for (int t = 1; t <= 64; ++t) {
+    const double w = (double)(near_cost(t, kCostUnit) + 1) / ((double)t * (double)kCostUnit);
+    v = w > v ? w : v;
+  }
+  return v;
+}
+constexpr double kMostCost = most_cost();
 
 // One segment of one target block's list; the block itself has seg = 0.
 struct NearUnit {
@@ -632,12 +641,15 @@ __global__ void __launch_bounds__(kBS) k_near_cut(int32_t nleaves, const int32_t
   }
 }
 
-// Room for the cut lists' segments and partial sums (the bounds above).
+// Room for the cut lists' segments and partial sums (the bounds above), shares
+// at most all / kMinShare of them for a phase that costs `all`: no target meets
+// more than the n particles.
 struct NearRoom {
   size_t units, parts;
 };
 NearRoom near_room(const Ctx& c, int64_t shares) {
-  const double s = (double)shares * (1.0 + 1.0 / 512.0);
+  const double all = kMostCost * (double)c.n * (double)c.n;
+  const double s = std::min((double)shares, all / (double)kMinShare) * (1.0 + 1.0 / 512.0);
   const int targets = c.depth < kMaxLevel ? std::min(64, c.opt.n_crit) : 64;
   return NearRoom{(size_t)(3.0 * s) + 64, (size_t)(1.5 * targets * s) + 64};
 }

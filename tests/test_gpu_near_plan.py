@@ -114,3 +114,21 @@ def test_cut_lists_in_every_solve(variant, order, softening, precision, how, mon
     oacc, opot = orc.solve(*p, theta=theta, n_crit=n_crit, variant=variant, softening=softening, order=order)
     _, _, gabs = orc.direct(*p, softening=softening)
     check(first, np.vstack([oacc, opot[None]]), gabs, precision)
+
+
+@pytest.mark.parametrize("n,n_crit", [(1, 1), (300, 128), (1000, 64), (4096, 25)])
+def test_room_follows_the_problem(n, n_crit, monkeypatch, capfd):
+    """A partial sum takes 48 bytes, a segment 40: a few thousand particles do
+    not hold tens of megabytes for lists that they cannot have."""
+    rng = np.random.default_rng(n)
+    P = to_dev(*rng.standard_normal((3, n)), np.full(n, 1.0 / n))
+    s = amfmm.Solver(n_crit=n_crit)
+    monkeypatch.setenv("AMFMM_DEBUG_NEAR", "1")
+    capfd.readouterr()
+    s.solve_gravity(*P, 0.5)
+    (cut, segments, units, parts, room), = plans(capfd)
+    s.close()
+    assert segments <= units and parts <= room
+    # every list costs less than 0.4 a target and source, a share at least 4000
+    most = 1.01 * 0.4 * n * n / 4000
+    assert units <= 3 * most + 64 and room <= 1.5 * 64 * most + 64, (units, room)
