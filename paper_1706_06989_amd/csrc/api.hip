@@ -65,19 +65,6 @@ static void* arena_take(Ctx& c, size_t bytes, bool top = false) {
   return c.arena + (top ? off + rest : off);
 }
 
-static void* arena_alloc(Ctx& c, size_t bytes) {
-  if (void* p = arena_take(c, bytes)) return p;
-  size_t largest = 0, total = 0;
-  for (const auto& f : c.arena_free) {
-    largest = std::max(largest, f.second);
-    total += f.second;
-  }
-  throw Error(AMFMM_E_OOM, "allocation-free solve: its scratch needs more than the " +
-                               std::to_string(c.arena_cap >> 20) + " MiB static array (request of " +
-                               std::to_string(bytes) + " bytes; " + std::to_string(total) + " bytes free, " +
-                               "largest block " + std::to_string(largest) + ")");
-}
-
 // grow an arena block in place into the free block behind it
 static bool arena_extend(Ctx& c, DevBuf& b, size_t want) {
   const size_t end = (size_t)((char*)b.p - c.arena) + b.cap, more = want - b.cap;
@@ -90,18 +77,69 @@ static bool arena_extend(Ctx& c, DevBuf& b, size_t want) {
   return true;
 }
 
-static void* alloc(Ctx& c, size_t bytes) {
-  if (c.arena) return arena_alloc(c, bytes);
-  if (c.opt.max_bytes > 0 && (int64_t)(c.bytes + bytes) > c.opt.max_bytes)
-    throw Error(AMFMM_E_OOM, "device scratch would exceed max_bytes (" + std::to_string(c.bytes + bytes) + " bytes)");
+// a device block of `bytes` (in an arena a multiple of kArenaAlign), nullptr
+// where there is no room
+static void* try_alloc(Ctx& c, size_t bytes, bool top) {
+  if (c.arena) return arena_take(c, bytes, top);
+  if (c.opt.max_bytes > 0 && (int64_t)(c.bytes + bytes) > c.opt.max_bytes) return nullptr;
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, bytes);
-  if (e != hipSuccess) {
+  if (hipMalloc(&p, bytes) != hipSuccess) {
     (void)hipGetLastError();
-    throw Error(AMFMM_E_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e));
+    return nullptr;
   }
   c.bytes += bytes;
   return p;
+}
+
+// Device memory that only makes a solve faster, given back when another buffer
+// finds no room: the near field's plan (without it no list is cut), then the far
+// field's records (without them it reads the cells' arrays).  These two take the
+// room of those before them only, and an allocation-free solve is run a second
+// time before it gives them back.
+static bool give_back(Ctx& c, const DevBuf& b) {
+  if (c.arena && !c.arena_tight) return false;
+  for (DevBuf* q : {&c.near_plan, &c.farrec}) {
+    if (q == &b) return false;
+    if (q->p) {
+      release(c, *q);
+      return true;
+    }
+  }
+  return false;
+}
+
+[[noreturn]] static void no_room(Ctx& c, size_t bytes) {
+  if (c.arena) {
+    size_t largest = 0, total = 0;
+    for (const auto& f : c.arena_free) {
+      largest = std::max(largest, f.second);
+      total += f.second;
+    }
+    throw Error(AMFMM_E_OOM, "allocation-free solve: its scratch needs more than the " +
+                                 std::to_string(c.arena_cap >> 20) + " MiB static array (request of " +
+                                 std::to_string(bytes) + " bytes; " + std::to_string(total) + " bytes free, " +
+                                 "largest block " + std::to_string(largest) + ")");
+  }
+  if (c.opt.max_bytes > 0 && (int64_t)(c.bytes + bytes) > c.opt.max_bytes)
+    throw Error(AMFMM_E_OOM, "device scratch would exceed max_bytes (" + std::to_string(c.bytes + bytes) + " bytes)");
+  throw Error(AMFMM_E_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed: out of memory");
+}
+
+// A block for b: of `want` bytes, or of `least` where there is no room for more;
+// *got becomes its size.  Under max_bytes `want` has to stay within its lower
+// half: what buffers hold beyond their need then takes a tenth of it at most, and
+// no solve is refused that needs less than nine tenths (four fifths, were the
+// whole of it given away so).
+static void* alloc(Ctx& c, const DevBuf& b, size_t want, size_t least, size_t* got, bool top = false) {
+  if (!c.arena && c.opt.max_bytes > 0 && (int64_t)(c.bytes + want) > c.opt.max_bytes / 2) want = least;
+  do {
+    for (size_t v : {want, least})
+      if (void* p = try_alloc(c, v, top)) {
+        *got = v;
+        return p;
+      }
+  } while (give_back(c, b));
+  no_room(c, least);
 }
 
 size_t free_device_bytes(Ctx& c) {
@@ -118,51 +156,50 @@ size_t free_device_bytes(Ctx& c) {
   return fr;
 }
 
-void* ensure(Ctx& c, DevBuf& b, size_t bytes) {
+static void* ensure(Ctx& c, DevBuf& b, size_t bytes, bool top) {
   if (bytes == 0) bytes = 8;
   if (b.cap >= bytes) return b.p;
   release(c, b);
-  // headroom for regrowth, except in the arena (exact blocks: buffers sized
-  // from the free space would otherwise outgrow it)
-  size_t want = bytes + bytes / 4;
-  if (c.arena) want = (bytes + kArenaAlign - 1) & ~(kArenaAlign - 1);
-  b.p = alloc(c, want);
-  b.cap = want;
+  // headroom for regrowth where there is room for it, except in the arena
+  // (exact blocks: buffers sized from the free space would otherwise outgrow it)
+  size_t least = bytes, want = bytes + bytes / 4;
+  if (c.arena) want = least = (bytes + kArenaAlign - 1) & ~(kArenaAlign - 1);
+  size_t got = 0;
+  b.p = alloc(c, b, want, least, &got, top);
+  b.cap = got;
   return b.p;
 }
 
-void* ensure_top(Ctx& c, DevBuf& b, size_t bytes) {
-  if (!c.arena) return ensure(c, b, bytes);
-  if (b.cap >= bytes) return b.p;
-  release(c, b);
-  const size_t want = (std::max<size_t>(bytes, 8) + kArenaAlign - 1) & ~(kArenaAlign - 1);
-  b.p = arena_take(c, want, true);
-  if (!b.p) b.p = arena_alloc(c, want);  // reports the shortage
-  b.cap = want;
-  return b.p;
+void* ensure(Ctx& c, DevBuf& b, size_t bytes) { return ensure(c, b, bytes, false); }
+void* ensure_top(Ctx& c, DevBuf& b, size_t bytes) { return ensure(c, b, bytes, true); }
+
+void* ensure_if_room(Ctx& c, DevBuf& b, size_t bytes) {
+  try {
+    return ensure(c, b, bytes);
+  } catch (const Error& e) {
+    if (e.code != AMFMM_E_OOM) throw;
+    return nullptr;
+  }
 }
 
 void* ensure_keep(Ctx& c, DevBuf& b, size_t bytes, size_t keep) {
   if (bytes == 0) bytes = 8;
   if (b.cap >= bytes) return b.p;
-  size_t want = bytes + bytes / 4;
-  void* p = nullptr;
+  size_t least = bytes, want = bytes + bytes / 4, got = 0;
   if (c.arena) {
-    // with headroom where there is room for it, else without
-    const size_t exact = (bytes + kArenaAlign - 1) & ~(kArenaAlign - 1);
-    want = c.arena_tight ? exact : (want + kArenaAlign - 1) & ~(kArenaAlign - 1);
-    if (b.p && in_arena(c, b.p) && (arena_extend(c, b, want) || arena_extend(c, b, exact))) return b.p;
-    p = arena_take(c, want);
-    if (!p) want = exact;
+    // (a tight arena: no headroom)
+    least = (least + kArenaAlign - 1) & ~(kArenaAlign - 1);
+    want = c.arena_tight ? least : (want + kArenaAlign - 1) & ~(kArenaAlign - 1);
+    if (b.p && in_arena(c, b.p) && (arena_extend(c, b, want) || arena_extend(c, b, least))) return b.p;
   }
-  if (!p) p = alloc(c, want);
+  void* p = alloc(c, b, want, least, &got);
   if (b.p && keep) AMFMM_HIP(hipMemcpyAsync(p, b.p, std::min(keep, b.cap), hipMemcpyDeviceToDevice, c.stream));
   if (b.p) {
     AMFMM_HIP(hipStreamSynchronize(c.stream));
     release(c, b);
   }
   b.p = p;
-  b.cap = want;
+  b.cap = got;
   return b.p;
 }
 

@@ -375,14 +375,15 @@ void zero_u64(Ctx& c, unsigned long long* p, int n, unsigned long long* clock) {
 // the 128-byte records carry traceless moments, enough for UC and TC of the
 // plain -1/R (the derivatives of a softened one, and eq. 8's tensor, are not
 // traceless)
-static bool use_records(const Ctx& c) {
+static bool has_records(const Ctx& c) {
   return c.opt.variant != AMFMM_TCO && c.opt.softening == 0.0 && c.opt.order == 3;
 }
 
 void far_prepare(Ctx& c) {
   if (c.opt.order != 3 && c.ncells > 0) order_pack(c);
-  if (!use_records(c) || c.ncells <= 0) return;
-  void* rec = ensure(c, c.farrec, sizeof(FarRec) * (size_t)c.ncells);
+  if (!has_records(c) || c.ncells <= 0) return;
+  void* rec = ensure_if_room(c, c.farrec, sizeof(FarRec) * (size_t)c.ncells);
+  if (!rec) return;
   hipLaunchKernelGGL(c.opt.precision == AMFMM_MIXED ? k_pack_far<true> : k_pack_far<false>, dim3(blocks_for(c.ncells, kBS)), dim3(kBS), 0, c.stream, c.ncells,
                      (const double4*)c.geo.p, (const double*)c.mom.p, rec);
   AMFMM_HIP(hipGetLastError());
@@ -398,7 +399,7 @@ void far_field(Ctx& c, int32_t c_lo, int32_t c_hi) {
     order_far(c, c_lo, c_hi, loc);
     return;
   }
-  if (use_records(c)) {
+  if (has_records(c) && c.farrec.p) {
     ++c.far_launches;
     const bool tc = c.opt.variant == AMFMM_TC;
     auto kern = c.opt.precision == AMFMM_MIXED ? (tc ? k_far_rec<AMFMM_TC, true> : k_far_rec<AMFMM_UC, true>)

@@ -94,7 +94,9 @@ struct Ctx {
   DevBuf fx, fy, fx2, fy2, grp, walkrec, fsave, gsave, counters, gqueue;
   bool frontier_mapped = false;  // fx holds the cell of every frontier entry
   DevBuf stage;  // walk: per-chunk staging windows of one level's terminal pairs
-  DevBuf farrec; // far field, UC/TC: source record per cell (128 bytes, order 4: 288)
+  // far field, UC/TC: source record per cell (128 bytes, order 4: 288); empty
+  // where it found no room or was given back
+  DevBuf farrec;
   // walk: terminal pairs per frontier entry of every level (far, near, split-X
   // bases; -1 = unknown) from the last walk under the rule walk_ratio_key
   std::vector<double> walk_ratio;
@@ -154,6 +156,9 @@ void* ensure(Ctx& c, DevBuf& b, size_t bytes);
 // ensure, in an arena from its top end: the walk's transient buffers stay out
 // of the way of the lists that grow beside them
 void* ensure_top(Ctx& c, DevBuf& b, size_t bytes);
+// ensure for a buffer that a solve can do without: nullptr (and an empty buffer)
+// where there is no room
+void* ensure_if_room(Ctx& c, DevBuf& b, size_t bytes);
 // grow keeping the first `keep` bytes
 void* ensure_keep(Ctx& c, DevBuf& b, size_t bytes, size_t keep);
 template <typename T>

@@ -785,13 +785,7 @@ void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doub
   plan.max_parts = (int64_t)room.parts;
   const size_t pb = sizeof(NearPart) * room.parts;
   const size_t ub = sizeof(NearUnit) * room.units, gb = ub;
-  char* w = nullptr;
-  try {
-    w = (char*)ensure(c, c.near_plan, pb + ub + gb + (size_t)count);
-  } catch (const Error& e) {
-    if (e.code != AMFMM_E_OOM) throw;
-  }
-  if (w) {
+  if (char* w = (char*)ensure_if_room(c, c.near_plan, pb + ub + gb + (size_t)count)) {
     plan.parts = (NearPart*)w;
     plan.units = (NearUnit*)(w + pb);
     plan.groups = (NearUnit*)(w + pb + ub);

@@ -385,6 +385,15 @@ constexpr int kCorrPieces = kRecO / 2, kFarPieces = (kRec - kRecZ) / 2;
 static_assert(kRecH + kNL - kMiH <= kRecZ && kRecQ + kMiO - kMiQ == kRecO && kRecO + kMiH - kMiO == kRec && kP == 4,
               "source record");
 
+// value i of a cell's record
+__device__ inline double record_value(int i, const double4* __restrict__ z, const double* __restrict__ m) {
+  if (i < kRecZ) return i - kRecH < kNL - kMiH ? m[kMiH + i - kRecH] : 0.0;
+  if (i < kRecZ + 3) return ((const double*)z)[i - kRecZ];
+  if (i < kRecQ) return m[0];
+  if (i < kRecO) return m[kMiQ + i - kRecQ];
+  return kSign.c[kMiO + i - kRecO] * m[kMiO + i - kRecO];
+}
+
 // (one thread per 16 bytes)
 __global__ void __launch_bounds__(kBS) k_pack_order(int32_t nc, const double4* __restrict__ geo,
                                                     const double* __restrict__ mono, double2* __restrict__ out) {
@@ -392,18 +401,16 @@ __global__ void __launch_bounds__(kBS) k_pack_order(int32_t nc, const double4* _
   const int64_t c = t / (kRec / 2);
   if (c >= nc) return;
   const int p = 2 * (int)(t - c * (kRec / 2));
-  const double* m = mono + c * kNL;
-  double v[2];
+  out[t] = make_double2(record_value(p, geo + c, mono + c * kNL), record_value(p + 1, geo + c, mono + c * kNL));
+}
+
+// PIECES times 16 bytes of the record of cell y, from value FROM on, without the
+// records: where they have no room (the same values, so the same results)
+template <int FROM, int PIECES>
+__device__ __forceinline__ void gather_record(const double4* __restrict__ geo, const double* __restrict__ mono,
+                                              int32_t y, double v[2 * PIECES]) {
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int i = p + u;
-    if (i < kRecZ) v[u] = i - kRecH < kNL - kMiH ? m[kMiH + i - kRecH] : 0.0;
-    else if (i < kRecZ + 3) v[u] = ((const double*)(geo + c))[i - kRecZ];
-    else if (i < kRecQ) v[u] = m[0];
-    else if (i < kRecO) v[u] = m[kMiQ + i - kRecQ];
-    else v[u] = kSign.c[kMiO + i - kRecO] * m[kMiO + i - kRecO];
-  }
-  out[t] = make_double2(v[0], v[1]);
+  for (int i = 0; i < 2 * PIECES; ++i) v[i] = record_value(FROM + i, geo + y, mono + (int64_t)y * kNL);
 }
 
 // 64 records (PIECES times 16 bytes of each, from `from` on) to the wave's LDS,
@@ -475,27 +482,29 @@ __device__ inline int wave_sum40(double v[40], int lane, double out[5]) {
 // the order-3 kernels that run after it, zeros in its loc record (the
 // evaluation at the particles adds this expansion separately).  One wave per
 // workgroup here and in k_corr_order (4M particles, both: 7.8 -> 6.9 ms).
+template <bool REC>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_far_order(
-    int32_t c_lo, const double2* __restrict__ rec, const int64_t* __restrict__ fstart,
-    const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, double* __restrict__ locg,
-    double* __restrict__ loc, double eps2, unsigned long long* clock) {
+    int32_t c_lo, const double2* __restrict__ rec, const double4* __restrict__ geo, const double* __restrict__ mono,
+    const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc,
+    double* __restrict__ locg, double* __restrict__ loc, double eps2, unsigned long long* clock) {
   take_time(clock);
-  __shared__ double2 buf[64 * kFarPieces];
+  __shared__ double2 buf[REC ? 64 * kFarPieces : 1];
   const int lane = threadIdx.x;
   const int32_t X = c_lo + (int32_t)xcd_block(blockIdx.x, gridDim.x);
   const int32_t cnt = uniform(fcount[X]);
   const int32_t* __restrict__ src = fsrc + fstart[X];
   const double2* __restrict__ from = rec + kRecZ / 2;
-  const double* zx = (const double*)(from + (int64_t)X * (kRec / 2));
+  const double* zx = REC ? (const double*)(from + (int64_t)X * (kRec / 2)) : (const double*)(geo + X);
   const double gx[3] = {zx[0], zx[1], zx[2]};
   double L[kNL];
 #pragma unroll
   for (int g = 0; g < kNL; ++g) L[g] = 0.0;
-  int32_t ahead = lane + 64 < cnt ? src[lane + 64] : X;
-  if (cnt > 0) fetch_records<kFarPieces>(from, lane < cnt ? src[lane] : X, lane, buf);
+  int32_t ahead = REC && lane + 64 < cnt ? src[lane + 64] : X;
+  if (REC && cnt > 0) fetch_records<kFarPieces>(from, lane < cnt ? src[lane] : X, lane, buf);
   for (int32_t j0 = 0; j0 < cnt; j0 += 64) {
     double v[2 * kFarPieces];
-    take_record<kFarPieces>(from, src, j0, cnt, X, lane, buf, ahead, v);
+    if (REC) take_record<kFarPieces>(from, src, j0, cnt, X, lane, buf, ahead, v);
+    else gather_record<kRecZ, kFarPieces>(geo, mono, j0 + lane < cnt ? src[j0 + lane] : X, v);
     if (j0 + lane < cnt) {
       const double R[3] = {gx[0] - v[0], gx[1] - v[1], gx[2] - v[2]};
       double D[kNL];
@@ -561,24 +570,27 @@ __device__ inline void corr_force(const double R[3], double eps2, const double* 
 // The correction (TC) of one target cell per wave over the same sources:
 // g_c = F_c / M_X into locg (after k_far_order).  Only the order-(P+1)
 // derivatives and the moments of orders 0, 2 and P enter.
+template <bool REC>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) k_corr_order(
-    int32_t c_lo, const double2* __restrict__ rec, const double* __restrict__ mono, const int64_t* __restrict__ fstart,
-    const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, double* __restrict__ locg, double eps2) {
+    int32_t c_lo, const double2* __restrict__ rec, const double4* __restrict__ geo, const double* __restrict__ mono,
+    const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc,
+    double* __restrict__ locg, double eps2) {
   constexpr int kNQ = num_mi(kP) - num_mi(kP - 1);  // order-P components
-  __shared__ double2 buf[64 * kCorrPieces];
+  __shared__ double2 buf[REC ? 64 * kCorrPieces : 1];
   const int lane = threadIdx.x;
   const int32_t X = c_lo + (int32_t)xcd_block(blockIdx.x, gridDim.x);
   const int32_t cnt = uniform(fcount[X]);
   const int32_t* __restrict__ src = fsrc + fstart[X];
-  const double* zx = (const double*)(rec + (int64_t)X * (kRec / 2)) + kRecZ;
+  const double* zx = REC ? (const double*)(rec + (int64_t)X * (kRec / 2)) + kRecZ : (const double*)(geo + X);
   const double gx[3] = {zx[0], zx[1], zx[2]};
   const double* mx = mono + (int64_t)X * kNL;
   double F[3] = {0.0, 0.0, 0.0};
-  int32_t ahead = lane + 64 < cnt ? src[lane + 64] : X;
-  if (cnt > 0) fetch_records<kCorrPieces>(rec, lane < cnt ? src[lane] : X, lane, buf);
+  int32_t ahead = REC && lane + 64 < cnt ? src[lane + 64] : X;
+  if (REC && cnt > 0) fetch_records<kCorrPieces>(rec, lane < cnt ? src[lane] : X, lane, buf);
   for (int32_t j0 = 0; j0 < cnt; j0 += 64) {
     double v[2 * kCorrPieces];
-    take_record<kCorrPieces>(rec, src, j0, cnt, X, lane, buf, ahead, v);
+    if (REC) take_record<kCorrPieces>(rec, src, j0, cnt, X, lane, buf, ahead, v);
+    else gather_record<0, kCorrPieces>(geo, mono, j0 + lane < cnt ? src[j0 + lane] : X, v);
     if (j0 + lane < cnt) {
       const double R[3] = {gx[0] - v[kRecZ], gx[1] - v[kRecZ + 1], gx[2] - v[kRecZ + 2]};
       double Q[kNQ];
@@ -704,7 +716,8 @@ void order_upward(Ctx& c) {
 }
 
 void order_pack(Ctx& c) {
-  double2* rec = (double2*)ensure(c, c.farrec, sizeof(double) * kRec * (size_t)c.ncells);
+  double2* rec = (double2*)ensure_if_room(c, c.farrec, sizeof(double) * kRec * (size_t)c.ncells);
+  if (!rec) return;
   hipLaunchKernelGGL(k_pack_order, dim3(blocks_for((int64_t)c.ncells * (kRec / 2), kBS)), dim3(kBS), 0, c.stream,
                      c.ncells, (const double4*)c.geo.p, (const double*)c.mono.p, rec);
   AMFMM_HIP(hipGetLastError());
@@ -715,14 +728,18 @@ void order_far(Ctx& c, int32_t c_lo, int32_t c_hi, double* loc) {
   if (nc <= 0) return;
   double* locg = (double*)ensure_keep(c, c.locg, sizeof(double) * kLocGen * (size_t)c.ncells,
                                       sizeof(double) * kLocGen * (size_t)c.ncells);
-  hipLaunchKernelGGL(k_far_order, dim3(nc), dim3(64), 0, c.stream, c_lo, (const double2*)c.farrec.p,
+  const bool recs = c.farrec.p != nullptr;
+  const double eps2 = c.opt.softening * c.opt.softening;
+  hipLaunchKernelGGL(recs ? k_far_order<true> : k_far_order<false>, dim3(nc), dim3(64), 0, c.stream, c_lo,
+                     (const double2*)c.farrec.p, (const double4*)c.geo.p, (const double*)c.mono.p,
                      (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, locg,
-                     loc, c.opt.softening * c.opt.softening, clock_word(c));
+                     loc, eps2, clock_word(c));
   AMFMM_HIP(hipGetLastError());
   if (c.opt.variant != AMFMM_UC) {
-    hipLaunchKernelGGL(k_corr_order, dim3(nc), dim3(64), 0, c.stream, c_lo, (const double2*)c.farrec.p,
-                       (const double*)c.mono.p, (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p,
-                       (const int32_t*)c.far_src.p, locg, c.opt.softening * c.opt.softening);
+    hipLaunchKernelGGL(recs ? k_corr_order<true> : k_corr_order<false>, dim3(nc), dim3(64), 0, c.stream, c_lo,
+                       (const double2*)c.farrec.p, (const double4*)c.geo.p, (const double*)c.mono.p,
+                       (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, locg,
+                       eps2);
     AMFMM_HIP(hipGetLastError());
   }
 }
