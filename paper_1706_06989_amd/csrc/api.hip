@@ -552,10 +552,16 @@ static int build_tree_impl(Ctx& c, int64_t n, const double* x, const double* y, 
   c.st_pending = false;
   amfmm::mark(c, amfmm::kPhValidate);
   amfmm::bbox_start(c, x, y, z, m, n);
-  amfmm::mark(c, amfmm::kPhSort);
-  amfmm::build_keys_sort(c, x, y, z, m, n);
-  amfmm::mark(c, amfmm::kPhTree);
-  const int st = amfmm::build_levels(c);
+  int st = AMFMM_OK;
+  try {
+    amfmm::mark(c, amfmm::kPhSort);
+    amfmm::build_keys_sort(c, x, y, z, m, n);
+    amfmm::mark(c, amfmm::kPhTree);
+    st = amfmm::build_levels(c);
+  } catch (const Error& e) {
+    // bad inputs are reported as such, also where the rest would find no room
+    if (e.code != AMFMM_E_OOM || (st = amfmm::input_status(c)) == AMFMM_OK) throw;
+  }
   if (st == AMFMM_E_NONFINITE) return fail(c, st, "non-finite position or mass");
   if (st != AMFMM_OK) return fail(c, st, "masses must be positive");
   c.have_tree = true;

@@ -188,10 +188,12 @@ void radix_sort(Ctx& c, uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32
 // ---- tree.hip ----
 // bounding box and input checks (enqueued: build_levels reads the result)
 void bbox_start(Ctx& c, const double* x, const double* y, const double* z, const double* m, int64_t n);
+// after bbox_start: synchronises; 0, or the amfmm_status of a non-finite or non-positive input
+int input_status(Ctx& c);
 void build_keys_sort(Ctx& c, const double* x, const double* y, const double* z, const double* m,
                      int64_t n);
-// cells of all levels; synchronises once; returns 0, or the amfmm_status of a
-// non-finite or non-positive input (the keys of such inputs are arbitrary but valid)
+// cells of all levels; synchronises once; returns input_status (the keys of bad
+// inputs are arbitrary but valid)
 int build_levels(Ctx& c);
 
 // ---- moments.hip ----

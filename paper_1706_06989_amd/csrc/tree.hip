@@ -350,6 +350,12 @@ void build_keys_sort(Ctx& c, const double* x, const double* y, const double* z, 
   c.n = n;
 }
 
+int input_status(Ctx& c) {
+  sync(c);
+  const double* box = (const double*)(c.pinned + kPinBox);
+  return box[6] != 0.0 ? AMFMM_E_NONFINITE : (box[7] != 0.0 ? AMFMM_E_INVALID : AMFMM_OK);
+}
+
 int build_levels(Ctx& c) {
   const int32_t n = (int32_t)c.n;
   const int nblk = (int)blocks_for(n, kTile);
@@ -362,10 +368,9 @@ int build_levels(Ctx& c) {
                      info, hist, nblk, clock_word(c));
   hipLaunchKernelGGL(k_tree_scan, dim3((unsigned)rows), dim3(kTile), 0, c.stream, hist, nblk, tot, host);
   AMFMM_HIP(hipGetLastError());
-  sync(c);
+  const int st = input_status(c);
+  if (st != AMFMM_OK) return st;
   const double* box = (const double*)(c.pinned + kPinBox);
-  if (box[6] != 0.0) return AMFMM_E_NONFINITE;
-  if (box[7] != 0.0) return AMFMM_E_INVALID;
   std::copy(box, box + 6, c.box);
   c.level_start.assign(1, 0);
   int32_t nc = 0, nleaves = 0;

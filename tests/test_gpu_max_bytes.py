@@ -93,3 +93,26 @@ def test_caps_that_held(sizes, kw, cap):
     s.close()
     ref.close()
     check(*(torch.stack([v[t] for v in o]).cpu().numpy() for o in (out, want)), gabs, kw.get("precision", amfmm.FP64))
+
+
+@pytest.mark.parametrize("cap", [1 << 12, 1 << 16, 0])
+@pytest.mark.parametrize("n", [100, 300])
+def test_bad_inputs_are_reported_as_such(n, cap):
+    """A cap that refuses the solve does not hide what is wrong with the inputs."""
+    say("bad inputs", n, cap)
+    s = amfmm.Solver(max_bytes=cap)
+    good = to_dev(*W.uniform_cube(n, seed=1))
+    for which, value, code in ((1, np.nan, amfmm.E_NONFINITE), (3, np.inf, amfmm.E_NONFINITE), (3, 0.0, amfmm.E_INVALID),
+                               (3, -1.0, amfmm.E_INVALID)):
+        bad = [v.clone() for v in good]
+        bad[which][n // 2] = value
+        for call in (lambda: s.solve_gravity(*bad, 0.5), lambda: s.build_tree(*bad),
+                     lambda: s.solve_gravity_noalloc(*bad, 0.5, s._outputs(n, True))):
+            with pytest.raises(amfmm.AmfmmError) as e:
+                call()
+            assert e.value.code == code, (which, value)
+    if cap == 1 << 12:
+        with pytest.raises(amfmm.AmfmmError) as e:
+            s.solve_gravity(*good, 0.5)
+        assert e.value.code == amfmm.E_OOM
+    s.close()
