@@ -232,6 +232,13 @@ __device__ inline int32_t wave_incl_scan(int32_t v) {
   return v;
 }
 
+// make this wave's LDS writes visible to its other lanes before they read
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs (block b on XCD
 // b mod 8), each with its own L2.  This bijection on [0, nb) gives each XCD
 // runs of kRun consecutive work blocks (runs dealt round-robin, so the load

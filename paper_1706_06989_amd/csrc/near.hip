@@ -47,13 +47,6 @@ constexpr int kWaves = kBS / 64;
 constexpr int kTGMax = 4; // targets per lane: 1, 2 or 4
 constexpr int kCap = 320; // source particles per wave staged in LDS (4 workgroups per CU)
 
-// make this wave's LDS writes visible to its other lanes before they read
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ inline int pow2floor(int v) { return 1 << (31 - __builtin_clz(v)); }
 
 constexpr int kFlush = 32;  // FP32 terms per lane and target before an FP64 flush

@@ -10,6 +10,7 @@
 // histograms itself, which saves the scan's launches.  Up to kSmall elements one
 // workgroup sorts in LDS, all passes in one launch (the 24 launches of 4096
 // elements took 165 us).
+#include "device_math.h"
 #include "internal.h"
 
 namespace amfmm {
@@ -109,13 +110,13 @@ __global__ void __launch_bounds__(kBS) k_scatter(const uint64_t* __restrict__ ki
     const int d = (int)((key[j] >> shift) & 0xFF);
     const uint64_t m = match_digit(d, valid);
     const int below = __popcll(m & lt);
-    // (LDS operations of one wave run in order: every lane reads before the
-    // first of a digit adds, and the next slab reads after)
+    // every lane reads before the first of a digit adds, and the next slab
+    // reads after
     const int32_t run = cnt[w][d];
     rank[j] = run + below;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     if (valid && below == 0) cnt[w][d] = run + __popcll(m);
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
   __syncthreads();
   {
@@ -179,9 +180,9 @@ __global__ void __launch_bounds__(kSmallBS) k_sort_small(uint64_t* __restrict__ 
       const int below = __popcll(m & lt);
       const int32_t run = cnt[w][d];
       rank[j] = run + below;
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
       if (valid && below == 0) cnt[w][d] = run + __popcll(m);
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
     }
     __syncthreads();
     int32_t all = 0;
