@@ -217,10 +217,41 @@ static DevBuf* all_bufs(Ctx& c, int i) {
 
 static __global__ void k_take_time(unsigned long long* word) { take_time(word); }
 
+// adds the times between words (device clock values) to ms, each under its first's phase
+static void add_times(const Ctx& c, const std::vector<unsigned long long>& words, double* ms) {
+  for (size_t i = 0; i + 1 < words.size(); ++i) {
+    const int ph = c.st_phase[i];
+    // (blocks of two kernels may start in either order)
+    if (ph < kPhEnd && words[i + 1] > words[i]) ms[ph] += (double)(words[i + 1] - words[i]) / (double)c.clock_khz;
+  }
+}
+
+// The words are full: their times go to the context and the last one becomes the
+// first (not while the stream is captured, where no value can be read).
+static bool fold_timeline(Ctx& c) {
+  hipStreamCaptureStatus capture;
+  if (hipStreamIsCapturing(c.stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return false;
+  const size_t n = c.st_phase.size();
+  std::vector<unsigned long long> w(n);
+  AMFMM_HIP(hipMemcpyAsync(w.data(), c.stamps, sizeof(w[0]) * n, hipMemcpyDeviceToHost, c.stream));
+  AMFMM_HIP(hipMemcpyAsync(c.stamps, c.stamps + n - 1, sizeof(w[0]), hipMemcpyDeviceToDevice, c.stream));
+  sync(c);
+  add_times(c, w, c.folded_ms);
+  c.st_phase.assign(1, c.st_phase.back());
+  return true;
+}
+
+static void start_timeline(Ctx& c) {
+  c.st_phase.clear();
+  c.st_pending = false;
+  std::fill(c.folded_ms, c.folded_ms + kPhEnd, 0.0);
+}
+
 void mark(Ctx& c, int phase) {
   if (c.arena) return;  // the allocation-free solve records no times
   if (!c.st_pending) {
-    if (c.st_phase.size() + 1 >= (size_t)kMaxStamps) return;  // (one left for the end)
+    // (one word left for the end)
+    if (c.st_phase.size() + 1 >= (size_t)kMaxStamps && !fold_timeline(c)) return;
     c.st_phase.push_back(phase);
   }
   c.st_phase.back() = phase;
@@ -548,8 +579,7 @@ static int build_tree_impl(Ctx& c, int64_t n, const double* x, const double* y, 
   if (n < 1 || n >= (int64_t)INT32_MAX) return fail(c, AMFMM_E_INVALID, "n must be in [1, 2^31)");
   if (!x || !y || !z || !m) return fail(c, AMFMM_E_INVALID, "null input pointer");
   c.have_tree = c.have_moments = c.have_lists = false;
-  c.st_phase.clear();
-  c.st_pending = false;
+  amfmm::start_timeline(c);
   amfmm::mark(c, amfmm::kPhValidate);
   amfmm::bbox_start(c, x, y, z, m, n);
   int st = AMFMM_OK;
@@ -927,8 +957,7 @@ int amfmm_solve_gravity_noalloc(amfmm_ctx* ctx, int64_t n, const double* x, cons
     } saved(c);
     c.arena = amfmm::device_scratch(c.device);
     c.arena_cap = amfmm::kNoAllocBytes;
-    c.st_phase.clear();
-    c.st_pending = false;
+    amfmm::start_timeline(c);
     // a solve that runs out of room is run once more with the walk's transient
     // buffers held small (more of its chunks are then walked twice)
     for (c.arena_tight = false;; c.arena_tight = true) {
@@ -1120,12 +1149,9 @@ int amfmm_get_phase_times(amfmm_ctx* ctx, double* ms, int32_t cap) {
     // (a phase that no kernel has started yet is left out)
     const size_t words = c.st_phase.size() - (c.st_pending ? 1 : 0);
     const auto w = fetch<unsigned long long>(c, c.stamps, words);
-    double t[amfmm::kPhEnd + 1] = {};
-    for (size_t i = 0; i + 1 < words; ++i) {
-      const int ph = c.st_phase[i];
-      // (blocks of two kernels may start in either order)
-      if (ph >= 0 && ph < amfmm::kPhEnd && w[i + 1] > w[i]) t[ph] += (double)(w[i + 1] - w[i]) / (double)c.clock_khz;
-    }
+    double t[amfmm::kPhEnd] = {};
+    std::copy(c.folded_ms, c.folded_ms + amfmm::kPhEnd, t);
+    add_times(c, w, t);
     // [0..7] phases (the walk including its pass), [8] total, [9] walk pass
     const double pass = t[amfmm::kPhWalkPass];
     t[amfmm::kPhWalk] += pass;

@@ -43,6 +43,12 @@ struct BudgetExceeded : Error {
       throw ::amfmm::Error(AMFMM_E_HIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// phases of a solve (amfmm_get_phase_times order)
+// kPhWalkPass: the walk's one pass over the pairs (its staging kernel), a part
+// of the walk that is also reported on its own
+enum Phase { kPhValidate = 0, kPhSort, kPhTree, kPhMoments, kPhWalk, kPhFar, kPhPush, kPhNear, kPhWalkPass, kPhEnd };
+constexpr int kMaxStamps = 1 << 15;  // clock words of a timeline (see mark)
+
 // Grow-only device buffer owned by a context.
 struct Arena;
 struct DevBuf {
@@ -136,6 +142,7 @@ struct Ctx {
   unsigned long long* stamps = nullptr;  // kMaxStamps device words
   std::vector<int> st_phase;             // phase of every word taken so far
   bool st_pending = false;               // the last word waits for its kernel
+  double folded_ms[kPhEnd] = {};         // times of the timeline's earlier words, where it outgrew them
   int clock_khz = 100000;
   // allocation-free solve: while arena is set, every device buffer is carved
   // from [arena, arena + arena_cap) (a static device array) instead of being
@@ -259,15 +266,10 @@ void direct_sum(Ctx& c, int64_t n, const double* x, const double* y, const doubl
 void balance(Ctx& c, int64_t n, const double* x, const double* y, const double* z,
              const double* m, const double* ax, const double* ay, const double* az, double* out);
 
-// phases of a solve (amfmm_get_phase_times order)
-// kPhWalkPass: the walk's one pass over the pairs (its staging kernel), a part
-// of the walk that is also reported on its own
-enum Phase { kPhValidate = 0, kPhSort, kPhTree, kPhMoments, kPhWalk, kPhFar, kPhPush, kPhNear, kPhWalkPass, kPhEnd };
 // A phase starts: the next kernel given clock_word(c) writes the device clock
 // there as it starts (a phase whose kernels are not launched takes no time).
 // An event per phase costs 3.7 us on the stream, and a solve of ten levels had
 // 28 of them.
-constexpr int kMaxStamps = 1 << 15;  // beyond, the last phase takes the rest
 void mark(Ctx& c, int phase);
 unsigned long long* clock_word(Ctx& c);
 void end_timeline(Ctx& c);  // the last phase ends here
