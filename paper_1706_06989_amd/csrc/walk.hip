@@ -1216,7 +1216,10 @@ static size_t stage_layout(Ctx& c, int lev, int64_t F, int64_t kn, const double*
 
 int64_t walk_levels(Ctx& c, int lev_first, int lev_last, const std::vector<int32_t>& lo,
                     const std::vector<int32_t>& hi, int64_t& far_base, int64_t& near_base) {
-  TreeView t{(const WalkRec*)c.walkrec.p, c.theta, c.theta * c.theta, c.walk_abs_tol, c.walk_mode, c.opt.error_tol,
+  // (an angle whose square is not a normal number gets none: no comparison with
+  // it holds, and every pair is decided in the stated form)
+  const double theta2 = c.theta > 1e-150 ? c.theta * c.theta : NAN;
+  TreeView t{(const WalkRec*)c.walkrec.p, c.theta, theta2, c.walk_abs_tol, c.walk_mode, c.opt.error_tol,
              c.opt.theta_max, c.opt.theta_max * c.opt.theta_max, (const float*)c.model.p, c.opt.learned_min_work,
              c.walk_mode != 0 ? (const double*)c.gmin.p + 3 * (size_t)c.ncells : nullptr, nullptr};
   static const bool debug_env = getenv("AMFMM_DEBUG_WALK") != nullptr;
