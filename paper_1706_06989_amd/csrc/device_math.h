@@ -43,6 +43,19 @@ __device__ inline double newton_step(double r2, double y) {
 __device__ inline double rsqrt_f64_1nr(double r2) { return newton_step(r2, __builtin_amdgcn_rsq(r2)); }
 __device__ inline double rsqrt_f64_1nr_or_zero(double r2) { return newton_step(r2, rsq_or_zero(r2)); }
 
+// Units of the far field's records: lengths of 2^el, the mass of the power of two
+// below the total (root: the root cell's mass).  Scaling by them is exact.
+struct FarUnit {
+  int el = 0, em = 0;
+  FarUnit() = default;
+  __device__ FarUnit(int length, const double* __restrict__ root) : el(length), em(__builtin_amdgcn_frexp_exp(root[0])) {}
+  // into the unit: a length's n-th power, a moment of order n
+  __device__ double length(double v, int n = 1) const { return __builtin_ldexp(v, -n * el); }
+  __device__ double moment(double v, int n) const { return __builtin_ldexp(v, -em - n * el); }
+  // out of it: a local coefficient of order n (1: an acceleration's too)
+  __device__ double coefficient(double v, int n) const { return __builtin_ldexp(v, em - (n + 1) * el); }
+};
+
 // Far-field coefficients of one source (moments M, quadrupole Q2) at R:
 // acc[0] C, acc[1..3] C_k, acc[4..9] C_kl, acc[10..19] C_klm (packed).
 // T = double (FP64 path) or float (mixed path).  The D tensors are written as

@@ -22,6 +22,7 @@
 // cancels M_X,jkl M_Y against M_X M_Y,jkl) stays FP64.  UC and TC of the plain
 // -1/R read each source from one 128-byte record (k_far_rec), the rest from the
 // cells' arrays (k_far).
+#include <cmath>
 #include <type_traits>
 
 #include "device_math.h"
@@ -40,7 +41,11 @@ constexpr int kFarFlush = 8;
 // octupole (7 components: xxx xxy xxz xyy xyz yyy yyz; xzz, yzz, zzz follow) is
 // all the correction needs, here over the cell's mass (masses are positive).  At FP64 the quadrupole is traceless too (5
 // components: xx xy xz yy yz); mixed precision keeps all six, rounded to FP32
-// as they are used.
+// as they are used.  FP64 records are in units of powers of two near the box's
+// side and the total mass (FarUnit), which changes no rounding: in the caller's
+// units M / R^7 leaves the exponent range long before the results do (lengths of
+// 10^18 with masses of 10^-192, say).  FP32 has no range to spare for a unit that
+// fits the box rather than the distances within it.
 struct alignas(128) FarRec {
   double z[3], m;
   double o[7];
@@ -56,7 +61,7 @@ static_assert(sizeof(FarRec) == 128 && sizeof(FarRec64) == 128, "far record");
 
 template <bool MIXED>
 __global__ void __launch_bounds__(kBS) k_pack_far(int32_t nc, const double4* __restrict__ geo,
-                                                  const double* __restrict__ mom, void* __restrict__ out) {
+                                                  const double* __restrict__ mom, int el, void* __restrict__ out) {
   const int32_t c = blockIdx.x * kBS + threadIdx.x;
   if (c >= nc) return;
   const double4 g = geo[c];
@@ -90,6 +95,14 @@ __global__ void __launch_bounds__(kBS) k_pack_far(int32_t nc, const double4* __r
     r.q[2] = mo[3];
     r.q[3] = mo[4] - tr;
     r.q[4] = mo[5];
+    const FarUnit unit(el, mom);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) r.z[u] = unit.length(r.z[u]);
+    r.m = unit.moment(r.m, 0);
+#pragma unroll
+    for (int u = 0; u < 7; ++u) r.o[u] = unit.length(r.o[u], 3);
+#pragma unroll
+    for (int u = 0; u < 5; ++u) r.q[u] = unit.moment(r.q[u], 2);
     ((FarRec64*)out)[c] = r;
   }
 }
@@ -118,8 +131,10 @@ __device__ inline void wave_sum24(double v[24], int lane, double out[3]) {
   }
 }
 
-// a target's coefficients and corrections (F: times cf) from every lane's sums
-__device__ inline void store_local(double* __restrict__ o, const double acc[20], const double F[3], double cf, int lane) {
+// a target's coefficients and corrections (F: times cf) from every lane's sums,
+// out of the unit they were made in
+__device__ inline void store_local(double* __restrict__ o, const double acc[20], const double F[3], double cf, int lane,
+                                   const FarUnit& unit) {
   double v[24], t[3];
 #pragma unroll
   for (int u = 0; u < 20; ++u) v[u] = acc[u];
@@ -130,7 +145,8 @@ __device__ inline void store_local(double* __restrict__ o, const double acc[20],
   const int first = 12 * ((lane >> 5) & 1) + 6 * ((lane >> 4) & 1) + 3 * ((lane >> 3) & 1), k = lane & 7;
   if (k < 3) {
     const double s = k == 0 ? t[0] : (k == 1 ? t[1] : t[2]);
-    o[first + k] = first + k >= 20 ? cf * s : s;
+    const int i = first + k, order = i >= 20 ? 1 : (i >= 10 ? 3 : (i >= 4 ? 2 : (i >= 1 ? 1 : 0)));
+    o[i] = unit.coefficient(i >= 20 ? cf * s : s, order);
   }
 }
 
@@ -149,8 +165,8 @@ __device__ inline void store_local(double* __restrict__ o, const double acc[20],
 template <int VARIANT, bool MIXED>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MIXED && VARIANT ? 3 : 4)))
 k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict__ fstart,
-          const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, double* __restrict__ loc,
-          unsigned long long* clock) {
+          const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, const double* __restrict__ mom, int el,
+          double* __restrict__ loc, unsigned long long* clock) {
   take_time(clock);
   using Rec = typename std::conditional<MIXED, FarRec, FarRec64>::type;
   const Rec* __restrict__ rec = (const Rec*)recs;
@@ -226,7 +242,8 @@ k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict
 #pragma unroll
     for (int u = 0; u < 20; ++u) acc[u] += (double)a32[u];
   }
-  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -45.0 / 6.0 : 0.0, lane);
+  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -45.0 / 6.0 : 0.0, lane,
+              MIXED ? FarUnit() : FarUnit(el, mom));
 }
 
 template <int VARIANT, bool MIXED>
@@ -285,7 +302,7 @@ __global__ void __launch_bounds__(64) k_far(int32_t c_lo, const double4* __restr
       for (int u = 0; u < 20; ++u) acc[u] += (double)a32[u];
     }
   }
-  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -1.0 / (6.0 * MX) : 0.0, lane);
+  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -1.0 / (6.0 * MX) : 0.0, lane, FarUnit());
 }
 
 // loc[c] += Taylor shift of its parent's coefficients to its centre
@@ -379,13 +396,19 @@ static bool has_records(const Ctx& c) {
   return c.opt.variant != AMFMM_TCO && c.opt.softening == 0.0 && c.opt.order == 3;
 }
 
+int length_exponent(const Ctx& c) {
+  double v = c.opt.softening;
+  for (int d = 0; d < 3; ++d) v = std::max(v, c.box[3 + d] - c.box[d]);
+  return v > 0.0 && std::isfinite(v) ? std::ilogb(v) : 0;
+}
+
 void far_prepare(Ctx& c) {
   if (c.opt.order != 3 && c.ncells > 0) order_pack(c);
   if (!has_records(c) || c.ncells <= 0) return;
   void* rec = ensure_if_room(c, c.farrec, sizeof(FarRec) * (size_t)c.ncells);
   if (!rec) return;
   hipLaunchKernelGGL(c.opt.precision == AMFMM_MIXED ? k_pack_far<true> : k_pack_far<false>, dim3(blocks_for(c.ncells, kBS)), dim3(kBS), 0, c.stream, c.ncells,
-                     (const double4*)c.geo.p, (const double*)c.mom.p, rec);
+                     (const double4*)c.geo.p, (const double*)c.mom.p, length_exponent(c), rec);
   AMFMM_HIP(hipGetLastError());
 }
 
@@ -405,8 +428,8 @@ void far_field(Ctx& c, int32_t c_lo, int32_t c_hi) {
     auto kern = c.opt.precision == AMFMM_MIXED ? (tc ? k_far_rec<AMFMM_TC, true> : k_far_rec<AMFMM_UC, true>)
                                                : (tc ? k_far_rec<AMFMM_TC, false> : k_far_rec<AMFMM_UC, false>);
     hipLaunchKernelGGL(kern, dim3(nc), dim3(64), 0, c.stream, c_lo, (const void*)c.farrec.p,
-                       (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, loc,
-                       clock_word(c));
+                       (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p,
+                       (const double*)c.mom.p, length_exponent(c), loc, clock_word(c));
     AMFMM_HIP(hipGetLastError());
     return;
   }

@@ -221,6 +221,7 @@ void group_arrays(Ctx& c, int64_t** gbeg, int32_t** gcnt);  // current level's g
 // UC and TC of the plain -1/R, and order 4: the far field's source records, one
 // per cell (after the moments)
 void far_prepare(Ctx& c);
+int length_exponent(const Ctx& c);  // of the larger of the box's side and the softening (FarUnit)
 void far_field(Ctx& c, int32_t c_lo, int32_t c_hi);
 // expansion order 4 (order.hip): moments, far field, push-down, evaluation at the particles
 void order_upward(Ctx& c);

@@ -23,6 +23,8 @@
 // Evaluated per directed pair (each target its own sources), one wave per
 // target cell, lanes over its sources, fixed-order butterfly sums: the same
 // organisation as the order-3 far field.
+#include <cmath>
+
 #include "device_math.h"
 #include "internal.h"
 
@@ -385,32 +387,38 @@ constexpr int kCorrPieces = kRecO / 2, kFarPieces = (kRec - kRecZ) / 2;
 static_assert(kRecH + kNL - kMiH <= kRecZ && kRecQ + kMiO - kMiQ == kRecO && kRecO + kMiH - kMiO == kRec && kP == 4,
               "source record");
 
-// value i of a cell's record
-__device__ inline double record_value(int i, const double4* __restrict__ z, const double* __restrict__ m) {
-  if (i < kRecZ) return i - kRecH < kNL - kMiH ? m[kMiH + i - kRecH] : 0.0;
-  if (i < kRecZ + 3) return ((const double*)z)[i - kRecZ];
-  if (i < kRecQ) return m[0];
-  if (i < kRecO) return m[kMiQ + i - kRecQ];
-  return kSign.c[kMiO + i - kRecO] * m[kMiO + i - kRecO];
+// value i of a cell's record, in powers of two of the box's side and the total
+// mass (see FarUnit: in the caller's units the correction's M^2 R^8 leaves the
+// exponent range at lengths of 10^18 with masses of 10^96)
+__device__ inline double record_value(int i, const double4* __restrict__ z, const double* __restrict__ m,
+                                      const FarUnit& unit) {
+  if (i < kRecZ) return i - kRecH < kNL - kMiH ? unit.moment(m[kMiH + i - kRecH], 4) : 0.0;
+  if (i < kRecZ + 3) return unit.length(((const double*)z)[i - kRecZ]);
+  if (i < kRecQ) return unit.moment(m[0], 0);
+  if (i < kRecO) return unit.moment(m[kMiQ + i - kRecQ], 2);
+  return kSign.c[kMiO + i - kRecO] * unit.moment(m[kMiO + i - kRecO], 3);
 }
 
 // (one thread per 16 bytes)
 __global__ void __launch_bounds__(kBS) k_pack_order(int32_t nc, const double4* __restrict__ geo,
-                                                    const double* __restrict__ mono, double2* __restrict__ out) {
+                                                    const double* __restrict__ mono, int el,
+                                                    double2* __restrict__ out) {
   const int64_t t = (int64_t)blockIdx.x * kBS + threadIdx.x;
   const int64_t c = t / (kRec / 2);
   if (c >= nc) return;
   const int p = 2 * (int)(t - c * (kRec / 2));
-  out[t] = make_double2(record_value(p, geo + c, mono + c * kNL), record_value(p + 1, geo + c, mono + c * kNL));
+  const FarUnit unit(el, mono);
+  const double* m = mono + c * kNL;
+  out[t] = make_double2(record_value(p, geo + c, m, unit), record_value(p + 1, geo + c, m, unit));
 }
 
 // PIECES times 16 bytes of the record of cell y, from value FROM on, without the
 // records: where they have no room (the same values, so the same results)
 template <int FROM, int PIECES>
 __device__ __forceinline__ void gather_record(const double4* __restrict__ geo, const double* __restrict__ mono,
-                                              int32_t y, double v[2 * PIECES]) {
+                                              int32_t y, const FarUnit& unit, double v[2 * PIECES]) {
 #pragma unroll
-  for (int i = 0; i < 2 * PIECES; ++i) v[i] = record_value(FROM + i, geo + y, mono + (int64_t)y * kNL);
+  for (int i = 0; i < 2 * PIECES; ++i) v[i] = record_value(FROM + i, geo + y, mono + (int64_t)y * kNL, unit);
 }
 
 // 64 records (PIECES times 16 bytes of each, from `from` on) to the wave's LDS,
@@ -485,7 +493,7 @@ __device__ inline int wave_sum40(double v[40], int lane, double out[5]) {
 template <bool REC>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_far_order(
     int32_t c_lo, const double2* __restrict__ rec, const double4* __restrict__ geo, const double* __restrict__ mono,
-    const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc,
+    const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, int el,
     double* __restrict__ locg, double* __restrict__ loc, double eps2, unsigned long long* clock) {
   take_time(clock);
   __shared__ double2 buf[REC ? 64 * kFarPieces : 1];
@@ -494,8 +502,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_
   const int32_t cnt = uniform(fcount[X]);
   const int32_t* __restrict__ src = fsrc + fstart[X];
   const double2* __restrict__ from = rec + kRecZ / 2;
+  const FarUnit unit(el, mono);
   const double* zx = REC ? (const double*)(from + (int64_t)X * (kRec / 2)) : (const double*)(geo + X);
-  const double gx[3] = {zx[0], zx[1], zx[2]};
+  const double gx[3] = {REC ? zx[0] : unit.length(zx[0]), REC ? zx[1] : unit.length(zx[1]),
+                        REC ? zx[2] : unit.length(zx[2])};
   double L[kNL];
 #pragma unroll
   for (int g = 0; g < kNL; ++g) L[g] = 0.0;
@@ -504,7 +514,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_
   for (int32_t j0 = 0; j0 < cnt; j0 += 64) {
     double v[2 * kFarPieces];
     if (REC) take_record<kFarPieces>(from, src, j0, cnt, X, lane, buf, ahead, v);
-    else gather_record<kRecZ, kFarPieces>(geo, mono, j0 + lane < cnt ? src[j0 + lane] : X, v);
+    else gather_record<kRecZ, kFarPieces>(geo, mono, j0 + lane < cnt ? src[j0 + lane] : X, unit, v);
     if (j0 + lane < cnt) {
       const double R[3] = {gx[0] - v[0], gx[1] - v[1], gx[2] - v[2]};
       double D[kNL];
@@ -524,8 +534,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_
   for (int g = 0; g < 40; ++g) v[g] = g < kNL ? L[g] : 0.0;
   static_assert(kNL <= 40 && kLocGen == 40, "sums of 40");
   const int first = wave_sum40(v, lane, t), k = lane & 7;
-  if (k < 5)
-    locg[(int64_t)X * kLocGen + first + k] = k == 0 ? t[0] : (k == 1 ? t[1] : (k == 2 ? t[2] : (k == 3 ? t[3] : t[4])));
+  if (k < 5) {
+    const int i = first + k, order = i >= kMiH ? 4 : (i >= kMiO ? 3 : (i >= kMiQ ? 2 : (i >= 1 ? 1 : 0)));
+    const double s = k == 0 ? t[0] : (k == 1 ? t[1] : (k == 2 ? t[2] : (k == 3 ? t[3] : t[4])));
+    locg[(int64_t)X * kLocGen + i] = unit.coefficient(s, order);
+  }
   if (lane < kLoc) loc[(int64_t)X * kLoc + lane] = 0.0;
   static_assert(kLoc <= 64, "one lane a coefficient");
 }
@@ -573,7 +586,7 @@ __device__ inline void corr_force(const double R[3], double eps2, const double* 
 template <bool REC>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) k_corr_order(
     int32_t c_lo, const double2* __restrict__ rec, const double4* __restrict__ geo, const double* __restrict__ mono,
-    const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc,
+    const int64_t* __restrict__ fstart, const int32_t* __restrict__ fcount, const int32_t* __restrict__ fsrc, int el,
     double* __restrict__ locg, double eps2) {
   constexpr int kNQ = num_mi(kP) - num_mi(kP - 1);  // order-P components
   __shared__ double2 buf[REC ? 64 * kCorrPieces : 1];
@@ -581,29 +594,39 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) k_
   const int32_t X = c_lo + (int32_t)xcd_block(blockIdx.x, gridDim.x);
   const int32_t cnt = uniform(fcount[X]);
   const int32_t* __restrict__ src = fsrc + fstart[X];
-  const double* zx = REC ? (const double*)(rec + (int64_t)X * (kRec / 2)) + kRecZ : (const double*)(geo + X);
-  const double gx[3] = {zx[0], zx[1], zx[2]};
-  const double* mx = mono + (int64_t)X * kNL;
+  const FarUnit unit(el, mono);
+  // the target's record in scalar registers
+  double own[2 * kCorrPieces];
+  if (REC) {
+#pragma unroll
+    for (int i = 0; i < 2 * kCorrPieces; ++i) own[i] = ((const double*)(rec + (int64_t)X * (kRec / 2)))[i];
+  } else {
+    gather_record<0, kCorrPieces>(geo, mono, X, unit, own);
+  }
+#pragma unroll
+  for (int i = 0; i < 2 * kCorrPieces; ++i) own[i] = uniform_f64(own[i]);
+  const double gx[3] = {own[kRecZ], own[kRecZ + 1], own[kRecZ + 2]};
+  const double MX = own[kRecZ + 3];
   double F[3] = {0.0, 0.0, 0.0};
   int32_t ahead = REC && lane + 64 < cnt ? src[lane + 64] : X;
   if (REC && cnt > 0) fetch_records<kCorrPieces>(rec, lane < cnt ? src[lane] : X, lane, buf);
   for (int32_t j0 = 0; j0 < cnt; j0 += 64) {
     double v[2 * kCorrPieces];
     if (REC) take_record<kCorrPieces>(rec, src, j0, cnt, X, lane, buf, ahead, v);
-    else gather_record<0, kCorrPieces>(geo, mono, j0 + lane < cnt ? src[j0 + lane] : X, v);
+    else gather_record<0, kCorrPieces>(geo, mono, j0 + lane < cnt ? src[j0 + lane] : X, unit, v);
     if (j0 + lane < cnt) {
       const double R[3] = {gx[0] - v[kRecZ], gx[1] - v[kRecZ + 1], gx[2] - v[kRecZ + 2]};
       double Q[kNQ];
 #pragma unroll
       for (int q = 0; q < kNQ; ++q) Q[q] = 0.0;
-      // the target's moments stay in scalar registers (wave-uniform loads); the
-      // constant goes with the source moment (products shared between terms)
+      // (the constant goes with the source moment: products shared between terms)
+      auto moment = [](const double* r, int be) {
+        return be == 0 ? r[kRecZ + 3] : (be < kMiO ? r[kRecQ + be - kMiQ] : r[kRecH + be - kMiH]);
+      };
 #pragma unroll
       for (int i = 0; i < kNCorr; ++i) {
         const CorrTerm& c = kCorr.t[i];
-        const double m = c.coef * (c.be == 0 ? v[kRecZ + 3]
-                                             : (c.be < kMiO ? v[kRecQ + c.be - kMiQ] : v[kRecH + c.be - kMiH]));
-        Q[c.q] = fma(mx[c.al], m, Q[c.q]);
+        Q[c.q] = fma(moment(own, c.al), c.coef * moment(v, c.be), Q[c.q]);
       }
       corr_force(R, eps2, Q, F);
     }
@@ -612,9 +635,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) k_
   for (int k = 0; k < 3; ++k) F[k] = wave_sum(F[k]);
   if (lane == 0) {
     double* o = locg + (int64_t)X * kLocGen;
-    const double MX = mx[0];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) o[kNL + k] = F[k] / (24.0 * MX);  // P! M_X
+    for (int k = 0; k < 3; ++k) o[kNL + k] = unit.coefficient(F[k] / (24.0 * MX), 1);  // P! M_X
   }
 }
 
@@ -719,7 +741,7 @@ void order_pack(Ctx& c) {
   double2* rec = (double2*)ensure_if_room(c, c.farrec, sizeof(double) * kRec * (size_t)c.ncells);
   if (!rec) return;
   hipLaunchKernelGGL(k_pack_order, dim3(blocks_for((int64_t)c.ncells * (kRec / 2), kBS)), dim3(kBS), 0, c.stream,
-                     c.ncells, (const double4*)c.geo.p, (const double*)c.mono.p, rec);
+                     c.ncells, (const double4*)c.geo.p, (const double*)c.mono.p, length_exponent(c), rec);
   AMFMM_HIP(hipGetLastError());
 }
 
@@ -729,17 +751,18 @@ void order_far(Ctx& c, int32_t c_lo, int32_t c_hi, double* loc) {
   double* locg = (double*)ensure_keep(c, c.locg, sizeof(double) * kLocGen * (size_t)c.ncells,
                                       sizeof(double) * kLocGen * (size_t)c.ncells);
   const bool recs = c.farrec.p != nullptr;
-  const double eps2 = c.opt.softening * c.opt.softening;
+  const int el = length_exponent(c);
+  const double eps = std::ldexp(c.opt.softening, -el), eps2 = eps * eps;
   hipLaunchKernelGGL(recs ? k_far_order<true> : k_far_order<false>, dim3(nc), dim3(64), 0, c.stream, c_lo,
                      (const double2*)c.farrec.p, (const double4*)c.geo.p, (const double*)c.mono.p,
-                     (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, locg,
-                     loc, eps2, clock_word(c));
+                     (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, el,
+                     locg, loc, eps2, clock_word(c));
   AMFMM_HIP(hipGetLastError());
   if (c.opt.variant != AMFMM_UC) {
     hipLaunchKernelGGL(recs ? k_corr_order<true> : k_corr_order<false>, dim3(nc), dim3(64), 0, c.stream, c_lo,
                        (const double2*)c.farrec.p, (const double4*)c.geo.p, (const double*)c.mono.p,
-                       (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, locg,
-                       eps2);
+                       (const int64_t*)c.far_start.p, (const int32_t*)c.far_count.p, (const int32_t*)c.far_src.p, el,
+                       locg, eps2);
     AMFMM_HIP(hipGetLastError());
   }
 }
