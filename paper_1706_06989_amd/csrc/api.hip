@@ -658,7 +658,7 @@ static void evaluate_all(Ctx& c, double* ax, double* ay, double* az, double* pot
   mark(c, kPhPush);
   push_down_all(c);
   mark(c, kPhNear);
-  near_field(c, (const int32_t*)c.leaves.p, 0, c.nleaves, ax, ay, az, pot);
+  near_field(c, nullptr, ax, ay, az, pot);
   end_timeline(c);
 }
 
@@ -745,7 +745,9 @@ static void solve_batched(Ctx& c, double theta, double* ax, double* ay, double* 
   mark(c, kPhPush);
   for (int l = 1; l < Ls; ++l) push_down(c, c.level_start[l], c.level_start[l + 1]);
   mark(c, kPhNear);
-  for (int l = 0; l < Ls; ++l) near_field(c, nullptr, lo[l], hi[l] - lo[l], ax, ay, az, pot);
+  CellRanges top;
+  for (int l = 0; l < Ls; ++l) top.add(lo[l], hi[l]);
+  near_field(c, &top, ax, ay, az, pot);
   // keep the level-Ls frontier and its groups
   const int64_t FL = c.frontier;
   const int32_t nL = c.level_start[Ls + 1] - c.level_start[Ls];
@@ -825,7 +827,9 @@ static void solve_batched(Ctx& c, double theta, double* ax, double* ay, double* 
     mark(c, kPhPush);
     for (int l = Ls; l <= c.depth; ++l) push_down(c, blo[l], bhi[l]);
     mark(c, kPhNear);
-    for (int l = Ls; l <= c.depth; ++l) near_field(c, nullptr, blo[l], bhi[l] - blo[l], ax, ay, az, pot);
+    CellRanges batch;
+    for (int l = Ls; l <= c.depth; ++l) batch.add(blo[l], bhi[l]);
+    near_field(c, &batch, ax, ay, az, pot);
     x0 = x1;
   }
   end_timeline(c);

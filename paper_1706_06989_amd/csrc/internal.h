@@ -232,10 +232,19 @@ void order_l2p(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doubl
                double* pot);
 void push_down(Ctx& c, int32_t c_lo, int32_t c_hi);  // cells of one level
 void push_down_all(Ctx& c);                         // every level, downwards
-// leaves != nullptr: the first `count` leaves of that list; else the leaves
-// among cells [c_lo, c_lo + count)
-void near_field(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, double* ax, double* ay, double* az,
-                double* pot);
+// a range of cells on each of some levels (a batch of subtrees)
+struct CellRanges {
+  int n = 0;
+  int32_t lo[kMaxLevel + 1], hi[kMaxLevel + 1];
+  void add(int32_t a, int32_t b) {
+    if (b > a) {
+      lo[n] = a;
+      hi[n++] = b;
+    }
+  }
+};
+// all leaves, or the leaves of those ranges
+void near_field(Ctx& c, const CellRanges* ranges, double* ax, double* ay, double* az, double* pot);
 // fills n (<= 64) device words with zero (a kernel, so it can sit in a graph)
 void zero_u64(Ctx& c, unsigned long long* p, int n, unsigned long long* clock = nullptr);
 

@@ -13,6 +13,7 @@ import torch
 
 from oracle import oracle as orc
 from paper_1706_06989_amd import amfmm
+from paper_1706_06989_amd import workloads as W
 from tests.gpu_util import say, to_dev
 from tests.test_gpu_near_segments import core_and_halo
 
@@ -132,3 +133,23 @@ def test_room_follows_the_problem(n, n_crit, monkeypatch, capfd):
     # every list costs less than 0.4 a target and source, a share at least 4000
     most = 1.01 * 0.4 * n * n / 4000
     assert units <= 3 * most + 64 and room <= 1.5 * 64 * most + 64, (units, room)
+
+
+@pytest.mark.parametrize("order", [3, 4])
+def test_one_near_phase_a_batch(order):
+    """One near-field phase for the top levels and one a batch of subtrees, where
+    the far field takes one for the top and one for each of a batch's levels (two
+    at least here)."""
+    p = W.plummer(1 << 17, seed=12)
+    P = to_dev(*p)
+    outs = []
+    for list_bytes in (0, 1 << 20):
+        s = amfmm.Solver(order=order, list_bytes=list_bytes)
+        outs.append(host(s.solve_gravity(*P, 0.7)))
+        c = s.get_counts()
+        if list_bytes:
+            assert c["near_launches"] > 1 and 2 * (c["near_launches"] - 1) <= c["far_launches"] - 1, c
+        s.close()
+    i = W.sample_targets(1 << 17, 256, seed=99)
+    _, _, gabs = orc.direct(*p, i)
+    check(outs[1][:, i], outs[0][:, i], gabs, amfmm.FP64)
