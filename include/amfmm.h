@@ -85,7 +85,9 @@ typedef struct {
   double G;           /* gravitational constant applied to all outputs */
   double error_tol;   /* ESTIMATE / LEARNED / MULTIPOLE: accepted pair error relative to the field scale */
   double theta_max;   /* ESTIMATE / LEARNED / MULTIPOLE: pairs with (R_A+R_B)/d > theta_max always open */
-  int64_t max_bytes;  /* cap on device scratch owned by the context (0 = no cap) */
+  int64_t max_bytes;  /* cap on device scratch owned by the context (0 = no cap); what only
+                         makes a solve faster gives way under it, and results then
+                         agree with those without it to rounding */
   int64_t list_bytes; /* device bytes the interaction lists of one batch may take
                          (0 = automatic: two fifths of the free device memory
                          plus the lists and staging room the context already
@@ -188,7 +190,7 @@ int amfmm_leapfrog(amfmm_ctx* ctx, int64_t n, double* x, double* y, double* z, d
  * pairs may be summed in another order), with every scratch buffer carved from
  * one static device array of 256 MiB that the library holds on each device it
  * runs on until the process ends.  It calls no hipMalloc, hipFree or other
- * allocating routine and records no timing events.  n may be at most 2^18
+ * allocating routine and takes no phase times.  n may be at most 2^18
  * (else AMFMM_E_INVALID); a solve whose scratch (particles, cells, interaction
  * lists, walk staging) would outgrow the array returns AMFMM_E_OOM: near that
  * size, small opening angles or tight error tolerances can (the geometric

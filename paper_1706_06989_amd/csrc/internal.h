@@ -50,7 +50,6 @@ enum Phase { kPhValidate = 0, kPhSort, kPhTree, kPhMoments, kPhWalk, kPhFar, kPh
 constexpr int kMaxStamps = 1 << 15;  // clock words of a timeline (see mark)
 
 // Grow-only device buffer owned by a context.
-struct Arena;
 struct DevBuf {
   void* p = nullptr;
   size_t cap = 0;
@@ -147,7 +146,7 @@ struct Ctx {
   // allocation-free solve: while arena is set, every device buffer is carved
   // from [arena, arena + arena_cap) (a static device array) instead of being
   // allocated (first fit over the free blocks, released blocks merged with
-  // their neighbours), and no timing events are recorded
+  // their neighbours), and no phase times are taken
   char* arena = nullptr;
   size_t arena_cap = 0;
   bool arena_tight = false;  // second attempt of a solve that did not fit

@@ -45,7 +45,9 @@ namespace {
 constexpr int kBS = 256;
 constexpr int kWaves = kBS / 64;
 constexpr int kTGMax = 4; // targets per lane: 1, 2 or 4
-constexpr int kCap = 320; // source particles per wave staged in LDS (4 workgroups per CU)
+// source particles staged in LDS: 10 KB a workgroup of one wave, so 16 of them fit
+// a CU's 160 KB, the four waves a SIMD that the registers allow
+constexpr int kCap = 320;
 
 __device__ inline int pow2floor(int v) { return 1 << (31 - __builtin_clz(v)); }
 
@@ -182,8 +184,11 @@ __device__ inline float4 offset32(const double4 p, const double4 c) {
 }
 
 // Targets per lane (1, 2 or 4) for a block of ntc <= 64 targets: the fewest
-// lane steps, a step over one source costing about 19 operations per target
-// and 3 of its own (ties: more targets per lane).
+// lane steps, a step over one source costing 19 units per target and 3 of its own
+// (ties: more targets per lane).  A fixed rule, one for both precisions: the
+// weights are those of an earlier pair loop (23 instructions at one target per
+// lane, 18.8 at four; now 15.5 and 14.3), and since they order sums of FP32 terms
+// they stay.
 __host__ __device__ constexpr int targets_per_lane(int ntc) {
   int best = kTGMax, bnsl = 64 / ((ntc + kTGMax - 1) / kTGMax);
   for (int k = 2; k >= 1; k >>= 1) {
@@ -461,7 +466,7 @@ __device__ __forceinline__ void near_block(int lane, int32_t tb, int ntc, int64_
       ph[u] += (double)cp[u];
     }
   }
-  // lane s < 4 of group g finishes target g*4 + s with the sums of the
+  // lane s < kTG of group g finishes target g kTG + s with the sums of the
   // group's first lane
   const int t = g * kTG + s;
   double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;

@@ -1,5 +1,5 @@
 // Octree build (Sec. 2): validation + bounding cube, Morton keys, stable sort,
-// gather into sorted double4 particles, and cells level by level.
+// gather into sorted double4 particles, and the cells of all levels at once.
 //
 // Cells are numbered in (level, first particle) order: cells of one level are
 // contiguous and sorted by their key prefix, children of a cell are

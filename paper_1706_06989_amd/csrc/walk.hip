@@ -823,9 +823,6 @@ __device__ inline const float* stage_model(const float* __restrict__ g, float* l
   return lds;
 }
 
-// One wave per chunk of a cell's frontier entries: walk it once, writing its
-// terminal pairs to its staging room, and record its counts (and whether it
-// ran out of room).
 // km .. ks: far, near, split-X, split-X times children, candidate pairs and
 // near particles of every chunk (zeros for k past the level's chunks, whose
 // number the host may know only as the bound kn)
@@ -865,6 +862,9 @@ __device__ inline int64_t sibling_order(const TreeView& t, int32_t c0, int32_t n
 template <int EXT>
 constexpr int kWalkThreads = EXT == kExtLearned ? kBS : 64;
 
+// One wave per chunk of a cell's frontier entries: walk it once, writing its
+// terminal pairs to its staging room, and record its counts (and whether it
+// ran out of room).
 // GQ: the work queues are in global memory (gq, qcap entries per chunk), else in LDS
 template <int EXT, bool GQ, bool DBG>
 __global__ void __launch_bounds__(kWalkThreads<EXT>) __attribute__((amdgpu_waves_per_eu(EXT == kExtLearned ? 1 : 4)))
