@@ -230,7 +230,11 @@ static void add_times(const Ctx& c, const std::vector<unsigned long long>& words
 // first (not while the stream is captured, where no value can be read).
 static bool fold_timeline(Ctx& c) {
   hipStreamCaptureStatus capture;
-  if (hipStreamIsCapturing(c.stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return false;
+  if (hipStreamIsCapturing(c.stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (capture != hipStreamCaptureStatusNone) return false;
   const size_t n = c.st_phase.size();
   std::vector<unsigned long long> w(n);
   AMFMM_HIP(hipMemcpyAsync(w.data(), c.stamps, sizeof(w[0]) * n, hipMemcpyDeviceToHost, c.stream));
