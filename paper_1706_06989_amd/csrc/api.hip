@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(256) k_count_near_pairs(int32_t nc, const int6
 // the number of pairs build_near_pairs would list, counted on the device
 static int64_t count_near_pairs(Ctx& c) {
   if (c.near_pairs_valid) return (int64_t)c.near_pairs_host.size();
-  unsigned long long* t = (unsigned long long*)amfmm::ensure(c, c.counters, 64) + 1;
+  unsigned long long* t = (unsigned long long*)amfmm::ensure(c, c.counters, amfmm::kCounterBytes + amfmm::kRangeBytes) + 1;
   amfmm::zero_u64(c, t, 1);
   hipLaunchKernelGGL(k_count_near_pairs, dim3(amfmm::blocks_for(c.ncells, 256)), dim3(256), 0, c.stream,
                      c.ncells, (const int64_t*)c.near_start.p, (const int32_t*)c.near_count.p,
@@ -650,7 +650,7 @@ int amfmm_walk(amfmm_ctx* ctx, double theta) {
 // (the walk's own are reset when a walk starts)
 static void zero_counters(Ctx& c) {
   c.far_launches = c.near_launches = 0;
-  void* p = amfmm::ensure(c, c.counters, 64);
+  void* p = amfmm::ensure(c, c.counters, amfmm::kCounterBytes + amfmm::kRangeBytes);
   amfmm::zero_u64(c, (unsigned long long*)p, 1);
 }
 

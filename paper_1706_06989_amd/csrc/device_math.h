@@ -43,12 +43,18 @@ __device__ inline double newton_step(double r2, double y) {
 __device__ inline double rsqrt_f64_1nr(double r2) { return newton_step(r2, __builtin_amdgcn_rsq(r2)); }
 __device__ inline double rsqrt_f64_1nr_or_zero(double r2) { return newton_step(r2, rsq_or_zero(r2)); }
 
+template <typename T>
+__device__ inline T uniform(T v) {
+  return (T)__builtin_amdgcn_readfirstlane((int)v);
+}
+
 // Units of the far field's records: lengths of 2^el, the mass of the power of two
 // below the total (root: the root cell's mass).  Scaling by them is exact.
 struct FarUnit {
   int el = 0, em = 0;
   FarUnit() = default;
-  __device__ FarUnit(int length, const double* __restrict__ root) : el(length), em(__builtin_amdgcn_frexp_exp(root[0])) {}
+  __device__ FarUnit(int length, const double* __restrict__ root)
+      : el(length), em(uniform(__builtin_amdgcn_frexp_exp(root[0]))) {}
   // into the unit: a length's n-th power, a moment of order n
   __device__ double length(double v, int n = 1) const { return __builtin_ldexp(v, -n * el); }
   __device__ double moment(double v, int n) const { return __builtin_ldexp(v, -em - n * el); }
@@ -263,11 +269,6 @@ __device__ inline uint32_t xcd_block(uint32_t b, uint32_t nb) {
   if (b >= full) return b;
   const uint32_t x = b % kXcds, q = b / kXcds;
   return ((q / kRun) * kXcds + x) * kRun + q % kRun;
-}
-
-template <typename T>
-__device__ inline T uniform(T v) {
-  return (T)__builtin_amdgcn_readfirstlane((int)v);
 }
 
 __device__ inline double uniform_f64(double v) {

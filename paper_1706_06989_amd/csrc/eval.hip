@@ -176,6 +176,7 @@ k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict
   const int32_t X = c_lo + Xi;
   const int32_t cnt = uniform(fcount[X]);
   const int32_t* __restrict__ src = fsrc + fstart[X];
+  const FarUnit unit = MIXED ? FarUnit() : FarUnit(el, mom);
   const Rec& rx = rec[X];
   // the target's side in scalar registers
   const double gx[3] = {uniform_f64(rx.z[0]), uniform_f64(rx.z[1]), uniform_f64(rx.z[2])};
@@ -242,8 +243,7 @@ k_far_rec(int32_t c_lo, const void* __restrict__ recs, const int64_t* __restrict
 #pragma unroll
     for (int u = 0; u < 20; ++u) acc[u] += (double)a32[u];
   }
-  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -45.0 / 6.0 : 0.0, lane,
-              MIXED ? FarUnit() : FarUnit(el, mom));
+  store_local(loc + (int64_t)X * kLoc, acc, F, VARIANT ? -45.0 / 6.0 : 0.0, lane, unit);
 }
 
 template <int VARIANT, bool MIXED>

@@ -231,6 +231,8 @@ void order_l2p(Ctx& c, const int32_t* leaves, int32_t c_lo, int32_t count, doubl
                double* pot);
 void push_down(Ctx& c, int32_t c_lo, int32_t c_hi);  // cells of one level
 void push_down_all(Ctx& c);                         // every level, downwards
+// bytes of Ctx::counters: the counters, then the near field's ranges
+constexpr size_t kCounterBytes = 64, kRangeBytes = 8 * (kMaxLevel + 1);
 // a range of cells on each of some levels (a batch of subtrees)
 struct CellRanges {
   int n = 0;

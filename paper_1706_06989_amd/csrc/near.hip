@@ -529,20 +529,24 @@ constexpr double kMostCost = most_cost();
 // of cells (unused: first is beyond all).  A phase per range took five launches
 // on each level of every batch of subtrees: 131072 particles at theta 0.7 in
 // batches of 1 MB of lists 1.10 ms in 28 phases, now 0.69 in 11.
-struct NearTargets {
-  const int32_t* leaves;
-  int32_t count;
+struct NearRanges {
   int32_t first[kMaxLevel + 1];  // targets before the range
   int32_t off[kMaxLevel + 1];    // its first cell, less those
+};
+struct NearTargets {
+  const int32_t* leaves;
+  const NearRanges* ranges;  // (in memory: as kernel arguments every wave would load them)
+  int32_t count;
   // target li's cell
   __device__ int32_t cell(int32_t li) const {
     if (leaves) return leaves[li];
-    int32_t o = off[0];
+    int32_t o = ranges->off[0];
 #pragma unroll
-    for (int r = 1; r <= kMaxLevel; ++r) o = li >= first[r] ? off[r] : o;
+    for (int r = 1; r <= kMaxLevel; ++r) o = li >= ranges->first[r] ? ranges->off[r] : o;
     return li + o;
   }
 };
+__global__ void k_near_ranges(NearRanges v, NearRanges* out) { *out = v; }
 
 // One segment of one target block's list; the block itself has seg = 0.
 struct NearUnit {
@@ -787,14 +791,20 @@ __global__ void __launch_bounds__(kBS) k_near_join(const int32_t* __restrict__ b
 }  // namespace
 
 void near_field(Ctx& c, const CellRanges* ranges, double* ax, double* ay, double* az, double* pot) {
-  NearTargets tg{};
-  tg.leaves = ranges ? nullptr : (const int32_t*)c.leaves.p;
-  tg.count = ranges ? 0 : c.nleaves;
-  std::fill(tg.first, tg.first + kMaxLevel + 1, INT32_MAX);
-  for (int r = 0; ranges && r < ranges->n; ++r) {
-    tg.first[r] = tg.count;
-    tg.off[r] = ranges->lo[r] - tg.count;
-    tg.count += ranges->hi[r] - ranges->lo[r];
+  NearTargets tg{ranges ? nullptr : (const int32_t*)c.leaves.p, nullptr, ranges ? 0 : c.nleaves};
+  if (ranges) {
+    NearRanges v{};
+    std::fill(v.first, v.first + kMaxLevel + 1, INT32_MAX);
+    for (int r = 0; r < ranges->n; ++r) {
+      v.first[r] = tg.count;
+      v.off[r] = ranges->lo[r] - tg.count;
+      tg.count += ranges->hi[r] - ranges->lo[r];
+    }
+    if (tg.count <= 0) return;
+    NearRanges* dev = (NearRanges*)((char*)c.counters.p + kCounterBytes);
+    static_assert(sizeof(NearRanges) <= kRangeBytes, "room behind the counters");
+    hipLaunchKernelGGL(k_near_ranges, dim3(1), dim3(1), 0, c.stream, v, dev);
+    tg.ranges = dev;
   }
   const int32_t count = tg.count;
   if (count <= 0) return;
